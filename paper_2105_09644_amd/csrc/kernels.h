@@ -214,6 +214,24 @@ __device__ inline int wave_max_nonneg(int v)
     return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Bitwise or over the 64 lanes, the same on every lane (as wave_max_nonneg).
+__device__ inline int wave_or(int v)
+{
+    v |= dpp_shr1(v);
+    v |= dpp_shr2(v);
+    v |= dpp_shr4(v);
+    v |= dpp_shr8(v);
+    v |= dpp_bc15(v);
+    v |= dpp_bc31(v);
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Set bits of the uniform mask m below this lane.
+__device__ inline int bits_below(uint64_t m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
 // Exclusive prefix sum over the 64 lanes with DPP (no LDS): an inclusive
 // scan inside each row of 16 (row_shr 1, 2, 4, 8 with zeros shifted in), then
 // the row totals carried by the row broadcasts of lanes 15 and 31.

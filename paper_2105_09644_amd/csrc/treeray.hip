@@ -398,11 +398,11 @@ struct RayRows {
     __device__ Real &eps(int k, int i) const { return e[(size_t)k * estride + i]; }
 };
 
-// Accumulation into a ray buffer shared by the waves of a workgroup.  AM: 0 a
-// plain add (one wave), 1 a hardware atomic add, 2 (FP32 in LDS) an add by
-// compare-and-swap on the value's bits: the same correctly rounded FP32 sum
-// in some order, through integer LDS atomics, which this chip runs at a
-// higher rate than FP32 ones when many waves deposit at once.
+// Accumulation into a ray buffer shared by the lanes and waves of a workgroup.
+// AM: 1 a hardware atomic add, 2 (FP32 in LDS) an add by compare-and-swap on
+// the value's bits: the same correctly rounded FP32 sum in some order.  An
+// FP32 atomic add in LDS takes this chip 3 cycles a lane (195 for 64 lanes);
+// three adds by compare-and-swap take 50 to 70 cycles for 64 lanes.
 template <typename Real, int AM>
 __device__ inline void buf_add(Real *p, Real v)
 {
@@ -417,16 +417,14 @@ __device__ inline void buf_add(Real *p, Real v)
                 break;
             old = seen;
         }
-    } else if constexpr (AM != 0) {
-        __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     } else {
-        *p += v;
+        __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 }
 
 // Three adds at once (A, E, V of one ray point): in the compare-and-swap form
 // the three reads and then the three swaps are in flight together, and only a
-// swap that lost a race (another wave changed the value) is repeated.
+// swap that lost a race (another lane changed the value) is repeated.
 template <typename Real, int AM>
 __device__ inline void buf_add3(Real *p0, Real v0, Real *p1, Real v1, Real *p2, Real v2)
 {
@@ -470,27 +468,22 @@ __device__ inline int nearest_copy_shift(int v, int L)
 // outermost emitting point of a ray
 // Per ray, a mask of the points 1 .. N_R - 1 that received emission: ew words
 // (1 for N_R <= 64, else 2) of 64 bits, bit i of word w for point 64 w + i.
-template <bool ATOMIC>
 __device__ inline void mask_or(unsigned long long *p, unsigned long long bits)
 {
-    if constexpr (ATOMIC)
-        __hip_atomic_fetch_or(p, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    else
-        *p |= bits;
+    __hip_atomic_fetch_or(p, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // marks points i0 (if e0) and i0 + 1 (if e1) of the ray whose mask starts at m
-template <bool ATOMIC>
 __device__ inline void mark_points(unsigned long long *m, int i0, bool e0, bool e1)
 {
     const int i1 = i0 + 1;
     const unsigned long long b0 = e0 && i0 >= 1 ? 1ull << (i0 & 63) : 0ull;
     const unsigned long long b1 = e1 ? 1ull << (i1 & 63) : 0ull;
     if ((i0 >> 6) == (i1 >> 6)) {
-        if (b0 | b1) mask_or<ATOMIC>(m + (i0 >> 6), b0 | b1);
+        if (b0 | b1) mask_or(m + (i0 >> 6), b0 | b1);
     } else {
-        if (b0) mask_or<ATOMIC>(m + (i0 >> 6), b0);
-        if (b1) mask_or<ATOMIC>(m + (i1 >> 6), b1);
+        if (b0) mask_or(m + (i0 >> 6), b0);
+        if (b1) mask_or(m + (i1 >> 6), b1);
     }
 }
 
@@ -1094,19 +1087,19 @@ __device__ inline Real emission_weight(int mode, int i, int io, int le, int ne, 
 //  Phase 1, lane = node: loads the node, its mass-centre distance d, the
 //   W_p normalisation over the evaluation points in its support and the W_f,3
 //   bracket of its emission (App. A).
-//  Phase 2, lane = angular sub-point, node by node: the pixel of each of the
-//   s^3 sub-box midpoints of the node's box (the share of pixel k is the count
-//   in k over s^3), then the scatter, with lanes covering (pixel, point) pairs.
-// The evaluation points are r_i = c i^2; the per-node loop recomputes them
-// in registers, so it makes no memory round trip besides its atomics.
+//  Phase 2, lane = (node, pixel) pair: the pairs of all the nodes, laid end to
+//   end, are taken 64 at a time; each lane runs over its node's support points
+//   and adds its pixel's share of A, E and V to each.  A node has few pairs
+//   (mean 2.8 at N_side 2, 5.3 at N_side 4) and few points with a weight (3 to
+//   4), so one node at a time leaves most lanes idle: 154 to 200 vector
+//   instructions per node, against 11 to 27 for the same adds in pairs.
+//   A node's pairs come from the angular table, or from classifying its s^3
+//   sub-points (lane = sub-point; the share of pixel k is the count in k over
+//   s^3), which the whole wave does for one node at a time.
+// The evaluation points are r_i = c i^2; the lanes recompute them in
+// registers, so the loop over them makes no memory round trip besides its
+// atomics.
 // KV: the radial-kernel variants of App. A (otherwise two-point W_f,3 and W_p)
-// This lane's (pixel, count) pair of the angular-table entry t ((first << 7) |
-// pairs; t < 0: none), 0 beyond the entry's pairs
-__device__ inline int table_pairs(const int32_t *pool, int t, int lane)
-{
-    return t >= 0 && lane < (t & 127) ? pool[(t >> 7) + lane] : 0;
-}
-
 template <typename Real, int ATOMIC, bool KV, bool PASS>
 __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned long long *emask, int ew, const int *per,
                           const Real *rt, int nr,
@@ -1115,16 +1108,14 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
                           double &guard_count, double &tab_count)
 {
     using R4 = typename R4T<Real>::T;
-    // emission rows (few writes; in device memory when the A, E, V rows alone fill LDS): hardware atomics
-    constexpr int EATOMIC = ATOMIC != 0 ? 1 : 0;
     const int lane = lane_id();
     const Real xe = (Real)0.86602540378443864676;
     // ---------------- phase 1 ----------------
     int bx = 0, by = 0, bz = 0, ex = 1, ey = 1, ez = 1, lo = 0, nsup = 0, ie = 1;
     Real d = 1, hinv = 1, wscale = 0, fb0 = 1, qa = 0, qe = 0, qv = 0, e0 = 0, e1 = 0;
     // emission spread over several points: mode 1 linear (a + b (i - le) on [le, le + ne)),
-    // 2 a smoothing kernel scaled by ea, 3 the mass fall-back weights; etop: outermost point
-    int emode = 0, le = 0, ne = 0, etop = 1;
+    // 2 a smoothing kernel scaled by ea, 3 the mass fall-back weights
+    int emode = 0, le = 0, ne = 0;
     Real ea = 0, eb = 0, qeps = 0;
     int tab = -1;   // the node's angular-table entry (-1: classify its sub-points)
     const bool mg = KV && a.mass_gauss != 0;
@@ -1174,11 +1165,19 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
         l0 = l0 < 0 ? 0 : l0;
         h0 = h0 > nr - 1 ? nr - 1 : h0;
         Real sum = 0;
-        for (int i = l0; i <= h0; ++i) sum += smooth_kernel<Real>(mg, (rcoef * (Real)(i * i) - d) * hinv);
+        int first = h0 + 1, npos = 0;   // the points with a weight (contiguous: the kernel is positive inside its support)
+        for (int i = l0; i <= h0; ++i) {
+            const Real v = smooth_kernel<Real>(mg, (rcoef * (Real)(i * i) - d) * hinv);
+            sum += v;
+            if (v > (Real)0) {
+                first = i < first ? i : first;
+                ++npos;
+            }
+        }
         if (sum > (Real)0) {
             wscale = frcp(sum);
-            lo = l0;
-            nsup = h0 - l0 + 1;
+            lo = KV ? l0 : first;   // (an emission variant may use a point that rounding leaves outside)
+            nsup = KV ? h0 - l0 + 1 : npos;
         } else if (d >= rt[nr - 1]) {   // no point in the support: linear split over the bracket
             lo = nr - 1;
             nsup = 1;
@@ -1200,13 +1199,11 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
                 for (int i = l0; i <= h0; ++i) {
                     const Real v = smooth_kernel<Real>(ek == K_G, (rcoef * (Real)(i * i) - d) * hinv);
                     es += v;
-                    if (v > (Real)0) etop = i;
                 }
                 emode = 2;
                 ea = frcp(es);
             } else {
                 emode = 3;
-                etop = lo + nsup - 1;
             }
         } else if (A.w > (Real)0) {   // W_f,3 bracket r_i <= d < r_{i+1}, i >= 1
             Real u0 = 1, u1 = 0;
@@ -1226,12 +1223,9 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
             }
             if (ek == K_F3N && sum > (Real)0)
                 n_point_f3(rt, l0, h0, (double)d, (double)h, emode, le, ne, ea, eb);
-            if (emode == 1) {
-                etop = le + ne - 1;
-            } else {
+            if (emode != 1) {
                 e0 = A.w * u0;
                 e1 = A.w * u1;
-                etop = u1 != (Real)0 ? ie + 1 : ie;
             }
         }
     }
@@ -1248,170 +1242,142 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     const Real inv_s3 = (Real)1 / (Real)s3;
     const uint64_t act_mask = __ballot(active);
     // each below 256; bit 24: the node emits (two-point emission weights e0, e1)
-    const int packed = lo | (nsup << 8) | (ie << 16) | ((e0 != (Real)0 || e1 != (Real)0) ? 1 << 24 : 0);
-    const int epacked = emode | (le << 2) | (ne << 10) | (etop << 18);   // 2 + 8 + 8 + 8 bits
-    // lanes of phase 2 cover (pixel slot, support point) pairs, span points per
-    // slot: slot of a lane = (lane mx) >> 16 with mx = ceil(2^16 / span) (exact
-    // for lanes below 64 and span <= 64), G = 64 / span slots per batch
-    int divp;
-    {
-        const int span1 = nsup < 1 ? 1 : (nsup < 64 ? nsup : 64);
-        divp = ((65536 + span1 - 1) / span1) | ((64 / span1) << 17);
-    }
+    const bool emits = e0 != (Real)0 || e1 != (Real)0;
+    const int packed = lo | (nsup << 8) | (ie << 16) | (emits ? 1 << 24 : 0);
+    const int epacked = emode | (le << 2) | (ne << 10);   // 2 + 8 + 8 bits
+    const bool any_emits = __ballot(emits) != 0ull;
     // the W_p normalisation, or (no support point: linear split) minus the
     // bracket weight of the lower point
     const Real wsf = wscale > (Real)0 ? wscale : -fb0;
     // per node (lane = node): sub-box origin relative to the target and sub-box steps, FP32
     const float ox = 0.5f * (float)(2 * bx - tx), oy = 0.5f * (float)(2 * by - ty), oz = 0.5f * (float)(2 * bz - tz);
     const float sx = (float)ex * inv_s, sy = (float)ey * inv_s, sz = (float)ez * inv_s;
-    // the table entries of the next node are fetched while one is mapped
-    int next_kc = table_pairs(a.atab_pool, cnt > 0 ? rdlane(tab, 0) : -1, lane);
-    for (int j = 0; j < cnt; ++j) {
-        // --- angular: slot q (lane q of slot_kc) holds the q-th distinct pixel
-        // and its sub-point count (pixel < 2^16, count <= 64), packed so that one
-        // shuffle hands a slot to the lanes that scatter it; from the table, or
-        // by classifying the node's sub-points ---
-        int nd = 0, slot_kc = 0;
-        const int jt = rdlane(tab, j);
-        const int this_kc = next_kc;
-        next_kc = table_pairs(a.atab_pool, j + 1 < cnt ? rdlane(tab, j + 1) : -1, lane);
-        if (jt >= 0) {
-            if (!PASS) {
-                nd = jt & 127;
-                if (lane < nd) slot_kc = this_kc;
-            } else {
-                // the pass's pixels only, as local ray indices
-                const int nall = jt & 127;
-                for (int q = 0; q < nall; ++q) {
-                    const int kc = __builtin_amdgcn_readlane(this_kc, q);
-                    const int kl = (kc & 0xffff) - k0;
-                    if ((unsigned)kl < (unsigned)np) {
-                        slot_kc = lane == nd ? (kl | (kc & ~0xffff)) : slot_kc;
-                        ++nd;
+    // The table nodes' pairs laid end to end: node n's start at off; lane q of
+    // perm holds the lane of the q-th table node, offc its start.
+    const bool in_tab = tab >= 0;
+    tab_count += in_tab ? 1.0 : 0.0;
+    const uint64_t tmask = __ballot(in_tab);
+    const int n_tab = (int)__popcll(tmask);
+    int ptot = 0;
+    const int off = wave_excl_scan_dpp(in_tab ? tab & 127 : 0, ptot);
+    const int rank = in_tab ? bits_below(tmask) : n_tab + bits_below(~tmask);
+    const int perm = __builtin_amdgcn_ds_permute(rank << 2, lane);
+    const int offc = __shfl(off, perm, 64);
+    uint64_t rem = (cnt < 64 ? (1ull << cnt) - 1ull : ~0ull) & ~tmask;   // nodes to classify
+    int ready = -1, ready_nd = 0, ready_kc = 0;   // a classified node (its pairs in lanes 0 ..) that found no room
+    for (int b = 0; b < ptot || rem != 0ull || ready >= 0; b += 64) {
+        // --- the next 64 pairs: node (its lane) and kc = pixel | count << 16 (pixel < 2^16, count <= 64) ---
+        int node = 0, kc = 0, fill = 0;
+        bool valid = false;
+        if (b < ptot) {
+            // S: the positions 1 .. 63 where a node's pairs start, shifted by one; r0: the node of position 0
+            const int rel = offc - b;
+            const bool is_node = lane < n_tab;
+            const int r0 = (int)__popcll(__ballot(is_node && rel <= 0)) - 1;
+            const uint64_t bit = is_node && rel > 0 && rel < 64 ? 1ull << (rel - 1) : 0ull;
+            const uint64_t S = ((uint64_t)(unsigned)wave_or((int)(bit >> 32)) << 32) | (unsigned)wave_or((int)bit);
+            node = __shfl(perm, r0 + bits_below(S), 64);
+            const int tn = __shfl(tab, node, 64), on = __shfl(off, node, 64);
+            fill = ptot - b < 64 ? ptot - b : 64;
+            valid = lane < fill;
+            if (valid) kc = a.atab_pool[(tn >> 7) + (b + lane - on)];
+            if (PASS) {   // the pass's pixels only, as local ray indices
+                kc -= k0;
+                valid = valid && (unsigned)(kc & 0xffff) < (unsigned)np;
+            }
+        }
+        // nodes without a table entry fill what is left of the 64
+        while (fill < 64 && (rem != 0ull || ready >= 0)) {
+            if (ready < 0) {
+                const int j = __ffsll((unsigned long long)rem) - 1;
+                rem &= rem - 1;
+                // FP32 with a guard band, FP64 inside it: the FP64 classifier's pixel
+                // for every sub-point, in both precisions
+                const float vx = fmaf(ca, rdlane(sx, j), rdlane(ox, j));
+                const float vy = fmaf(cb, rdlane(sy, j), rdlane(oy, j));
+                const float vz = fmaf(cc, rdlane(sz, j), rdlane(oz, j));
+                bool unsure = false;
+                int pix = ang2pix_f(ns, vx, vy, vz, a.guard_tol, unsure);
+                unsure &= active;
+                if (__ballot(unsure)) {
+                    const int jbx = rdlane(bx, j), jby = rdlane(by, j), jbz = rdlane(bz, j);
+                    const int jex = rdlane(ex, j), jey = rdlane(ey, j), jez = rdlane(ez, j);
+                    if (unsure) {
+                        pix = subpoint_pix_d(ns, s, jbx, jby, jbz, jex, jey, jez, tx, ty, tz, ia, ib, ic);
+                        guard_count += 1.0;
                     }
                 }
-            }
-            tab_count += lane == 0 ? 1.0 : 0.0;
-        } else {
-            // FP32 with a guard band, FP64 inside it: the FP64 classifier's pixel
-            // for every sub-point, in both precisions
-            const float vx = fmaf(ca, rdlane(sx, j), rdlane(ox, j));
-            const float vy = fmaf(cb, rdlane(sy, j), rdlane(oy, j));
-            const float vz = fmaf(cc, rdlane(sz, j), rdlane(oz, j));
-            bool unsure = false;
-            int pix = ang2pix_f(ns, vx, vy, vz, a.guard_tol, unsure);
-            unsure &= active;
-            if (__ballot(unsure)) {
-                const int jbx = rdlane(bx, j), jby = rdlane(by, j), jbz = rdlane(bz, j);
-                const int jex = rdlane(ex, j), jey = rdlane(ey, j), jez = rdlane(ez, j);
-                if (unsure) {
-                    pix = subpoint_pix_d(ns, s, jbx, jby, jbz, jex, jey, jez, tx, ty, tz, ia, ib, ic);
-                    guard_count += 1.0;
+                if ((unsigned)pix >= (unsigned)a.npix) {
+                    // cannot happen for a finite direction: reported, never written out of bounds
+                    atomicOr(&a.queue[1], 4);
+                    pix = 0;
                 }
-            }
-            if ((unsigned)pix >= (unsigned)a.npix) {
-                // cannot happen for a finite direction: reported, never written out of bounds
-                atomicOr(&a.queue[1], 4);
-                pix = 0;
-            }
-            // the distinct pixels
-            uint64_t rem = act_mask;
-            while (rem) {
-                const int first = __ffsll((unsigned long long)rem) - 1;
-                const int k = __builtin_amdgcn_readlane(pix, first);
-                const uint64_t m = __ballot(pix == k) & rem;
-                rem &= ~m;
-                // (a pass keeps its own pixels, as local ray indices)
-                if (!PASS || (unsigned)(k - k0) < (unsigned)np) {
-                    const int kc = (k - k0) | ((int)__popcll(m) << 16);   // uniform
-                    slot_kc = lane == nd ? kc : slot_kc;
-                    ++nd;
+                // the distinct pixels
+                uint64_t left = act_mask;
+                ready_nd = 0;
+                while (left) {
+                    const int first = __ffsll((unsigned long long)left) - 1;
+                    const int k = __builtin_amdgcn_readlane(pix, first);
+                    const uint64_t m = __ballot(pix == k) & left;
+                    left &= ~m;
+                    // (a pass keeps its own pixels, as local ray indices)
+                    if (!PASS || (unsigned)(k - k0) < (unsigned)np) {
+                        const int v = (k - k0) | ((int)__popcll(m) << 16);   // uniform
+                        ready_kc = lane == ready_nd ? v : ready_kc;
+                        ++ready_nd;
+                    }
                 }
+                ready = j;
+            }
+            if (fill + ready_nd > 64) break;   // (a node has at most 64 pairs: it fits in the next 64)
+            const int kr = __shfl(ready_kc, (lane - fill) & 63, 64);
+            const bool mine = lane >= fill && lane < fill + ready_nd;
+            kc = mine ? kr : kc;
+            node = mine ? ready : node;
+            valid = valid || mine;
+            fill += ready_nd;
+            ready = -1;
+        }
+        // --- deposit: this lane's pair over its node's support points lo .. lo + n - 1 ---
+        const int npk = __shfl(packed, node, 64);
+        const int jlo = npk & 255, n = valid ? (npk >> 8) & 255 : 0;
+        const Real jd = __shfl(d, node, 64), jhinv = __shfl(hinv, node, 64), jwf = __shfl(wsf, node, 64);
+        const Real ja = __shfl(qa, node, 64), je = __shfl(qe, node, 64), jv = __shfl(qv, node, 64);
+        const int k = kc & 0xffff;
+        const Real wk = (Real)(kc >> 16) * inv_s3;
+        if (any_emits) {
+            // the pixel's share of the emission on the two bracket points, marked in the
+            // ray's mask (the spread forms go with A, E, V below)
+            const Real je0 = __shfl(e0, node, 64), je1 = __shfl(e1, node, 64);
+            if (valid && ((npk >> 24) & 1)) {
+                const int jie = (npk >> 16) & 255;
+                Real *row = &R.eps(k, jie);
+                if (je0 != (Real)0) buf_add<Real, 1>(row, wk * je0);
+                if (je1 != (Real)0) buf_add<Real, 1>(row + 1, wk * je1);
+                mark_points(emask + (size_t)k * ew, jie, je0 != (Real)0, je1 != (Real)0);
             }
         }
-        // --- radial weights: this lane serves support point lo + io of batch slot po ---
-        const int jpk = rdlane(packed, j);
-        const int jlo = jpk & 255, jn = (jpk >> 8) & 255, jie = (jpk >> 16) & 255;
-        const Real jd = rdlane(d, j), jhinv = rdlane(hinv, j), jwf = rdlane(wsf, j);
-        const Real ja = rdlane(qa, j), je = rdlane(qe, j), jv = rdlane(qv, j);
-        Real je0 = 0, je1 = 0;
-        if ((jpk >> 24) & 1) {
-            je0 = rdlane(e0, j);
-            je1 = rdlane(e1, j);
-        }
-        const int jep = KV ? rdlane(epacked, j) : 0;
+        const int jep = KV ? __shfl(epacked, node, 64) : 0;
         const int jemode = jep & 3, jle = (jep >> 2) & 255, jne = (jep >> 10) & 255;
-        const bool has_eps = je0 != (Real)0 || je1 != (Real)0 || jemode != 0;
-        const int span = jn < 64 ? jn : 64;                         // points per batch slot
-        const int jdv = rdlane(divp, j);
-        const int G = jdv >> 17;                                    // pixels per batch
-        const int po = (lane * (jdv & 0x1ffff)) >> 16;              // lane / span
-        const int io = lane - po * span;
-        const bool lane_ok = po < G;
-        Real wa = 0, we = 0, wv = 0, wq = 0;   // wq: emission spread over the support (modes 1-3)
-        const Real jfb = -jwf;                  // the bracket weight when there is no W_p support
-        if (lane_ok) {
-            Real w;
-            if (jwf > (Real)0) {
-                const int i = jlo + io;
-                w = smooth_kernel<Real>(mg, (rcoef * (Real)(i * i) - jd) * jhinv) * jwf;
-            } else {
-                w = io == 0 ? jfb : (Real)1 - jfb;
-            }
-            wa = w * ja;
-            we = w * je;
-            wv = w * jv;
-            if (KV && jemode != 0) wq = emission_weight<Real>(jemode, jlo + io, io, jle, jne, rdlane(ea, j), rdlane(eb, j),
-                                                       jfb, rcoef, jd, jhinv, a.eps_kernel == K_G) *
-                                  rdlane(qeps, j);
+        Real jea = 0, jeb = 0, jqeps = 0;
+        if (KV) {
+            jea = __shfl(ea, node, 64);
+            jeb = __shfl(eb, node, 64);
+            jqeps = __shfl(qeps, node, 64);
         }
-        const int slot_k = slot_kc & 0xffff, slot_c = slot_kc >> 16;
-        // emission: lane q deposits pixel q's share on the two bracket points and
-        // marks them in the ray's mask (the spread forms go with A, E, V below)
-        if (has_eps && lane < nd && jemode == 0) {
-            const Real wk = (Real)slot_c * inv_s3;
-            Real *row = &R.eps(slot_k, jie);
-            if (je0 != (Real)0) buf_add<Real, EATOMIC>(row, wk * je0);
-            if (je1 != (Real)0) buf_add<Real, EATOMIC>(row + 1, wk * je1);
-            mark_points<ATOMIC != 0>(emask + (size_t)slot_k * ew, jie, je0 != (Real)0, je1 != (Real)0);
-        }
-        // A, E, V: lanes cover (pixel slot, point) pairs, G slots at a time
-        for (int b0 = 0; b0 < nd; b0 += G) {
-            const int q = b0 + po;
-            const int kc = __shfl(slot_kc, q & 63, 64);
-            const int kq = kc & 0xffff, cq = kc >> 16;
-            if (lane_ok && q < nd) {
-                const Real wk = (Real)cq * inv_s3;
-                Real *row = &R.A(kq, jlo + io);
-                buf_add3<Real, ATOMIC>(row, wk * wa, row + nrm, wk * we, row + 2 * nrm, wk * wv);
-                if (KV && wq != (Real)0) {   // the emission row
-                    buf_add<Real, EATOMIC>(&R.eps(kq, jlo + io), wk * wq);
-                    mark_points<ATOMIC != 0>(emask + (size_t)kq * ew, jlo + io, true, false);
-                }
-            }
-        }
-        if (jn > 64) {
-            // support wider than a wave (N_R > 64): the remaining points, pixel by pixel
-            for (int q = 0; q < nd; ++q) {
-                const int k = __builtin_amdgcn_readlane(slot_k, q);
-                const Real wk = (Real)__builtin_amdgcn_readlane(slot_c, q) * inv_s3;
-                Real *row = &R.A(k, jlo);
-                for (int i2 = 64 + lane; i2 < jn; i2 += 64) {
-                    const int i = jlo + i2;
-                    const Real w2 =
-                        jwf > (Real)0 ? smooth_kernel<Real>(mg, (rcoef * (Real)(i * i) - jd) * jhinv) * jwf : (Real)0;
-                    buf_add<Real, ATOMIC>(row + i2, wk * w2 * ja);
-                    buf_add<Real, ATOMIC>(row + nrm + i2, wk * w2 * je);
-                    buf_add<Real, ATOMIC>(row + 2 * nrm + i2, wk * w2 * jv);
-                    if (KV && jemode != 0) {
-                        const Real q2 = emission_weight<Real>(jemode, i, i2, jle, jne, rdlane(ea, j), rdlane(eb, j), jfb,
-                                                              rcoef, jd, jhinv, a.eps_kernel == K_G) *
-                                        rdlane(qeps, j);
-                        if (q2 != (Real)0) {
-                            buf_add<Real, EATOMIC>(&R.eps(k, jlo + i2), wk * q2);
-                            mark_points<ATOMIC != 0>(emask + (size_t)k * ew, jlo + i2, true, false);
-                        }
-                    }
+        const Real jfb = -jwf;   // the bracket weight when there is no W_p support
+        Real *row = &R.A(k, jlo);
+        Real fi = (Real)jlo;
+        for (int io = 0; io < n; ++io, ++row, fi += (Real)1) {
+            const Real w = jwf > (Real)0 ? smooth_kernel<Real>(mg, (rcoef * (fi * fi) - jd) * jhinv) * jwf
+                                         : (io == 0 ? jfb : (Real)1 - jfb);
+            buf_add3<Real, ATOMIC>(row, wk * (w * ja), row + nrm, wk * (w * je), row + 2 * nrm, wk * (w * jv));
+            if (KV && jemode != 0) {   // the emission row
+                const Real wq = emission_weight<Real>(jemode, jlo + io, io, jle, jne, jea, jeb, jfb, rcoef, jd, jhinv,
+                                                      a.eps_kernel == K_G) * jqeps;
+                if (wq != (Real)0) {
+                    buf_add<Real, 1>(&R.eps(k, jlo + io), wk * wq);
+                    mark_points(emask + (size_t)k * ew, jlo + io, true, false);
                 }
             }
         }
@@ -1623,7 +1589,7 @@ template <typename Real, int WAVES, bool LDSBUF, bool FALLBACK, bool KV, bool CA
 __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 {
     using R4 = typename R4T<Real>::T;
-    constexpr int ATOMIC = WAVES == 1 ? 0 : (CAS ? 2 : 1);
+    constexpr int ATOMIC = CAS ? 2 : 1;
     constexpr int CHUNK = 64;   // nodes claimed at a time by a mapping wave (one per lane in phase 1)
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;

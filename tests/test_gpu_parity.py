@@ -571,3 +571,19 @@ def test_many_ray_passes(T, orc):
         compare(g0, j0, f0, i0, TOL64, name=f"N_side 8 passes waves {waves} thin")
         g1, j1, _ = gpu_sweep(T, P, T.TR_FP64, targets=tg, launch=(waves, 0, 1, 0, 0))
         compare(g1, j1, f1, i1, TOL64, name=f"N_side 8 passes waves {waves} absorbing")
+
+
+@pytest.mark.parametrize("nside,sub", [(1, 1), (1, 4), (8, 2), (8, 3), (16, 4)])
+def test_pair_batches(T, orc, nside, sub):
+    """The mapping takes (node, pixel) pairs 64 at a time: one pair per node
+    (s = 1: 64 nodes in a batch) up to nodes of nearly 64 pairs (N_side 16:
+    few or one in a batch, some left for the next), on a grid whose larger
+    nodes are outside the angular table (24 cells: partial nodes)."""
+    P = W.small_lognormal(24, n_src=5, seed=50 + sub, nside=nside, n_radial=20)
+    P.params.subsample = sub
+    tg = np.sort(np.random.default_rng(51).choice(P.total_cells(), 150, replace=False))
+    f0, i0 = orc_sweep(orc, P, thin=True, targets=tg)
+    for prec, tol in ((T.TR_FP64, TOL64), (T.TR_FP32C, TOL32)):
+        g0, j0, st = gpu_sweep(T, P, prec, thin=True, targets=tg)
+        assert 0 < st.nodes_tabulated < st.nodes_accepted * (12 * nside ** 2)
+        compare(g0, j0, f0, i0, tol, name=f"pairs N_side {nside} s {sub} prec {prec}")
