@@ -14,6 +14,10 @@ constexpr int kBlock = 8;          // cells per block edge
 constexpr int kMaxRadial = 128;    // evaluation points per ray (two 64-bit masks)
 constexpr int kAtabRatios = 4;    // angular-weight table: nodes of 1, 2, 4 and 8 target sizes
 constexpr int kMaxLevels = 24;
+constexpr int kListCap = 4096;         // accepted nodes listed per target, and
+constexpr int kListTargets = 1 << 15;  // targets walked and listed at a time (512 MB of lists)
+constexpr int kWalkFront = 1024;       // frontier entries of a walk in LDS
+constexpr int kWalkPerCu = 5;          // workgroups per compute unit of the walk kernel
 constexpr int kGlobalList = 1 << 16;   // frontier / accepted-list entries of the fallback walk
 constexpr int kFallbackPerCu = 2;       // workgroups per compute unit in the fallback pass
 constexpr int kGlNodes = 24;            // Gauss-Legendre nodes of the sphere-deposit quadrature

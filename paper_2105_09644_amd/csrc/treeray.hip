@@ -327,6 +327,15 @@ template <typename Real> struct R4T;
 template <> struct R4T<float> { using T = float4; };
 template <> struct R4T<double> { using T = double4; };
 
+// One target of a chunk, written by k_walk for the sweep: doubled centre and
+// size, domain, how its accepted nodes were listed, output index, moments.
+struct TargetRec {
+    int32_t tx, ty, tz, tsize;
+    int32_t dom, n_tab, n_oth, skip;   // skip: nothing to map (bad index, or queued for the fallback pass)
+    int64_t out;
+    double eps, alpha, e, v;
+};
+
 struct SweepArgs {
     const int4 *geo;
     const int4 *olo;
@@ -343,6 +352,13 @@ struct SweepArgs {
     const int32_t *order;    // all cells in (domain, Morton) order
     int64_t n_items;
     int64_t n_cells;
+    // the chunk of the work items [item0, item0 + n_chunk) whose walks are
+    // listed: target i's accepted nodes inside the angular table's range at
+    // lists[i list_cap ..] upwards, the others from its last entry downwards
+    int64_t item0;
+    int32_t n_chunk, list_cap;
+    int32_t *lists;
+    TargetRec *rec;
     double *f_out;
     uint8_t *ion_out;
     int32_t *queue;          // [0] next item, [1] overflow flag
@@ -353,7 +369,8 @@ struct SweepArgs {
     int32_t split;           // 1: A, E, V rows in LDS (stride_k = 3 nr_max + 1), emission rows in ebuf
     double theta2, theta_if2, theta_src2;   // squared opening angles (0: criterion off)
     float guard_tol;
-    int32_t nside, npix, subsample, fmax, amax, nr_max, stride_k, zeta_g;
+    int32_t f32;             // 1: float records (FP32C), 0: double
+    int32_t nside, npix, subsample, nr_max, stride_k, zeta_g;
     int32_t int_wave;        // 1: a wave per ray (lanes = points); 0: a lane per ray
     int32_t int_group;       // > 0: a group of this many lanes per ray (slots = emitting points)
     int32_t int_fp32;        // 1 (FP32 buffers, groups): the FP32 march, FP64 again near a front
@@ -361,7 +378,7 @@ struct SweepArgs {
     int32_t eps_kernel;      // emission kernel (K_F1 .. K_G; 0 or K_F3: two-point W_f,3)
     int32_t periodic;        // 1: every node through its periodic copy closest to the target
     int32_t mass_gauss;      // 1: W_g for A, E, V and the self term; 0: W_p
-    // walk lists too long for LDS: the item is queued in ovf and a second
+    // walks too long for the lists: the item is queued in ovf and a second
     // launch (k_sweep_fallback) walks it with per-workgroup lists of gfmax /
     // gamax entries in device memory
     int32_t *ovf;
@@ -397,6 +414,23 @@ struct RayRows {
     __device__ Real &V(int k, int i) const { return b[(size_t)k * stride + oa + 2 * nrm + i]; }
     __device__ Real &eps(int k, int i) const { return e[(size_t)k * estride + i]; }
 };
+
+// Index into the angular table of a node whose cube has its (shifted) corner
+// at (bx, by, bz), or -1: a cube of 1, 2, 4 or 8 target sizes within the
+// table's window; offsets of its corner in target sizes (exact).
+__device__ inline int table_key(const SweepArgs &a, int gw, int bx, int by, int bz, int tx, int ty, int tz, int tsize)
+{
+    const int size = gw & kSizeMask;
+    if (!a.atab_idx || (gw & kPartialBit)) return -1;
+    const int ri = size == tsize ? 0 : size == 2 * tsize ? 1 : size == 4 * tsize ? 2 : size == 8 * tsize ? 3 : -1;
+    if (ri < 0) return -1;
+    const int sh = __builtin_ctz((unsigned)tsize);
+    const int kx = (bx - ((tx - tsize) >> 1)) >> sh, ky = (by - ((ty - tsize) >> 1)) >> sh,
+              kz = (bz - ((tz - tsize) >> 1)) >> sh;
+    const int w = a.atab_w[ri], nw = 2 * w + 1;
+    if (abs(kx) > w || abs(ky) > w || abs(kz) > w) return -1;
+    return a.atab_base[ri] + ((kx + w) * nw + (ky + w)) * nw + (kz + w);
+}
 
 // Accumulation into a ray buffer shared by the lanes and waves of a workgroup.
 // AM: 1 a hardware atomic add, 2 (FP32 in LDS) an add by compare-and-swap on
@@ -1082,7 +1116,7 @@ __device__ inline Real emission_weight(int mode, int i, int io, int le, int ne, 
     return io == 0 ? fb : (Real)1 - fb;
 }
 
-// Maps the accepted nodes acc[0..cnt) (cnt <= 64) onto the target's rays;
+// Maps cnt <= 64 accepted nodes, node n on lane < cnt, onto the target's rays;
 // executed by a whole wave in two phases.
 //  Phase 1, lane = node: loads the node, its mass-centre distance d, the
 //   W_p normalisation over the evaluation points in its support and the W_f,3
@@ -1104,7 +1138,7 @@ template <typename Real, int ATOMIC, bool KV, bool PASS>
 __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned long long *emask, int ew, const int *per,
                           const Real *rt, int nr,
                           Real rc_inv,
-                          Real rcoef, const int *acc, int cnt, int tx, int ty, int tz, int tsize, int k0, int np,
+                          Real rcoef, int n, int cnt, int tx, int ty, int tz, int tsize, int k0, int np,
                           double &guard_count, double &tab_count)
 {
     using R4 = typename R4T<Real>::T;
@@ -1120,7 +1154,6 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     int tab = -1;   // the node's angular-table entry (-1: classify its sub-points)
     const bool mg = KV && a.mass_gauss != 0;
     if (lane < cnt) {
-        const int n = acc[lane];
         const int4 g = a.geo[n];
         const int size = g.w & kSizeMask;
         bx = g.x; by = g.y; bz = g.z;
@@ -1142,18 +1175,8 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
             by += shy;
             bz += shz;
         }
-        if (a.atab_idx && !(g.w & kPartialBit)) {
-            // a cube of 1, 2, 4 or 8 target sizes: offsets of its corner in target sizes (exact)
-            const int ri = size == tsize ? 0 : size == 2 * tsize ? 1 : size == 4 * tsize ? 2 : size == 8 * tsize ? 3 : -1;
-            if (ri >= 0) {
-                const int sh = __builtin_ctz((unsigned)tsize);
-                const int kx = (bx - ((tx - tsize) >> 1)) >> sh, ky = (by - ((ty - tsize) >> 1)) >> sh,
-                          kz = (bz - ((tz - tsize) >> 1)) >> sh;
-                const int w = a.atab_w[ri], nw = 2 * w + 1;
-                if (abs(kx) <= w && abs(ky) <= w && abs(kz) <= w)
-                    tab = a.atab_idx[a.atab_base[ri] + ((kx + w) * nw + (ky + w)) * nw + (kz + w)];
-            }
-        }
+        const int key = table_key(a, g.w, bx, by, bz, tx, ty, tz, tsize);
+        if (key >= 0) tab = a.atab_idx[key];
         const Real dxc = (A.x + (Real)shx) - (Real)0.5 * (Real)tx, dyc = (A.y + (Real)shy) - (Real)0.5 * (Real)ty,
                    dzc = (A.z + (Real)shz) - (Real)0.5 * (Real)tz;
         d = fsqrt(dxc * dxc + dyc * dyc + dzc * dzc);
@@ -1338,9 +1361,9 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
             fill += ready_nd;
             ready = -1;
         }
-        // --- deposit: this lane's pair over its node's support points lo .. lo + n - 1 ---
+        // --- deposit: this lane's pair over its node's support points lo .. lo + npt - 1 ---
         const int npk = __shfl(packed, node, 64);
-        const int jlo = npk & 255, n = valid ? (npk >> 8) & 255 : 0;
+        const int jlo = npk & 255, npt = valid ? (npk >> 8) & 255 : 0;
         const Real jd = __shfl(d, node, 64), jhinv = __shfl(hinv, node, 64), jwf = __shfl(wsf, node, 64);
         const Real ja = __shfl(qa, node, 64), je = __shfl(qe, node, 64), jv = __shfl(qv, node, 64);
         const int k = kc & 0xffff;
@@ -1368,7 +1391,7 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
         const Real jfb = -jwf;   // the bracket weight when there is no W_p support
         Real *row = &R.A(k, jlo);
         Real fi = (Real)jlo;
-        for (int io = 0; io < n; ++io, ++row, fi += (Real)1) {
+        for (int io = 0; io < npt; ++io, ++row, fi += (Real)1) {
             const Real w = jwf > (Real)0 ? smooth_kernel<Real>(mg, (rcoef * (fi * fi) - jd) * jhinv) * jwf
                                          : (io == 0 ? jfb : (Real)1 - jfb);
             buf_add3<Real, ATOMIC>(row, wk * (w * ja), row + nrm, wk * (w * je), row + 2 * nrm, wk * (w * jv));
@@ -1386,115 +1409,184 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
 
 // LDS flags of the per-target walk (acquire/release inside the workgroup)
 __device__ inline int lds_load(const int *p) { return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP); }
-__device__ inline void lds_store(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP); }
 
-// Breadth-first walk of one target by a single wave (Sec. 2.3, 2.4): a node
-// containing the target is opened, every other leaf is accepted, other nodes
-// are accepted when size^2 < theta^2 d^2 (geometric centre, doubled integer
-// coordinates, the product taken in FP64).  Accepted nodes are appended to
-// acc and published through sc[S_AVAIL] as each batch of tests completes, so
-// the other waves map them while the walk goes on.
-// S_PRE: the bank's item was claimed (and possibly walked, S_WALKED) ahead,
-// during the previous target's integration
-enum { S_ITEM = 0, S_AVAIL, S_CLAIM, S_DONE, S_OVF, S_TOTAL, S_PRE, S_WALKED,
-       // a walk by several waves: the claim's generation, their meetings, the next
-       // frontier's length (three by level), the accepted count, an overflow
-       S_PGEN, S_PMEET, S_PNEXT, S_PACC = S_PNEXT + 3, S_POVF, S_COUNT = 16 };
+// One node of a walk (Sec. 2.3, 2.4): a node containing the target is opened,
+// every other leaf is accepted, other nodes are accepted when
+// size^2 < theta^2 d^2 (geometric centre, doubled integer coordinates, the
+// product taken in FP64).  Returns 1 accepted, 2 opened, 0 neither (the target
+// itself); sh: the shift to the node's periodic copy.
+__device__ inline int test_node(const SweepArgs &a, const int *per, const int4 g, bool leaf, int tx, int ty, int tz,
+                                int sh[3])
+{
+    const int sz = g.w & kSizeMask;
+    sh[0] = sh[1] = sh[2] = 0;
+    const bool inside = (2 * g.x <= tx && tx < 2 * (g.x + sz)) && (2 * g.y <= ty && ty < 2 * (g.y + sz)) &&
+                        (2 * g.z <= tz && tz < 2 * (g.z + sz));
+    if (inside) return leaf ? 0 : 2;
+    int vx = 2 * g.x + sz - tx, vy = 2 * g.y + sz - ty, vz = 2 * g.z + sz - tz;
+    if (per) {
+        sh[0] = nearest_copy_shift(vx, per[0]);
+        sh[1] = nearest_copy_shift(vy, per[1]);
+        sh[2] = nearest_copy_shift(vz, per[2]);
+        vx += 2 * sh[0];
+        vy += 2 * sh[1];
+        vz += 2 * sh[2];
+    }
+    if (leaf) return 1;
+    const double ddx = (double)vx, ddy = (double)vy, ddz = (double)vz;
+    const double D2 = ddx * ddx + ddy * ddy + ddz * ddz;
+    double th2 = a.theta2;   // lowered by the IF and Src MACs (Sec. 2.4)
+    if ((g.w & kIfBit) && a.theta_if2 > 0.0) th2 = fmin(th2, a.theta_if2);
+    if ((g.w & kSrcBit) && a.theta_src2 > 0.0) th2 = fmin(th2, a.theta_src2);
+    return th2 * D2 > 4.0 * (double)sz * (double)sz ? 1 : 2;
+}
+
+// Queues work item `item` for the fallback pass; without room (or in that pass
+// itself) the target fails: NaN and the overflow flag.  One lane.
+__device__ inline void queue_overflow(const SweepArgs &a, bool fallback, int64_t item, int64_t out)
+{
+    if (!fallback && a.ovf) {
+        const int q = atomicAdd(&a.queue[3], 1);
+        if (q < a.ovf_cap) {
+            a.ovf[q] = (int32_t)item;
+            return;
+        }
+    }
+    a.f_out[out] = __longlong_as_double(0x7ff8000000000000ll);
+    if (a.ion_out) a.ion_out[out] = 0;
+    atomicOr(&a.queue[1], 1);
+}
+
+// Breadth-first walks of a chunk's targets, a wave per target: one node per
+// lane, ballot and prefix scan to append the accepted nodes to the target's
+// list in device memory and the next frontier in LDS.  A walk is a chain of
+// dependent node reads (a level at a time), so it is bound by latency: in a
+// kernel of its own many walks hide each other's (5 workgroups of 4 waves per
+// compute unit by the frontiers' 32 KB), where inside the sweep one target's
+// walk held up the others' barrier.
+constexpr int kWalkWaves = 4;
+__global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
+{
+    __shared__ int front[kWalkWaves][2][kWalkFront];
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.queue[0] = 0;   // the sweep of this chunk starts from its first target
+    const uint64_t below = (1ull << lane) - 1ull;
+    double n_test = 0, n_acc = 0;
+    for (int i = (int)blockIdx.x * kWalkWaves + wave; i < a.n_chunk; i += (int)gridDim.x * kWalkWaves) {
+        const int64_t item = a.item0 + i;
+        const int64_t cell = a.targets ? a.targets[item] : (int64_t)a.order[item];
+        TargetRec r{};
+        r.out = a.targets ? item : cell;
+        if (cell < 0 || cell >= a.n_cells) {
+            r.skip = 1;
+            if (lane == 0) {
+                a.f_out[r.out] = __longlong_as_double(0x7ff8000000000000ll);
+                if (a.ion_out) a.ion_out[r.out] = 0;
+                atomicOr(&a.queue[1], 2);
+                a.rec[i] = r;
+            }
+            continue;
+        }
+        r.dom = uniform(a.cell_dom[cell]);
+        const DomDev &D = a.doms[r.dom];
+        const int tnode = uniform(a.cell_node[cell]);
+        const int4 tg = a.geo[tnode];
+        r.tsize = tg.w & kSizeMask;
+        r.tx = 2 * tg.x + r.tsize;
+        r.ty = 2 * tg.y + r.tsize;
+        r.tz = 2 * tg.z + r.tsize;
+        int per_ext[3] = {D.ext[0], D.ext[1], D.ext[2]};
+        const int *per = a.periodic ? per_ext : nullptr;
+        int *const list = a.lists + (size_t)i * a.list_cap;
+        int *cur = front[wave][0], *nxt = front[wave][1];
+        if (lane == 0) cur[0] = D.root;
+        int nfr = 1, nt = 0, no = 0;
+        bool ovf = false;
+        while (nfr > 0 && !ovf) {
+            int nn = 0;
+            for (int base = 0; base < nfr; base += 64) {
+                const bool valid = base + lane < nfr;
+                int n = 0, nch = 0, fc = 0;
+                bool in_tab = false, other = false;
+                if (valid) {
+                    n = cur[base + lane];
+                    const int4 g = a.geo[n];
+                    const int2 tp = a.topo[n];
+                    int sh[3];
+                    const int what = test_node(a, per, g, tp.y == 0, r.tx, r.ty, r.tz, sh);
+                    if (what == 1) {
+                        in_tab = table_key(a, g.w, g.x + sh[0], g.y + sh[1], g.z + sh[2], r.tx, r.ty, r.tz, r.tsize) >= 0;
+                        other = !in_tab;
+                    }
+                    nch = what == 2 ? tp.y : 0;
+                    fc = tp.x;
+                }
+                n_test += valid ? 1.0 : 0.0;
+                const uint64_t mt = __ballot(in_tab), mo = __ballot(other);
+                int tot = 0;
+                const int off = wave_excl_scan_dpp(nch, tot);
+                const int ct = (int)__popcll(mt), co = (int)__popcll(mo);
+                if (nt + no + ct + co > a.list_cap || nn + tot > kWalkFront) {
+                    ovf = true;
+                    break;
+                }
+                if (in_tab) list[nt + (int)__popcll(mt & below)] = n;
+                if (other) list[a.list_cap - 1 - no - (int)__popcll(mo & below)] = n;
+                for (int c = 0; c < nch; ++c) nxt[nn + off + c] = fc + c;
+                nt += ct;
+                no += co;
+                nn += tot;
+            }
+            int *t = cur;
+            cur = nxt;
+            nxt = t;
+            nfr = nn;
+        }
+        r.n_tab = nt;
+        r.n_oth = no;
+        r.skip = ovf ? 1 : 0;
+        n_acc += ovf || lane != 0 ? 0.0 : (double)(nt + no);
+        if (lane == 0) {
+            if (a.f32) {
+                const float4 A = ((const float4 *)a.pA)[tnode], B = ((const float4 *)a.pB)[tnode];
+                r.eps = A.w; r.alpha = B.x; r.e = B.y; r.v = B.z;
+            } else {
+                const double4 A = ((const double4 *)a.pA)[tnode], B = ((const double4 *)a.pB)[tnode];
+                r.eps = A.w; r.alpha = B.x; r.e = B.y; r.v = B.z;
+            }
+            a.rec[i] = r;
+            if (ovf) queue_overflow(a, false, item, r.out);
+        }
+    }
+    n_test = wave_sum(n_test);
+    n_acc = wave_sum(n_acc);
+    if (lane == 0) {
+        if (n_acc > 0) atomicAdd(&a.stats[0], (unsigned long long)n_acc);
+        if (n_test > 0) atomicAdd(&a.stats[1], (unsigned long long)n_test);
+    }
+}
+
+// LDS words of a sweep workgroup: its next work item, and (fallback pass) the
+// shared walk's meetings, the next frontier's length (three by level), the
+// accepted count, an overflow
+enum { S_NEXT = 0, S_PMEET, S_PNEXT, S_PACC = S_PNEXT + 3, S_POVF, S_COUNT = 16 };
 
 // Waits until this wave's device-memory stores have completed (vmcnt 0), so
 // that an LDS flag written next publishes them to the workgroup's other waves
 // (a workgroup-scope release does not wait for them).
 __device__ inline void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// dev_lists: acc is in device memory (the mappers read it after the LDS counts)
-__device__ void walk_target(const SweepArgs &a, int root, const int *per, int tx, int ty, int tz, int *fr0, int *fr1,
-                            int *acc, int *sc, int fmax, int amax, double &n_test, bool dev_lists)
-{
-    const int lane = lane_id();
-    int *cur = fr0, *nxt = fr1;
-    if (lane == 0) cur[0] = root;
-    int nfr = 1, nacc = 0;
-    bool ovf = false;
-    while (nfr > 0 && !ovf) {
-        int nn = 0;
-        for (int base = 0; base < nfr; base += 64) {
-            const int idx = base + lane;
-            const bool valid = idx < nfr;
-            int n = 0, nch = 0, fc = 0;
-            bool acc_it = false;
-            if (valid) {
-                n = cur[idx];
-                const int4 g = a.geo[n];
-                const int2 tp = a.topo[n];
-                const int sz = g.w & kSizeMask;
-                const bool leaf = tp.y == 0;
-                const bool inside = (2 * g.x <= tx && tx < 2 * (g.x + sz)) && (2 * g.y <= ty && ty < 2 * (g.y + sz)) &&
-                                    (2 * g.z <= tz && tz < 2 * (g.z + sz));
-                bool open_it = false;
-                if (inside) {
-                    open_it = !leaf;
-                } else if (leaf) {
-                    acc_it = true;
-                } else {
-                    int vx = 2 * g.x + sz - tx, vy = 2 * g.y + sz - ty, vz = 2 * g.z + sz - tz;
-                    if (per) {
-                        vx += 2 * nearest_copy_shift(vx, per[0]);
-                        vy += 2 * nearest_copy_shift(vy, per[1]);
-                        vz += 2 * nearest_copy_shift(vz, per[2]);
-                    }
-                    const double ddx = (double)vx, ddy = (double)vy, ddz = (double)vz;
-                    const double D2 = ddx * ddx + ddy * ddy + ddz * ddz;
-                    double th2 = a.theta2;   // lowered by the IF and Src MACs (Sec. 2.4)
-                    if ((g.w & kIfBit) && a.theta_if2 > 0.0) th2 = fmin(th2, a.theta_if2);
-                    if ((g.w & kSrcBit) && a.theta_src2 > 0.0) th2 = fmin(th2, a.theta_src2);
-                    acc_it = th2 * D2 > 4.0 * (double)sz * (double)sz;
-                    open_it = !acc_it;
-                }
-                nch = open_it ? tp.y : 0;
-                fc = tp.x;
-            }
-            n_test += valid ? 1.0 : 0.0;
-            const uint64_t macc = __ballot(acc_it);
-            const int cacc = __popcll(macc);
-            int tot = 0;
-            const int off = wave_excl_scan_dpp(nch, tot);
-            if (nacc + cacc > amax || nn + tot > fmax) {
-                ovf = true;
-                break;
-            }
-            if (acc_it) acc[nacc + __popcll(macc & ((1ull << lane) - 1ull))] = n;
-            for (int c = 0; c < nch; ++c) nxt[nn + off + c] = fc + c;
-            nacc += cacc;
-            nn += tot;
-            if (cacc) {
-                if (dev_lists) wait_stores();
-                if (lane == 0) lds_store(&sc[S_AVAIL], nacc);
-            }
-        }
-        int *t = cur;
-        cur = nxt;
-        nxt = t;
-        nfr = nn;
-    }
-    if (dev_lists) wait_stores();
-    if (lane == 0) {
-        sc[S_TOTAL] = nacc;
-        if (ovf) sc[S_OVF] = 1;
-        lds_store(&sc[S_AVAIL], nacc);
-        lds_store(&sc[S_DONE], 1);
-    }
-}
-
-// The same walk by K waves (half 0 to K - 1) of one workgroup, into a list
-// that is read only once the walk is done: the batches of 64 nodes of a level
-// go round the waves, their appends to the next frontier and to the accepted
-// list are reserved by LDS atomics, and the waves meet at an LDS counter after
-// every level (all leave the loop at the same level).  sc[S_PMEET],
-// sc[S_PNEXT], sc[S_PACC], sc[S_POVF] and cur[0] = root are set by half 0
-// before any starts.  Half 0 publishes the list.
+// The walk of one target by the K waves of a workgroup, with its lists in
+// device memory (fallback pass): the batches of 64 nodes of a level go round
+// the waves, their appends to the next frontier and to the accepted list are
+// reserved by LDS atomics, and the waves meet at an LDS counter after every
+// level (all leave the loop at the same level).  The S_P words are zero and
+// cur[0] = root before any starts.  Returns the accepted count (the same on
+// every wave), or -1 after an overflow.
 template <int K>
-__device__ void walk_target_pair(const SweepArgs &a, int half, const int *per, int tx, int ty, int tz, int *fr0,
-                                 int *fr1, int *acc, int *sc, int fmax, int amax, double &n_test, bool dev_lists)
+__device__ int walk_shared(const SweepArgs &a, int wave, const int *per, int tx, int ty, int tz, int *fr0, int *fr1,
+                           int *acc, int *sc, int fmax, int amax, double &n_test)
 {
     const int lane = lane_id();
     int *cur = fr0, *nxt = fr1;
@@ -1502,46 +1594,23 @@ __device__ void walk_target_pair(const SweepArgs &a, int half, const int *per, i
     for (int lev = 0;; ++lev) {
         int *const next_count = &sc[S_PNEXT + lev % 3];
         // the counter of the level after next is free (read before the last meeting)
-        if (half == 0 && lane == 0) sc[S_PNEXT + (lev + 1) % 3] = 0;
-        for (int base = 64 * half; base < nfr; base += 64 * K) {
-            const int idx = base + lane;
-            const bool valid = idx < nfr;
+        if (wave == 0 && lane == 0) sc[S_PNEXT + (lev + 1) % 3] = 0;
+        for (int base = 64 * wave; base < nfr; base += 64 * K) {
+            const bool valid = base + lane < nfr;
             int n = 0, nch = 0, fc = 0;
             bool acc_it = false;
             if (valid) {
-                n = cur[idx];
-                const int4 g = a.geo[n];
+                n = cur[base + lane];
                 const int2 tp = a.topo[n];
-                const int sz = g.w & kSizeMask;
-                const bool leaf = tp.y == 0;
-                const bool inside = (2 * g.x <= tx && tx < 2 * (g.x + sz)) && (2 * g.y <= ty && ty < 2 * (g.y + sz)) &&
-                                    (2 * g.z <= tz && tz < 2 * (g.z + sz));
-                bool open_it = false;
-                if (inside) {
-                    open_it = !leaf;
-                } else if (leaf) {
-                    acc_it = true;
-                } else {
-                    int vx = 2 * g.x + sz - tx, vy = 2 * g.y + sz - ty, vz = 2 * g.z + sz - tz;
-                    if (per) {
-                        vx += 2 * nearest_copy_shift(vx, per[0]);
-                        vy += 2 * nearest_copy_shift(vy, per[1]);
-                        vz += 2 * nearest_copy_shift(vz, per[2]);
-                    }
-                    const double ddx = (double)vx, ddy = (double)vy, ddz = (double)vz;
-                    const double D2 = ddx * ddx + ddy * ddy + ddz * ddz;
-                    double th2 = a.theta2;   // lowered by the IF and Src MACs (Sec. 2.4)
-                    if ((g.w & kIfBit) && a.theta_if2 > 0.0) th2 = fmin(th2, a.theta_if2);
-                    if ((g.w & kSrcBit) && a.theta_src2 > 0.0) th2 = fmin(th2, a.theta_src2);
-                    acc_it = th2 * D2 > 4.0 * (double)sz * (double)sz;
-                    open_it = !acc_it;
-                }
-                nch = open_it ? tp.y : 0;
+                int sh[3];
+                const int what = test_node(a, per, a.geo[n], tp.y == 0, tx, ty, tz, sh);
+                acc_it = what == 1;
+                nch = what == 2 ? tp.y : 0;
                 fc = tp.x;
             }
             n_test += valid ? 1.0 : 0.0;
             const uint64_t macc = __ballot(acc_it);
-            const int cacc = __popcll(macc);
+            const int cacc = (int)__popcll(macc);
             int tot = 0;
             const int off = wave_excl_scan_dpp(nch, tot);
             int oa = 0, on = 0;
@@ -1556,41 +1625,31 @@ __device__ void walk_target_pair(const SweepArgs &a, int half, const int *per, i
                 if (lane == 0) sc[S_POVF] = lev + 1;
                 continue;
             }
-            if (acc_it) acc[oa + __popcll(macc & ((1ull << lane) - 1ull))] = n;
+            if (acc_it) acc[oa + (int)__popcll(macc & ((1ull << lane) - 1ull))] = n;
             for (int c = 0; c < nch; ++c) nxt[on + off + c] = fc + c;
         }
         // meet the other waves: the level's appends are all written
-        if (dev_lists) wait_stores();
+        wait_stores();
         if (lane == 0) atomicAdd(&sc[S_PMEET], 1);
         while (lds_load(&sc[S_PMEET]) < K * (lev + 1)) __builtin_amdgcn_s_sleep(1);
         nfr = uniform(lds_load(next_count));
-        // (an overflow of the other wave's next level is not this level's)
+        // (an overflow of another wave's next level is not this level's)
         const int ov = uniform(lds_load(&sc[S_POVF]));
-        if (nfr == 0 || (ov != 0 && ov <= lev + 1)) break;
+        if (ov != 0 && ov <= lev + 1) return -1;
+        if (nfr == 0) return uniform(lds_load(&sc[S_PACC]));
         int *t = cur;
         cur = nxt;
         nxt = t;
     }
-    if (half == 0 && lane == 0) {
-        // after an overflow the list has gaps: nothing is mapped (the target
-        // goes to the second pass)
-        const bool ovf = lds_load(&sc[S_POVF]) != 0;
-        sc[S_TOTAL] = ovf ? 0 : lds_load(&sc[S_PACC]);
-        if (ovf) sc[S_OVF] = 1;
-        lds_store(&sc[S_AVAIL], sc[S_TOTAL]);
-        lds_store(&sc[S_DONE], 1);
-        sc[S_WALKED] = 1;
-    }
 }
 
-// The sweep of one launch.  FALLBACK: the second pass over the items whose
-// walk lists did not fit in LDS, with the lists in device memory.
+// The sweep of one launch over the listed targets of a chunk.  FALLBACK: the
+// second pass over the items whose walks did not fit in the lists, walked here
+// by the whole workgroup with lists in device memory.
 template <typename Real, int WAVES, bool LDSBUF, bool FALLBACK, bool KV, bool CAS = false, bool PASS = false>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 {
-    using R4 = typename R4T<Real>::T;
     constexpr int ATOMIC = CAS ? 2 : 1;
-    constexpr int CHUNK = 64;   // nodes claimed at a time by a mapping wave (one per lane in phase 1)
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar loops over waves' work
@@ -1619,87 +1678,77 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     p += nrm * sizeof(double);
     double *rd2 = (double *)p;  // 1 / (2 r_i)
     p += nrm * sizeof(double);
-    int *fr0, *fr1, *acc;
-    int fmax, amax;
-    if (FALLBACK) {
-        int *gl = a.glist + (size_t)blockIdx.x * (2 * (size_t)a.gfmax + a.gamax);
-        fmax = a.gfmax;
-        amax = a.gamax;
-        fr0 = gl;
-        fr1 = gl + fmax;
-        acc = gl + 2 * (size_t)fmax;
-    } else {
-        fmax = a.fmax;
-        amax = a.amax;
-        fr0 = (int *)p;
-        p += fmax * sizeof(int);
-        fr1 = (int *)p;
-        p += fmax * sizeof(int);
-        acc = (int *)p;
-        p += amax * sizeof(int);
-    }
-    int *sc = (int *)p;   // two banks of S_COUNT: the current target's and the next one's
-    p += 2 * S_COUNT * sizeof(int);
+    int *sc = (int *)p;
+    p += S_COUNT * sizeof(int);
     double *red = (double *)p;
     p += WAVES * sizeof(double);
     // per ray: the mask of its points that hold emission (ew words)
     const int ew = nrm > 64 ? 2 : 1;
     unsigned long long *const emask = (unsigned long long *)p;
+    int *fr0 = nullptr;   // fallback: frontiers of gfmax entries, then gamax accepted nodes
+    if (FALLBACK) fr0 = a.glist + (size_t)blockIdx.x * (2 * (size_t)a.gfmax + a.gamax);
 
     double n_acc = 0, n_test = 0, n_guard = 0, n_f32 = 0, n_f64 = 0, n_tab = 0, n_re = 0;
     const int64_t n_items =
         FALLBACK ? min((int64_t)__hip_atomic_load(&a.queue[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), a.ovf_cap)
-                   : a.n_items;
-
-    // a bank takes the next work item with its walk counters reset
-    auto claim = [&](int *b) {
-        b[S_ITEM] = atomicAdd(&a.queue[FALLBACK ? 2 : 0], 1);
-        b[S_AVAIL] = 0;
-        b[S_CLAIM] = 0;
-        b[S_DONE] = 0;
-        b[S_OVF] = 0;
-        b[S_TOTAL] = 0;
-        b[S_WALKED] = 0;
+                 : a.n_chunk;
+    int32_t *const next_item = &a.queue[FALLBACK ? 2 : 0];
+    // the claim of the next item, by one thread after everyone has read the last one
+    auto claim = [&]() {
+        if (tid == 0) sc[S_NEXT] = atomicAdd(next_item, 1);
     };
-    if (tid == 0) {
-        sc[S_PRE] = sc[S_COUNT + S_PRE] = 0;
-        sc[S_PGEN] = sc[S_COUNT + S_PGEN] = 0;   // (generations start at 1)
-    }
-    int bank = 0;
-    int titer = 0;   // targets begun by this workgroup (the generation of a shared walk's claim)
+    claim();
+    __syncthreads();
     int cached_dom = -1, cached_tsize = -1;   // whose radial tables the LDS holds
     for (;;) {
-        int *const scb = sc + bank * S_COUNT;
-        ++titer;
-        __syncthreads();
-        if (tid == 0) {
-            if (!scb[S_PRE]) claim(scb);
-            scb[S_PRE] = 0;
-        }
-        __syncthreads();
-        const int64_t item = uniform(scb[S_ITEM]);   // the same on every lane: scalar loads below
+        const int64_t item = uniform(sc[S_NEXT]);   // the same on every lane: scalar loads below
         if (item >= n_items) break;
-        const int64_t it = FALLBACK ? (int64_t)a.ovf[item] : item;
-        const int64_t cell = a.targets ? a.targets[it] : (int64_t)a.order[it];
-        const int64_t o = a.targets ? it : cell;   // output index
-        if (cell < 0 || cell >= a.n_cells) {
-            if (tid == 0) {
-                a.f_out[o] = __longlong_as_double(0x7ff8000000000000ll);
-                if (a.ion_out) a.ion_out[o] = 0;
-                atomicOr(&a.queue[1], 2);
+        int dom, tsize, tx, ty, tz, nt = 0, no = 0;
+        int64_t o;
+        Real teps, talpha, te, tv;
+        const int32_t *list = nullptr;
+        if (!FALLBACK) {
+            const TargetRec &r = a.rec[item];
+            dom = uniform(r.dom);
+            tsize = uniform(r.tsize);
+            tx = uniform(r.tx);
+            ty = uniform(r.ty);
+            tz = uniform(r.tz);
+            nt = uniform(r.n_tab);
+            no = uniform(r.n_oth);
+            o = r.out;
+            teps = (Real)r.eps;
+            talpha = (Real)r.alpha;
+            te = (Real)r.e;
+            tv = (Real)r.v;
+            list = a.lists + (size_t)item * a.list_cap;
+            if (uniform(r.skip)) {
+                __syncthreads();
+                claim();
+                __syncthreads();
+                continue;
             }
-            continue;
+        } else {
+            using R4 = typename R4T<Real>::T;
+            const int64_t it = a.ovf[item];   // (its cell index was checked when it was queued)
+            const int64_t cell = a.targets ? a.targets[it] : (int64_t)a.order[it];
+            o = a.targets ? it : cell;
+            dom = a.cell_dom[cell];
+            const int tnode = a.cell_node[cell];
+            const int4 tg = a.geo[tnode];
+            tsize = tg.w & kSizeMask;
+            tx = 2 * tg.x + tsize;
+            ty = 2 * tg.y + tsize;
+            tz = 2 * tg.z + tsize;
+            const R4 tA = ((const R4 *)a.pA)[tnode], tB = ((const R4 *)a.pB)[tnode];
+            teps = tA.w;
+            talpha = tB.x;
+            te = tB.y;
+            tv = tB.z;
         }
-        const int dom = a.cell_dom[cell];
-        const DomDev D = a.doms[dom];
+        const DomDev &D = a.doms[dom];
         const int nr = D.nr;
-        const int tnode = a.cell_node[cell];
-        const int4 tg = a.geo[tnode];
-        const int tsize = tg.w & kSizeMask;
-        // doubled target centre: exact integers
-        const int tx = 2 * tg.x + tsize, ty = 2 * tg.y + tsize, tz = 2 * tg.z + tsize;
-        const R4 tA = ((const R4 *)a.pA)[tnode];
-        const R4 tB = ((const R4 *)a.pB)[tnode];
+        const int *per = a.periodic ? D.ext : nullptr;
         const Real rc_inv = (Real)D.rc_inv;
         const Real rcoef = (Real)(1.0 / D.rc_inv);
 
@@ -1728,11 +1777,30 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             cached_dom = dom;
             cached_tsize = tsize;
         }
+        if (FALLBACK) {
+            // the walk, by all waves
+            if (tid == 0) {
+                for (int q = S_PMEET; q <= S_POVF; ++q) sc[q] = 0;
+                fr0[0] = D.root;
+            }
+            wait_stores();
+            __syncthreads();
+            int *const acc = fr0 + 2 * (size_t)a.gfmax;
+            nt = walk_shared<WAVES>(a, wave, per, tx, ty, tz, fr0, fr0 + a.gfmax, acc, sc, a.gfmax, a.gamax, n_test);
+            list = acc;
+            if (nt < 0) {
+                __syncthreads();
+                if (tid == 0) queue_overflow(a, true, item, o);
+                claim();
+                __syncthreads();
+                continue;
+            }
+            n_acc += tid == 0 ? (double)nt : 0.0;
+        }
         double ftarget = 0.0;   // this lane's share of the target's flux over the passes
         // The rays k0 .. k0 + np - 1: all of them, or (PASS) one pass of prays
-        // consecutive pixels at a time, the passes looping back here (a target
-        // whose walk overflows leaves with continue).  Without passes there is
-        // no loop, so the body compiles as straight-line code.
+        // consecutive pixels at a time, the passes looping back here.  Without
+        // passes there is no loop, so the body compiles as straight-line code.
         int pass = 0;
     next_pass:
         {
@@ -1749,7 +1817,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                     const int row = e / nrm + (split ? 1 : 0), i = e - (e / nrm) * nrm;
                     Real v = (Real)0;
                     if (e < per_ray && row != Q_EPS && i < nr) {
-                        const Real mom = row == Q_A ? tB.x : row == Q_E ? tB.y : tB.z;
+                        const Real mom = row == Q_A ? talpha : row == Q_E ? te : tv;
                         v = mom * (wself[i] * inv_npix);
                     }
                     val[m] = v;
@@ -1761,86 +1829,36 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                         if (64 * m < per_ray && lane + 64 * m < per_ray) dst[lane + 64 * m] = val[m];
                 }
                 for (int e = tid; e < np * ew; e += WAVES * 64) emask[e] = 0ull;
-                // a later pass maps the same accepted nodes again
-                if (pass > 0 && tid == 0) scb[S_CLAIM] = 0;
                 // (the emission plane of split buffers is zero here: cleared when
                 // allocated and, entry by entry, by the march that reads it)
             }
             __syncthreads();
+            if (pass == 0) claim();   // (visible to all after the mapping)
 
-            // --- wave 0 walks (unless the target was walked ahead); every wave maps ---
-            const int *per = a.periodic ? D.ext : nullptr;
-            if (pass == 0 && wave == 0 && !scb[S_WALKED])
-                walk_target(a, D.root, per, tx, ty, tz, fr0, fr1, acc, scb, fmax, amax, n_test, FALLBACK);
-            for (;;) {
-                // claims of CHUNK nodes; once the walk is done, smaller ones near the
-                // end of the list (a share of what is left), so the waves finish together
-                int start = 0, size = CHUNK;
-                if (lane == 0) {
-                    if (lds_load(&scb[S_DONE])) {
-                        const int left = lds_load(&scb[S_TOTAL]) - lds_load(&scb[S_CLAIM]);
-                        size = min(CHUNK, max(4, left / (2 * WAVES)));
-                    }
-                    start = atomicAdd(&scb[S_CLAIM], size);
+            // --- every wave maps an equal share of the table nodes and of the others, in
+            // rounds of at most 64 nodes (62 on average: each share is rounded; classifying a node takes a wave ten times as
+            // long as mapping one from the table, so the shares are equal in both) ---
+            {
+                const int rounds = (nt + no + 62 * WAVES - 1) / (62 * WAVES);
+                const int nc = max(rounds, 1) * WAVES;
+                for (int r = 0; r < rounds; ++r) {
+                    const int c = r * WAVES + wave;
+                    const int t0 = nt * c / nc, mt = nt * (c + 1) / nc - t0;
+                    const int o0 = no * c / nc, mo = no * (c + 1) / nc - o0;
+                    const int cnt = mt + mo;
+                    int n = 0;
+                    if (lane < cnt) n = lane < mo ? list[a.list_cap - 1 - o0 - lane] : list[t0 + lane - mo];
+                    map_nodes<Real, ATOMIC, KV, PASS>(a, R, emask, ew, per, rt, nr, rc_inv, rcoef, n, cnt, tx, ty, tz,
+                                                      tsize, k0, np, n_guard, n_tab);
                 }
-                start = __shfl(start, 0, 64);
-                size = __shfl(size, 0, 64);
-                int end = 0;
-                for (;;) {
-                    const int avail = lds_load(&scb[S_AVAIL]);
-                    if (avail >= start + size) {
-                        end = start + size;
-                        break;
-                    }
-                    if (lds_load(&scb[S_DONE])) {
-                        const int total = lds_load(&scb[S_TOTAL]);
-                        end = min(start + size, total);
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                }
-                end = uniform(end);
-                if (end <= start) break;
-                map_nodes<Real, ATOMIC, KV, PASS>(a, R, emask, ew, per, rt, nr, rc_inv, rcoef, acc + start, end - start, tx, ty, tz,
-                                            tsize, k0, np, n_guard, n_tab);
             }
             __syncthreads();
-            if (scb[S_OVF]) {
-                // the partly mapped emission is not integrated: clear the plane
-                if (split)
-                    for (int e = tid; e < npix * nrm; e += WAVES * 64) eplane[e] = (Real)0;
-                if (tid == 0) {
-                    bool queued = false;
-                    if (!FALLBACK && a.ovf) {
-                        const int q = atomicAdd(&a.queue[3], 1);
-                        if (q < a.ovf_cap) {
-                            a.ovf[q] = (int32_t)item;
-                            queued = true;
-                        }
-                    }
-                    if (!queued) {
-                        a.f_out[o] = __longlong_as_double(0x7ff8000000000000ll);
-                        if (a.ion_out) a.ion_out[o] = 0;
-                        atomicOr(&a.queue[1], 1);
-                    }
-                }
-                continue;
-            }
-            if (pass == 0) n_acc += (wave == 0 && lane == 0) ? (double)scb[S_TOTAL] : 0.0;
 
-            // --- per-ray integration and the sum over rays (rays without emission give 0),
-            // by waves 0 .. IW - 1; the others meanwhile walk the next target ---
-            // (at 16 waves the last four walk it, else the last one: with fewer waves
-            // one more integrating wave is worth more than a faster walk; at 16 the
-            // walk on fewer waves outlasts the integration, on more it slows it)
-            constexpr int kWalk = WAVES >= 16 ? 4 : 1;   // waves that walk the next target
-            constexpr bool kPair = kWalk > 1;
-            constexpr int IW = kPair ? WAVES - kWalk : (WAVES > 1 ? WAVES - 1 : 1);
+            // --- per-ray integration and the sum over rays (rays without emission give 0) ---
+            constexpr int IW = WAVES;
             double fsum = 0.0;
             float cs_hi = 0.0f, cs_lo = 0.0f;   // compensated FP32 sum of this lane's FP32-marched rays
-            if (wave >= IW) {
-                // no rays here
-            } else if (a.int_group > 0) {
+            if (a.int_group > 0) {
                 // Every emitting ray gets a group of lanes sized by its number of
                 // emitting points: a power of two from the launch's group up to 64
                 // (its class), more than 64 points a wave (class 7).  Rays of one
@@ -1939,61 +1957,6 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                     if (t > 0) fsum += integrate_ray<Real>(R, k, rd, rd2, nr, t, a.nside, a.zeta_g, split);
                 }
             }
-            // the next target: claimed and walked into the other bank by the last
-            // wave, or the last four (the node lists and that bank are not in use
-            // until the next barrier)
-            if ((kPair ? wave >= WAVES - kWalk : wave == WAVES - 1) && pass == npass - 1) {
-                int *const nsc = sc + (bank ^ 1) * S_COUNT;
-                const int half = WAVES - 1 - wave;
-                if (half == 0) {
-                    if (lane == 0) {
-                        claim(nsc);
-                        nsc[S_PRE] = 1;
-                    }
-                } else {
-                    // half 0's claim of this generation
-                    while (lds_load(&nsc[S_PGEN]) != titer) __builtin_amdgcn_s_sleep(1);
-                }
-                const int64_t nitem = uniform(lds_load(&nsc[S_ITEM]));
-                bool walk = false;
-                int ndom = 0, ntx = 0, nty = 0, ntz = 0;
-                if (nitem < n_items) {
-                    const int64_t nit = FALLBACK ? (int64_t)a.ovf[nitem] : nitem;
-                    const int64_t ncell = a.targets ? a.targets[nit] : (int64_t)a.order[nit];
-                    if (ncell >= 0 && ncell < a.n_cells) {
-                        walk = true;
-                        ndom = a.cell_dom[ncell];
-                        const int4 ng = a.geo[a.cell_node[ncell]];
-                        const int nsz = ng.w & kSizeMask;
-                        ntx = 2 * ng.x + nsz;
-                        nty = 2 * ng.y + nsz;
-                        ntz = 2 * ng.z + nsz;
-                    }
-                }
-                const int *nper = a.periodic ? a.doms[ndom].ext : nullptr;
-                if (!kPair) {
-                    if (walk) {
-                        walk_target(a, a.doms[ndom].root, nper, ntx, nty, ntz, fr0, fr1, acc, nsc, fmax, amax, n_test,
-                                    FALLBACK);
-                        if (lane == 0) nsc[S_WALKED] = 1;
-                    }
-                } else {
-                    if (half == 0) {
-                        if (lane == 0) {
-                            nsc[S_PMEET] = 0;
-                            nsc[S_PNEXT] = 0;
-                            nsc[S_PACC] = 0;
-                            nsc[S_POVF] = 0;
-                            if (walk) fr0[0] = a.doms[ndom].root;
-                        }
-                        if (FALLBACK) wait_stores();   // (fr0 in device memory)
-                        if (lane == 0) lds_store(&nsc[S_PGEN], titer);
-                    }
-                    if (walk)
-                        walk_target_pair<kWalk>(a, half, nper, ntx, nty, ntz, fr0, fr1, acc, nsc, fmax, amax, n_test,
-                                                FALLBACK);
-                }
-            }
             ftarget += fsum + ((double)cs_hi + (double)cs_lo);
         }
         if (PASS && ++pass < npass) {
@@ -2007,13 +1970,13 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             double f = 0.0;
             for (int w = 0; w < WAVES; ++w) f += red[w];
             const double rtp = 0.5 * (double)tsize;
-            f += 3.0 * (double)tA.w / (4.0 * kPi * rtp * rtp);
+            f += 3.0 * (double)teps / (4.0 * kPi * rtp * rtp);
             a.f_out[o] = f * D.flux_unit;
             if (a.ion_out) a.ion_out[o] = f > 0.0 ? 1 : 0;
         }
-        bank ^= 1;
     }
     // statistics
+    n_acc = wave_sum(n_acc);
     n_test = wave_sum(n_test);
     n_guard = wave_sum(n_guard);
     n_f32 = wave_sum(n_f32);
@@ -2021,7 +1984,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     n_tab = wave_sum(n_tab);
     n_re = wave_sum(n_re);
     if (lane == 0) {
-        if (wave == 0 && n_acc > 0) atomicAdd(&a.stats[0], (unsigned long long)n_acc);
+        if (n_acc > 0) atomicAdd(&a.stats[0], (unsigned long long)n_acc);
         if (n_test > 0) atomicAdd(&a.stats[1], (unsigned long long)n_test);
         if (n_guard > 0) atomicAdd(&a.stats[2], (unsigned long long)n_guard);
         if (n_f32 > 0) atomicAdd(&a.stats[3], (unsigned long long)n_f32);
@@ -2347,6 +2310,9 @@ struct tr_ctx {
     size_t gbuf_bytes = 0;
     void *ebuf = nullptr;   // emission rows of split LDS buffers
     size_t ebuf_bytes = 0;
+    int32_t *lists = nullptr;            // the listed walks of a chunk of targets and their records
+    TargetRec *rec = nullptr;
+    int64_t list_targets = 0;
     int32_t *glist = nullptr;            // walk lists of the fallback pass
     int32_t *ovf = nullptr;              // items queued for it
     int64_t ovf_cap = 0;
@@ -2432,6 +2398,9 @@ void free_domains(tr_ctx *c)
     c->gbuf_bytes = 0;
     dfree(c->ebuf);
     c->ebuf_bytes = 0;
+    dfree(c->lists);
+    dfree(c->rec);
+    c->list_targets = 0;
     dfree(c->glist);
     dfree(c->ovf);
     c->ovf_cap = 0;
@@ -2480,14 +2449,13 @@ tr_status dalloc(tr_ctx *c, void **p, size_t bytes)
 }
 
 // LDS bytes of one sweep workgroup (must mirror the carve-up in k_sweep)
-size_t sweep_lds_bytes(size_t real, int npix, int stride_k, int nrm, int fmax, int amax, int waves, bool ldsbuf)
+size_t sweep_lds_bytes(size_t real, int npix, int stride_k, int nrm, int waves, bool ldsbuf)
 {
     size_t b = 0;
     if (ldsbuf) b += (((size_t)npix * stride_k * real + 15) / 16) * 16;
     b += 2 * (((size_t)nrm * real + 15) / 16) * 16;
     b += 2 * (size_t)nrm * 8;
-    b += 2 * (size_t)fmax * 4 + (size_t)amax * 4;
-    b += 2 * 16 * 4;
+    b += S_COUNT * 4;
     b += (size_t)waves * 8;
     b += (size_t)npix * 8 * (nrm > 64 ? 2 : 1);
     return b;
@@ -2548,7 +2516,8 @@ KernelFn pick_kernel(int waves, bool ldsbuf, bool fallback)
 
 struct LaunchPlan {
     KernelFn fn = nullptr, fn_fb = nullptr;
-    int waves = 0, blocks = 0, per_cu = 0, fmax = 0, amax = 0, stride_k = 0;
+    int waves = 0, blocks = 0, per_cu = 0, stride_k = 0;
+    int64_t chunk = 0;   // targets walked and listed at a time
     size_t lds = 0;
     bool ldsbuf = true;
     bool cas = false;   // FP32 LDS buffers accumulated by compare-and-swap
@@ -2577,16 +2546,13 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     const bool kv = !((c->p.eps_kernel == 0 || c->p.eps_kernel == 3) && (c->p.mass_kernel == 0 || c->p.mass_kernel == 5));
     if (kv) waves = waves <= 4 ? 4 : 8;
     L.waves = waves;
-    // per-level frontier and per-target accepted-node capacities (overflow is reported)
-    L.fmax = 512;
-    L.amax = 2048;
     int bm = buf_req > 0 ? buf_req : c->tuned_buf[f32 ? 1 : 0];
     // four rows per ray in LDS (odd stride: ray k of lane k hits distinct banks); else, in
     // FP32, the A, E, V rows in LDS and the emission rows in device memory; else all in
     // device memory
     const int stride4 = 4 * nrm + 1, stride3 = 3 * nrm + 1;
-    const bool fits4 = sweep_lds_bytes(real, npix, stride4, nrm, L.fmax, L.amax, waves, true) <= kLdsMax;
-    const bool fits3 = f32 && !kv && sweep_lds_bytes(real, npix, stride3, nrm, L.fmax, L.amax, waves, true) <= kLdsMax;
+    const bool fits4 = sweep_lds_bytes(real, npix, stride4, nrm, waves, true) <= kLdsMax;
+    const bool fits3 = f32 && !kv && sweep_lds_bytes(real, npix, stride3, nrm, waves, true) <= kLdsMax;
     // else (FP64, or radial-kernel variants) the rays in LDS for as many as fit, with four rows
     // per ray or (fewer passes) the split rows, a target's rays mapped and integrated in
     // passes over equal pixel ranges
@@ -2595,7 +2561,7 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     if (!fits4 && !fits3 && bm != 2 && !kv && (waves == 4 || waves == 8 || waves == 16)) {
         auto passes = [&](int stride) {   // passes of the largest ray count that fits (0: none)
             for (int r = npix - 1; r >= 16; --r)
-                if (sweep_lds_bytes(real, r, stride, nrm, L.fmax, L.amax, waves, true) <= kLdsMax) return (npix + r - 1) / r;
+                if (sweep_lds_bytes(real, r, stride, nrm, waves, true) <= kLdsMax) return (npix + r - 1) / r;
             return 0;
         };
         const int n4 = passes(stride4), n3 = kv ? 0 : passes(stride3);
@@ -2611,11 +2577,7 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     L.pass_rays = L.ldsbuf && !fits4 && !fits3 ? pass_rays : 0;
     L.split = L.ldsbuf && !fits4 && (fits3 || (L.pass_rays > 0 && pass_split));
     L.stride_k = L.split ? stride3 : stride4;
-    if (!L.ldsbuf) {
-        L.fmax = 1024;
-        L.amax = 4096;
-    }
-    L.lds = sweep_lds_bytes(real, L.pass_rays > 0 ? L.pass_rays : npix, L.stride_k, nrm, L.fmax, L.amax, waves, L.ldsbuf);
+    L.lds = sweep_lds_bytes(real, L.pass_rays > 0 ? L.pass_rays : npix, L.stride_k, nrm, waves, L.ldsbuf);
     if (kv) {
         L.fn = f32 ? pick_kernel_kv<float>(waves, L.ldsbuf, false) : pick_kernel_kv<double>(waves, L.ldsbuf, false);
         L.fn_fb = f32 ? pick_kernel_kv<float>(waves, L.ldsbuf, true) : pick_kernel_kv<double>(waves, L.ldsbuf, true);
@@ -2651,9 +2613,19 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     // (FP32 buffers march in FP32 by default, the FP64 form in FP64)
     L.intm = im > 0 ? im : (npix >= 192 ? 5 : 4) + (f32 ? 3 : 0);
     if (L.intm >= 6 && !f32) L.intm -= 3;
-    int64_t blocks = (int64_t)c->n_cu * L.per_cu;
-    if (blocks > n_items) blocks = std::max<int64_t>(1, n_items);
-    L.blocks = (int)blocks;
+    L.chunk = std::min<int64_t>(n_items, kListTargets);
+    L.blocks = (int)std::min<int64_t>((int64_t)c->n_cu * L.per_cu, L.chunk);
+    // (a captured step graph holds these too)
+    if (c->list_targets < L.chunk) {
+        drop_graph(c);
+        dfree(c->lists);
+        dfree(c->rec);
+        c->list_targets = 0;
+        if (dalloc(c, (void **)&c->lists, sizeof(int32_t) * (size_t)L.chunk * kListCap) ||
+            dalloc(c, (void **)&c->rec, sizeof(TargetRec) * (size_t)L.chunk))
+            return TR_ENOMEM;
+        c->list_targets = L.chunk;
+    }
     if (!c->glist &&
         dalloc(c, (void **)&c->glist, sizeof(int32_t) * (size_t)c->n_cu * kFallbackPerCu * 3 * kGlobalList))
         return TR_ENOMEM;
@@ -2738,8 +2710,10 @@ tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_o
     a.nside = c->p.nside;
     a.npix = 12 * c->p.nside * c->p.nside;
     a.subsample = c->p.subsample;
-    a.fmax = L.fmax;
-    a.amax = L.amax;
+    a.f32 = c->p.precision == TR_FP32C ? 1 : 0;
+    a.lists = c->lists;
+    a.rec = c->rec;
+    a.list_cap = kListCap;
     a.nr_max = c->nr_max;
     a.stride_k = L.stride_k;
     a.zeta_g = c->p.zeta_g;
@@ -2765,12 +2739,20 @@ tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_o
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, c->stream, c->queue, (int64_t)4, 0);
     hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, c->stream, c->stats, (int64_t)8);
     if (timed) HIPCHK(hipEventRecord(c->ev0, c->stream));
-    hipLaunchKernelGGL(L.fn, dim3(L.blocks), dim3(L.waves * 64), L.lds, c->stream, a);
-    // the targets whose walk lists did not fit in LDS, again with lists in device memory
-    // (one workgroup per compute unit; it ends at once when none was queued)
+    // the targets a chunk at a time: their walks, then their mapping and integration
+    for (int64_t i0 = 0; i0 < n; i0 += L.chunk) {
+        a.item0 = i0;
+        a.n_chunk = (int32_t)std::min<int64_t>(L.chunk, n - i0);
+        const int wb = std::min((a.n_chunk + kWalkWaves - 1) / kWalkWaves, c->n_cu * kWalkPerCu);
+        hipLaunchKernelGGL(k_walk, dim3(wb), dim3(kWalkWaves * 64), 0, c->stream, a);
+        hipLaunchKernelGGL(L.fn, dim3(std::min(L.blocks, a.n_chunk)), dim3(L.waves * 64), L.lds, c->stream, a);
+    }
+    // the targets whose walks did not fit in the lists, again with longer lists per workgroup
+    // (it ends at once when none was queued)
     {
+        a.list_cap = 0;   // (their lists hold every node in walk order)
         const size_t lds = sweep_lds_bytes(c->p.precision == TR_FP32C ? 4 : 8, L.pass_rays > 0 ? L.pass_rays : a.npix,
-                                           L.stride_k, c->nr_max, 0, 0, L.waves, L.ldsbuf);
+                                           L.stride_k, c->nr_max, L.waves, L.ldsbuf);
         hipLaunchKernelGGL(L.fn_fb, dim3(c->n_cu * std::min(L.per_cu, kFallbackPerCu)), dim3(L.waves * 64), lds,
                            c->stream, a);
     }

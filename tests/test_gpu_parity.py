@@ -587,3 +587,31 @@ def test_pair_batches(T, orc, nside, sub):
         g0, j0, st = gpu_sweep(T, P, prec, thin=True, targets=tg)
         assert 0 < st.nodes_tabulated < st.nodes_accepted * (12 * nside ** 2)
         compare(g0, j0, f0, i0, tol, name=f"pairs N_side {nside} s {sub} prec {prec}")
+
+
+@pytest.mark.parametrize("theta", [0.5, 0.35])
+def test_target_chunks(T, orc, theta):
+    """Targets are walked and listed 32768 at a time: a list of two chunks and
+    77 more, a bad index in each (NaN and an error at the sync), all other
+    targets as the oracle has them; theta 0.35 accepts more nodes than half a
+    list holds."""
+    P = W.small_lognormal(16, n_src=3, seed=60)
+    f0, i0 = orc_sweep(orc, P, thin=True, theta=theta)
+    n = P.total_cells()
+    tg = np.arange(2 * 32768 + 77, dtype=np.int64) % n
+    bad = [5, 32768 + 9, 65536 + 70]
+    tg[bad] = [-1, n, n + 7]
+    ok = np.ones(tg.size, bool)
+    ok[bad] = False
+    for prec, tol in ((T.TR_FP64, TOL64), (T.TR_FP32C, TOL32)):
+        with T.context_for(P, prec, theta=theta) as ctx:
+            ctx.build(torch.tensor(P.n_h[0], device="cuda"), thin=True)
+            out = torch.zeros(tg.size, dtype=torch.float64, device="cuda")
+            ion = torch.full((tg.size,), 7, dtype=torch.uint8, device="cuda")
+            ctx.sweep_targets(torch.tensor(tg, device="cuda"), out, ion)
+            with pytest.raises(T.TreeRayError) as e:
+                ctx.sync()
+            assert e.value.status == T.TR_EINVAL
+            g, j = out.cpu().numpy(), ion.cpu().numpy()
+        assert np.all(np.isnan(g[bad])) and np.all(j[bad] == 0)
+        compare(g[ok], j[ok], f0[tg[ok]], i0[tg[ok]], tol, name=f"chunks theta {theta} prec {prec}")
