@@ -18,6 +18,10 @@ constexpr double kJit0 = 4.1e-4, kJit1 = 7.3e-4, kJit2 = 2.3e-4;
 __device__ inline int lane_id() { return (int)__lane_id(); }
 
 __device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ inline uint64_t uniform(uint64_t v)
+{
+    return ((uint64_t)(unsigned)uniform((int)(v >> 32)) << 32) | (unsigned)uniform((int)v);
+}
 
 // Sum over the 64 lanes with DPP: an inclusive scan inside each row of 16
 // lanes (row_shr 1, 2, 4, 8), then row broadcasts of lanes 15 and 31; lane
@@ -397,19 +401,26 @@ __device__ inline int ang2pix_f(int ns, float x, float y, float z, float tol, bo
 // outer branch is the cubic with a double root at sqrt(3)/2 that equals A
 // at 1/2 and has leading coefficient a2.
 // ---------------------------------------------------------------------------
+// v, computed where this is written and not moved into a branch on a lane value.
+template <typename Real>
+__device__ inline Real here(Real v)
+{
+    __asm__ volatile("" : "+v"(v));
+    return v;
+}
+
 template <typename Real>
 __device__ inline Real wp_kernel(Real x)
 {
     const Real a1 = (Real)1.21, a2 = (Real)-6.35, A = (Real)0.408, M = (Real)1.184;
     const Real xe = (Real)0.86602540378443864676;
     const Real q = (Real)(2.0 * 0.408 * (2.0 + 1.73205080756887729353) + 0.5 * 6.35);
-    x = x < (Real)0 ? -x : x;
-    if (x < (Real)0.5) return (a1 * x - ((Real)0.5 * a1 + (Real)4 * (M - A))) * x * x + M;
-    if (x < xe) {
-        const Real u = x - xe;
-        return u * u * (a2 * x + q);
-    }
-    return (Real)0;
+    // (both branches computed and one selected: lanes fall on either side)
+    x = __builtin_elementwise_abs(x);
+    const Real inner = here((a1 * x - ((Real)0.5 * a1 + (Real)4 * (M - A))) * x * x + M);
+    const Real u = x - xe;
+    const Real outer = here(u * u * (a2 * x + q));
+    return x < (Real)0.5 ? inner : (x < xe ? outer : (Real)0);
 }
 
 }  // namespace tr

@@ -437,6 +437,12 @@ __device__ inline int table_key(const SweepArgs &a, int gw, int bx, int by, int 
 // the value's bits: the same correctly rounded FP32 sum in some order.  An
 // FP32 atomic add in LDS takes this chip 3 cycles a lane (195 for 64 lanes);
 // three adds by compare-and-swap take 50 to 70 cycles for 64 lanes.
+__device__ inline unsigned lds_swap(unsigned *q, unsigned expected, unsigned desired)
+{
+    __hip_atomic_compare_exchange_strong(q, &expected, desired, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+    return expected;   // what the word held
+}
 template <typename Real, int AM>
 __device__ inline void buf_add(Real *p, Real v)
 {
@@ -457,8 +463,9 @@ __device__ inline void buf_add(Real *p, Real v)
 }
 
 // Three adds at once (A, E, V of one ray point): in the compare-and-swap form
-// the three reads and then the three swaps are in flight together, and only a
-// swap that lost a race (another lane changed the value) is repeated.
+// the three reads and then the three swaps are in flight together.  Lanes that
+// meet on a point meet on all three rows and lose there to the same lane, so
+// the three are repeated together; one that is through adds zero.
 template <typename Real, int AM>
 __device__ inline void buf_add3(Real *p0, Real v0, Real *p1, Real v1, Real *p2, Real v2)
 {
@@ -467,20 +474,19 @@ __device__ inline void buf_add3(Real *p0, Real v0, Real *p1, Real v1, Real *p2, 
         unsigned o0 = __hip_atomic_load(q0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         unsigned o1 = __hip_atomic_load(q1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         unsigned o2 = __hip_atomic_load(q2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        unsigned r0 = atomicCAS(q0, o0, __float_as_uint(__uint_as_float(o0) + v0));
-        unsigned r1 = atomicCAS(q1, o1, __float_as_uint(__uint_as_float(o1) + v1));
-        unsigned r2 = atomicCAS(q2, o2, __float_as_uint(__uint_as_float(o2) + v2));
-        while (r0 != o0) {
-            o0 = r0;
-            r0 = atomicCAS(q0, o0, __float_as_uint(__uint_as_float(o0) + v0));
-        }
-        while (r1 != o1) {
-            o1 = r1;
-            r1 = atomicCAS(q1, o1, __float_as_uint(__uint_as_float(o1) + v1));
-        }
-        while (r2 != o2) {
-            o2 = r2;
-            r2 = atomicCAS(q2, o2, __float_as_uint(__uint_as_float(o2) + v2));
+        for (;;) {
+            const unsigned r0 = lds_swap(q0, o0, __float_as_uint(__uint_as_float(o0) + v0));
+            const unsigned r1 = lds_swap(q1, o1, __float_as_uint(__uint_as_float(o1) + v1));
+            const unsigned r2 = lds_swap(q2, o2, __float_as_uint(__uint_as_float(o2) + v2));
+            const bool d0 = r0 == o0, d1 = r1 == o1, d2 = r2 == o2;
+            if (d0 && d1 && d2) break;
+            // (a row that is through holds o + v now)
+            o0 = d0 ? __float_as_uint(__uint_as_float(o0) + v0) : r0;
+            o1 = d1 ? __float_as_uint(__uint_as_float(o1) + v1) : r1;
+            o2 = d2 ? __float_as_uint(__uint_as_float(o2) + v2) : r2;
+            v0 = d0 ? 0.0f : v0;
+            v1 = d1 ? 0.0f : v1;
+            v2 = d2 ? 0.0f : v2;
         }
     } else {
         buf_add<Real, AM>(p0, v0);
@@ -1183,9 +1189,10 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
         const Real h = (Real)size;
         hinv = frcp(h);   // a power of two: exact
         const Real rl = d - xe * h, rh = d + xe * h;
-        int l0 = rl > (Real)0 ? (int)fsqrt(rl * rc_inv) - 1 : 0;
-        int h0 = (int)fsqrt(rh * rc_inv) + 2;
-        l0 = l0 < 0 ? 0 : l0;
+        // the points inside the support, and one beyond it on either side at most (a square
+        // root that rounds across an integer loses none)
+        const int l0 = rl > (Real)0 ? (int)fsqrt(rl * rc_inv) : 0;
+        int h0 = (int)fsqrt(rh * rc_inv) + 1;
         h0 = h0 > nr - 1 ? nr - 1 : h0;
         Real sum = 0;
         int first = h0 + 1, npos = 0;   // the points with a weight (contiguous: the kernel is positive inside its support)
@@ -1283,10 +1290,12 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     const int n_tab = (int)__popcll(tmask);
     int ptot = 0;
     const int off = wave_excl_scan_dpp(in_tab ? tab & 127 : 0, ptot);
-    const int rank = in_tab ? bits_below(tmask) : n_tab + bits_below(~tmask);
+    const uint64_t nmask = uniform(~tmask);
+    const int rank_t = bits_below(tmask), rank_n = n_tab + bits_below(nmask);
+    const int rank = in_tab ? rank_t : rank_n;
     const int perm = __builtin_amdgcn_ds_permute(rank << 2, lane);
     const int offc = __shfl(off, perm, 64);
-    uint64_t rem = (cnt < 64 ? (1ull << cnt) - 1ull : ~0ull) & ~tmask;   // nodes to classify
+    uint64_t rem = (cnt < 64 ? (1ull << cnt) - 1ull : ~0ull) & nmask;   // nodes to classify
     int ready = -1, ready_nd = 0, ready_kc = 0;   // a classified node (its pairs in lanes 0 ..) that found no room
     for (int b = 0; b < ptot || rem != 0ull || ready >= 0; b += 64) {
         // --- the next 64 pairs: node (its lane) and kc = pixel | count << 16 (pixel < 2^16, count <= 64) ---
@@ -1389,11 +1398,11 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
             jqeps = __shfl(qeps, node, 64);
         }
         const Real jfb = -jwf;   // the bracket weight when there is no W_p support
-        Real *row = &R.A(k, jlo);
+        Real *row = R.b + ((int)__umul24(k, R.stride) + R.oa + jlo);
         Real fi = (Real)jlo;
         for (int io = 0; io < npt; ++io, ++row, fi += (Real)1) {
-            const Real w = jwf > (Real)0 ? smooth_kernel<Real>(mg, (rcoef * (fi * fi) - jd) * jhinv) * jwf
-                                         : (io == 0 ? jfb : (Real)1 - jfb);
+            const Real ws = here(smooth_kernel<Real>(mg, (rcoef * (fi * fi) - jd) * jhinv) * jwf);
+            const Real w = jwf > (Real)0 ? ws : (io == 0 ? jfb : (Real)1 - jfb);
             buf_add3<Real, ATOMIC>(row, wk * (w * ja), row + nrm, wk * (w * je), row + 2 * nrm, wk * (w * jv));
             if (KV && jemode != 0) {   // the emission row
                 const Real wq = emission_weight<Real>(jemode, jlo + io, io, jle, jne, jea, jeb, jfb, rcoef, jd, jhinv,
@@ -1836,18 +1845,21 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             if (pass == 0) claim();   // (visible to all after the mapping)
 
             // --- every wave maps an equal share of the table nodes and of the others, in
-            // rounds of at most 64 nodes (62 on average: each share is rounded; classifying a node takes a wave ten times as
-            // long as mapping one from the table, so the shares are equal in both) ---
+            // rounds of at most 64 nodes (62 on average: each share is rounded; classifying
+            // a node takes a wave ten times as long as mapping one from the table, so the
+            // shares are equal in both).  A share is every nc-th node of the walk: its nodes
+            // come level by level, so those of a batch have supports of similar length, but
+            // from all directions: siblings side by side would meet on the same rays' points
+            // (3.3 lanes on one point at N_side 2, 2.0 at N_side 4, against 1.6 and 1.1) ---
             {
                 const int rounds = (nt + no + 62 * WAVES - 1) / (62 * WAVES);
                 const int nc = max(rounds, 1) * WAVES;
                 for (int r = 0; r < rounds; ++r) {
-                    const int c = r * WAVES + wave;
-                    const int t0 = nt * c / nc, mt = nt * (c + 1) / nc - t0;
-                    const int o0 = no * c / nc, mo = no * (c + 1) / nc - o0;
+                    const int ct = r * WAVES + wave, co = nc - 1 - ct;
+                    const int mt = (nt - ct + nc - 1) / nc, mo = (no - co + nc - 1) / nc;
                     const int cnt = mt + mo;
                     int n = 0;
-                    if (lane < cnt) n = lane < mo ? list[a.list_cap - 1 - o0 - lane] : list[t0 + lane - mo];
+                    if (lane < cnt) n = lane < mo ? list[a.list_cap - 1 - co - nc * lane] : list[ct + nc * (lane - mo)];
                     map_nodes<Real, ATOMIC, KV, PASS>(a, R, emask, ew, per, rt, nr, rc_inv, rcoef, n, cnt, tx, ty, tz,
                                                       tsize, k0, np, n_guard, n_tab);
                 }
