@@ -12,7 +12,8 @@ namespace tr {
 
 constexpr int kBlock = 8;          // cells per block edge
 constexpr int kMaxRadial = 128;    // evaluation points per ray (two 64-bit masks)
-constexpr int kAtabRatios = 4;    // angular-weight table: nodes of 1, 2, 4 and 8 target sizes
+constexpr int kAtabRatios = 5;    // angular-weight table: nodes of 1, 2, 4, 8 and 16 target sizes
+constexpr unsigned kNoEntry = ~0u;
 constexpr int kMaxLevels = 24;
 constexpr int kListCap = 4096;         // accepted nodes listed per target, and
 constexpr int kListTargets = 1 << 15;  // targets walked and listed at a time (512 MB of lists)

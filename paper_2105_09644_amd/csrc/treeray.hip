@@ -387,11 +387,11 @@ struct SweepArgs {
     int32_t gfmax, gamax;
     int32_t pass_rays;   // > 0: the LDS ray buffers hold this many rays; a target's rays are mapped
                          // and integrated in passes over consecutive pixel ranges
-    // angular-weight table (NULL: none): for a node of 1, 2, 4 or 8 times the
-    // target's size (ri = 0 .. 3) at offset o in target sizes from the
-    // target's lower corner, |o_a| <= atab_w[ri], the entry
+    // angular-weight table (NULL: none): for a node of 2^ri times the target's
+    // size (ri < kAtabRatios) at offset o in target sizes from the target's
+    // lower corner, |o_a| <= atab_w[ri], the entry
     // atab_idx[atab_base[ri] + ((o_x + w)(2w + 1) + o_y + w)(2w + 1) + o_z + w]
-    // = (first pair << 7) | pairs, each pair in atab_pool = pixel | count << 16
+    // = (first pair << 6) | (pairs - 1), each pair in atab_pool = pixel | count << 16
     const int32_t *atab_idx;
     const int32_t *atab_pool;
     int32_t atab_w[kAtabRatios], atab_base[kAtabRatios];
@@ -416,20 +416,26 @@ struct RayRows {
 };
 
 // Index into the angular table of a node whose cube has its (shifted) corner
-// at (bx, by, bz), or -1: a cube of 1, 2, 4 or 8 target sizes within the
+// at (bx, by, bz), or -1: a cube of 1, 2, 4, ... target sizes within the
 // table's window; offsets of its corner in target sizes (exact).
 __device__ inline int table_key(const SweepArgs &a, int gw, int bx, int by, int bz, int tx, int ty, int tz, int tsize)
 {
     const int size = gw & kSizeMask;
     if (!a.atab_idx || (gw & kPartialBit)) return -1;
-    const int ri = size == tsize ? 0 : size == 2 * tsize ? 1 : size == 4 * tsize ? 2 : size == 8 * tsize ? 3 : -1;
-    if (ri < 0) return -1;
-    const int sh = __builtin_ctz((unsigned)tsize);
+    const int sh = __builtin_ctz((unsigned)tsize);   // (sizes are powers of two)
+    const int ri = __builtin_ctz((unsigned)size) - sh;
+    if ((unsigned)ri >= (unsigned)kAtabRatios) return -1;
+    int w = a.atab_w[0], base = a.atab_base[0];
+#pragma unroll
+    for (int q = 1; q < kAtabRatios; ++q) {
+        w = ri == q ? a.atab_w[q] : w;
+        base = ri == q ? a.atab_base[q] : base;
+    }
     const int kx = (bx - ((tx - tsize) >> 1)) >> sh, ky = (by - ((ty - tsize) >> 1)) >> sh,
               kz = (bz - ((tz - tsize) >> 1)) >> sh;
-    const int w = a.atab_w[ri], nw = 2 * w + 1;
+    const int nw = 2 * w + 1;   // (w = -1: this ratio is not tabulated)
     if (abs(kx) > w || abs(ky) > w || abs(kz) > w) return -1;
-    return a.atab_base[ri] + ((kx + w) * nw + (ky + w)) * nw + (kz + w);
+    return base + ((kx + w) * nw + (ky + w)) * nw + (kz + w);
 }
 
 // Accumulation into a ray buffer shared by the lanes and waves of a workgroup.
@@ -1140,6 +1146,78 @@ __device__ inline Real emission_weight(int mode, int i, int io, int le, int ne, 
 // registers, so the loop over them makes no memory round trip besides its
 // atomics.
 // KV: the radial-kernel variants of App. A (otherwise two-point W_f,3 and W_p)
+// A lane's place in the s^3 sub-point lattice of a node's box (lanes from s^3
+// on have none).
+struct Lattice {
+    int s, ia, ib, ic;
+    float ca, cb, cc;   // index + 1/2 + the fixed shift
+    bool active;
+    uint64_t mask;
+    __device__ Lattice(int s_) : s(s_)
+    {
+        const int lane = lane_id();
+        ia = lane / (s * s);
+        ib = (lane / s) % s;
+        ic = lane % s;
+        ca = ((float)ia + 0.5f) + (float)kJit0;
+        cb = ((float)ib + 0.5f) + (float)kJit1;
+        cc = ((float)ic + 0.5f) + (float)kJit2;
+        active = lane < s * s * s;
+        mask = __ballot(active);
+    }
+};
+
+// A node's box: its lower corner relative to the target and its sub-box steps
+// in FP32, and the same as integers (corner, extent in finest cells).
+struct Box {
+    float o[3], step[3];
+    int b[3], e[3];
+};
+
+// The pixels of a box's sub-points, by a whole wave (lane = sub-point): FP32
+// with a guard band, FP64 inside it, so the FP64 classifier's pixel for every
+// sub-point.  Returns the number of distinct pixels; lane q of kc holds the
+// q-th and its sub-point count, pixel | count << 16.  PASS: the pixels k0 ..
+// k0 + np - 1 only, as local indices.
+template <bool PASS>
+__device__ __forceinline__ int classify_box(const Lattice &L, int ns, int npix, float guard_tol, const Box &box, int tx,
+                                            int ty, int tz, int k0, int np, int32_t *flag, double &guard_count, int &kc)
+{
+    const int lane = lane_id();
+    const float vx = fmaf(L.ca, box.step[0], box.o[0]);
+    const float vy = fmaf(L.cb, box.step[1], box.o[1]);
+    const float vz = fmaf(L.cc, box.step[2], box.o[2]);
+    bool unsure = false;
+    int pix = ang2pix_f(ns, vx, vy, vz, guard_tol, unsure);
+    unsure &= L.active;
+    if (__ballot(unsure)) {
+        if (unsure) {
+            pix = subpoint_pix_d(ns, L.s, box.b[0], box.b[1], box.b[2], box.e[0], box.e[1], box.e[2], tx, ty, tz, L.ia,
+                                 L.ib, L.ic);
+            guard_count += 1.0;
+        }
+    }
+    if ((unsigned)pix >= (unsigned)npix) {
+        // cannot happen for a finite direction: reported, never written out of bounds
+        atomicOr(flag, 4);
+        pix = 0;
+    }
+    uint64_t left = L.mask;
+    int nd = 0;
+    while (left) {
+        const int first = __ffsll((unsigned long long)left) - 1;
+        const int k = __builtin_amdgcn_readlane(pix, first);
+        const uint64_t m = __ballot(pix == k) & left;
+        left &= ~m;
+        if (!PASS || (unsigned)(k - k0) < (unsigned)np) {
+            const int v = (k - k0) | ((int)__popcll(m) << 16);   // uniform
+            kc = lane == nd ? v : kc;
+            ++nd;
+        }
+    }
+    return nd;
+}
+
 template <typename Real, int ATOMIC, bool KV, bool PASS>
 __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned long long *emask, int ew, const int *per,
                           const Real *rt, int nr,
@@ -1157,7 +1235,7 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     // 2 a smoothing kernel scaled by ea, 3 the mass fall-back weights
     int emode = 0, le = 0, ne = 0;
     Real ea = 0, eb = 0, qeps = 0;
-    int tab = -1;   // the node's angular-table entry (-1: classify its sub-points)
+    unsigned tab = kNoEntry;   // the node's angular-table entry (none: classify its sub-points)
     const bool mg = KV && a.mass_gauss != 0;
     if (lane < cnt) {
         const int4 g = a.geo[n];
@@ -1182,7 +1260,7 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
             bz += shz;
         }
         const int key = table_key(a, g.w, bx, by, bz, tx, ty, tz, tsize);
-        if (key >= 0) tab = a.atab_idx[key];
+        if (key >= 0) tab = (unsigned)a.atab_idx[key];
         const Real dxc = (A.x + (Real)shx) - (Real)0.5 * (Real)tx, dyc = (A.y + (Real)shy) - (Real)0.5 * (Real)ty,
                    dzc = (A.z + (Real)shz) - (Real)0.5 * (Real)tz;
         d = fsqrt(dxc * dxc + dyc * dyc + dzc * dzc);
@@ -1261,16 +1339,11 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     }
 
     // ---------------- phase 2 ----------------
-    const int s = a.subsample, s3 = s * s * s;
     const int ns = a.nside;
     const int nrm = a.nr_max;
-    const bool active = lane < s3;
-    const int ia = lane / (s * s), ib = (lane / s) % s, ic = lane % s;
-    const float ca = ((float)ia + 0.5f) + (float)kJit0, cb = ((float)ib + 0.5f) + (float)kJit1,
-                cc = ((float)ic + 0.5f) + (float)kJit2;
-    const float inv_s = 1.0f / (float)s;
-    const Real inv_s3 = (Real)1 / (Real)s3;
-    const uint64_t act_mask = __ballot(active);
+    const Lattice L(a.subsample);
+    const Real inv_s3 = (Real)1 / (Real)(a.subsample * a.subsample * a.subsample);
+    const float inv_s = 1.0f / (float)a.subsample;
     // each below 256; bit 24: the node emits (two-point emission weights e0, e1)
     const bool emits = e0 != (Real)0 || e1 != (Real)0;
     const int packed = lo | (nsup << 8) | (ie << 16) | (emits ? 1 << 24 : 0);
@@ -1284,12 +1357,12 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     const float sx = (float)ex * inv_s, sy = (float)ey * inv_s, sz = (float)ez * inv_s;
     // The table nodes' pairs laid end to end: node n's start at off; lane q of
     // perm holds the lane of the q-th table node, offc its start.
-    const bool in_tab = tab >= 0;
+    const bool in_tab = tab != kNoEntry;
     tab_count += in_tab ? 1.0 : 0.0;
     const uint64_t tmask = __ballot(in_tab);
     const int n_tab = (int)__popcll(tmask);
     int ptot = 0;
-    const int off = wave_excl_scan_dpp(in_tab ? tab & 127 : 0, ptot);
+    const int off = wave_excl_scan_dpp(in_tab ? (int)(tab & 63u) + 1 : 0, ptot);
     const uint64_t nmask = uniform(~tmask);
     const int rank_t = bits_below(tmask), rank_n = n_tab + bits_below(nmask);
     const int rank = in_tab ? rank_t : rank_n;
@@ -1309,10 +1382,11 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
             const uint64_t bit = is_node && rel > 0 && rel < 64 ? 1ull << (rel - 1) : 0ull;
             const uint64_t S = ((uint64_t)(unsigned)wave_or((int)(bit >> 32)) << 32) | (unsigned)wave_or((int)bit);
             node = __shfl(perm, r0 + bits_below(S), 64);
-            const int tn = __shfl(tab, node, 64), on = __shfl(off, node, 64);
+            const unsigned tn = (unsigned)__shfl((int)tab, node, 64);
+            const int on = __shfl(off, node, 64);
             fill = ptot - b < 64 ? ptot - b : 64;
             valid = lane < fill;
-            if (valid) kc = a.atab_pool[(tn >> 7) + (b + lane - on)];
+            if (valid) kc = a.atab_pool[(int)(tn >> 6) + (b + lane - on)];
             if (PASS) {   // the pass's pixels only, as local ray indices
                 kc -= k0;
                 valid = valid && (unsigned)(kc & 0xffff) < (unsigned)np;
@@ -1323,42 +1397,13 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
             if (ready < 0) {
                 const int j = __ffsll((unsigned long long)rem) - 1;
                 rem &= rem - 1;
-                // FP32 with a guard band, FP64 inside it: the FP64 classifier's pixel
-                // for every sub-point, in both precisions
-                const float vx = fmaf(ca, rdlane(sx, j), rdlane(ox, j));
-                const float vy = fmaf(cb, rdlane(sy, j), rdlane(oy, j));
-                const float vz = fmaf(cc, rdlane(sz, j), rdlane(oz, j));
-                bool unsure = false;
-                int pix = ang2pix_f(ns, vx, vy, vz, a.guard_tol, unsure);
-                unsure &= active;
-                if (__ballot(unsure)) {
-                    const int jbx = rdlane(bx, j), jby = rdlane(by, j), jbz = rdlane(bz, j);
-                    const int jex = rdlane(ex, j), jey = rdlane(ey, j), jez = rdlane(ez, j);
-                    if (unsure) {
-                        pix = subpoint_pix_d(ns, s, jbx, jby, jbz, jex, jey, jez, tx, ty, tz, ia, ib, ic);
-                        guard_count += 1.0;
-                    }
-                }
-                if ((unsigned)pix >= (unsigned)a.npix) {
-                    // cannot happen for a finite direction: reported, never written out of bounds
-                    atomicOr(&a.queue[1], 4);
-                    pix = 0;
-                }
-                // the distinct pixels
-                uint64_t left = act_mask;
-                ready_nd = 0;
-                while (left) {
-                    const int first = __ffsll((unsigned long long)left) - 1;
-                    const int k = __builtin_amdgcn_readlane(pix, first);
-                    const uint64_t m = __ballot(pix == k) & left;
-                    left &= ~m;
-                    // (a pass keeps its own pixels, as local ray indices)
-                    if (!PASS || (unsigned)(k - k0) < (unsigned)np) {
-                        const int v = (k - k0) | ((int)__popcll(m) << 16);   // uniform
-                        ready_kc = lane == ready_nd ? v : ready_kc;
-                        ++ready_nd;
-                    }
-                }
+                Box box;
+                box.o[0] = rdlane(ox, j); box.o[1] = rdlane(oy, j); box.o[2] = rdlane(oz, j);
+                box.step[0] = rdlane(sx, j); box.step[1] = rdlane(sy, j); box.step[2] = rdlane(sz, j);
+                box.b[0] = rdlane(bx, j); box.b[1] = rdlane(by, j); box.b[2] = rdlane(bz, j);
+                box.e[0] = rdlane(ex, j); box.e[1] = rdlane(ey, j); box.e[2] = rdlane(ez, j);
+                ready_nd = classify_box<PASS>(L, ns, a.npix, a.guard_tol, box, tx, ty, tz, k0, np, &a.queue[1],
+                                              guard_count, ready_kc);
                 ready = j;
             }
             if (fill + ready_nd > 64) break;   // (a node has at most 64 pairs: it fits in the next 64)
@@ -2064,71 +2109,59 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_pass_fallback(SweepArgs
 // ---------------------------------------------------------------------------
 // Angular-weight table (Sec. 2.3 "Mapping nodes onto rays").  A node's
 // angular weights depend only on its box relative to the target; for nodes of
-// 1, 2 or 4 times the target's size they are tabulated once per context by
-// offset, in units of the target's size, with the FP64 classifier the sweep
-// itself uses: relative sub-point positions scale exactly with the size, so a
-// table entry holds exactly what the sweep would compute for that node.  One
-// thread per offset; first the number of distinct pixels, then (after a
-// prefix sum on the host) the pairs themselves, in the order of first
-// appearance over the sub-points.
+// 1, 2, 4, ... times the target's size they are tabulated once per context by
+// offset, in units of the target's size, with the classifier the sweep itself
+// uses: relative sub-point positions scale exactly with the size, so a table
+// entry holds exactly what the sweep would compute for that node.  A wave
+// takes a contiguous run of offsets: first (idx NULL) it counts their pairs,
+// then, with the runs' first pairs known, it writes them.  A wave per offset
+// classifies in FP32 with the FP64 guard band: 1.2 ms for 4.8 million offsets
+// where a thread per offset in FP64 took 1 ms for 0.6 million.
 // ---------------------------------------------------------------------------
 struct AtabGeom {
     int32_t w[kAtabRatios], base[kAtabRatios], nkeys;
 };
 
-__device__ inline void atab_key(const AtabGeom &G, int key, int &r, int &ox, int &oy, int &oz)
+__global__ __launch_bounds__(256) void k_atab(AtabGeom G, int ns, int s, float guard_tol, int run, int64_t *__restrict__ sums,
+                                              int32_t *__restrict__ idx, int32_t *__restrict__ pool, int32_t *flag)
 {
-    int ri = 0;
-    while (ri + 1 < kAtabRatios && key >= G.base[ri + 1]) ++ri;
-    int k = key - G.base[ri];
-    const int w = G.w[ri], n = 2 * w + 1;
-    oz = k % n - w;
-    k /= n;
-    oy = k % n - w;
-    ox = k / n - w;
-    r = 1 << ri;
-}
-
-__device__ int atab_pairs(const AtabGeom &G, int key, int ns, int s, int *pix, int *cnt)
-{
-    int r, ox, oy, oz;
-    atab_key(G, key, r, ox, oy, oz);
-    int npl = 0;
-    for (int ia = 0; ia < s; ++ia)
-        for (int ib = 0; ib < s; ++ib)
-            for (int ic = 0; ic < s; ++ic) {
-                // a unit target with its lower corner at the origin: twice its centre is (1, 1, 1)
-                const int p = subpoint_pix_d(ns, s, ox, oy, oz, r, r, r, 1, 1, 1, ia, ib, ic);
-                int q = 0;
-                while (q < npl && pix[q] != p) ++q;
-                if (q == npl) {
-                    pix[npl] = p;
-                    cnt[npl] = 0;
-                    ++npl;
-                }
-                ++cnt[q];
+    const int wave = uniform((int)(blockIdx.x * 4 + (threadIdx.x >> 6))), lane = lane_id();
+    const Lattice L(s);
+    int64_t at = idx ? sums[wave] : 0;
+    double guard = 0;
+    for (int key = wave * run; key < min((wave + 1) * run, G.nkeys); ++key) {
+        int ri = 0;
+#pragma unroll
+        for (int q = 1; q < kAtabRatios; ++q)
+            if (G.w[q] >= 0 && key >= G.base[q]) ri = q;
+        int w = G.w[0], k = key - G.base[0];
+#pragma unroll
+        for (int q = 1; q < kAtabRatios; ++q)
+            if (ri == q) {
+                w = G.w[q];
+                k = key - G.base[q];
             }
-    return npl;
-}
-
-__global__ void k_atab_count(AtabGeom G, int ns, int s, int32_t *npairs)
-{
-    const int key = blockIdx.x * blockDim.x + threadIdx.x;
-    if (key >= G.nkeys) return;
-    int pix[64], cnt[64];
-    npairs[key] = atab_pairs(G, key, ns, s, pix, cnt);
-}
-
-__global__ void k_atab_fill(AtabGeom G, int ns, int s, const int32_t *__restrict__ first, int32_t *idx,
-                            int32_t *pool)
-{
-    const int key = blockIdx.x * blockDim.x + threadIdx.x;
-    if (key >= G.nkeys) return;
-    int pix[64], cnt[64];
-    const int n = atab_pairs(G, key, ns, s, pix, cnt);
-    const int f = first[key];
-    for (int q = 0; q < n; ++q) pool[f + q] = pix[q] | (cnt[q] << 16);
-    idx[key] = (f << 7) | n;
+        const int n = 2 * w + 1;
+        Box box;
+        box.b[2] = k % n - w;
+        k /= n;
+        box.b[1] = k % n - w;
+        box.b[0] = k / n - w;
+        for (int q = 0; q < 3; ++q) {
+            box.e[q] = 1 << ri;
+            // a unit target with its lower corner at the origin: twice its centre is (1, 1, 1)
+            box.o[q] = 0.5f * (float)(2 * box.b[q] - 1);
+            box.step[q] = (float)(1 << ri) * (1.0f / (float)s);
+        }
+        int kc = 0;
+        const int nd = classify_box<false>(L, ns, 12 * ns * ns, guard_tol, box, 1, 1, 1, 0, 0, flag, guard, kc);
+        if (idx) {
+            if (lane < nd) pool[at + lane] = kc;
+            if (lane == 0) idx[key] = (int32_t)(((unsigned)at << 6) | (unsigned)(nd - 1));
+        }
+        at += nd;
+    }
+    if (!idx && lane == 0) sums[wave] = at;
 }
 
 // The domain of a cell: from the per-cell array of a context, or from the
@@ -2679,6 +2712,8 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     return TR_OK;
 }
 
+float guard_tolerance(int nside);
+
 tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_out, uint8_t *ion, bool timed,
                        int waves_req, int tpc_req, int buf_req, int int_req, int atom_req = 0)
 {
@@ -2716,9 +2751,7 @@ tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_o
     a.theta2 = c->p.theta * c->p.theta;
     a.theta_if2 = c->p.theta_if > 0.0 ? c->p.theta_if * c->p.theta_if : 0.0;
     a.theta_src2 = c->p.theta_src > 0.0 ? c->p.theta_src * c->p.theta_src : 0.0;
-    // guard band: 1e-5 N_side (at least 2e-5), several times the worst-case
-    // FP32 error of the pixel-edge quantities (a few 1e-7 N_side)
-    a.guard_tol = 1e-5f * std::max(2.0f, (float)c->p.nside);
+    a.guard_tol = guard_tolerance(c->p.nside);
     a.nside = c->p.nside;
     a.npix = 12 * c->p.nside * c->p.nside;
     a.subsample = c->p.subsample;
@@ -2842,59 +2875,87 @@ tr_status upload_gauss_legendre(tr_ctx *c)
     return TR_OK;
 }
 
-// The angular-weight table of the context's N_side and s: offsets up to
-// (2/theta + 1) r target sizes per axis for nodes of r = 1, 2, 4 target sizes
-// (every node the Barnes-Hut walk accepts at theta_lim lies inside), capped so
-// that the table stays small; nodes outside classify their sub-points.
+// Guard band of the FP32 pixel classifier: 1e-5 N_side (at least 2e-5), several
+// times the worst-case FP32 error of the pixel-edge quantities (a few 1e-7 N_side).
+float guard_tolerance(int nside) { return 1e-5f * std::max(2.0f, (float)nside); }
+
+// The angular-weight table of the context's N_side and s: for nodes of r = 1,
+// 2, 4, 8, 16 target sizes the offsets up to (2/theta + 1) r target sizes per
+// axis (every node accepted at the smallest opening angle lies inside); nodes
+// outside classify their sub-points.  Classifying a node in the sweep takes
+// about 150 vector instructions of a wave more than reading its entry, and
+// building an entry twice that: a ratio gets at most 32 entries per cell
+// (a target accepts about 50 nodes of each of the middle ratios), so that the
+// table has paid for itself within about two sweeps, at least 65536 and at
+// most 4.5 million (theta 0.5 needs 4.2 million at r = 16; the next would
+// need 33 million, half a GB, for 4% of the nodes).
 tr_status build_angular_table(tr_ctx *c)
 {
     const int s = c->p.subsample, ns = c->p.nside;
-    const double th = c->p.theta > 0.05 ? c->p.theta : 0.05;
-    const int cap[kAtabRatios] = {12, 20, 24, 40};
-    AtabGeom G{};
-    int64_t nk = 0;
-    for (int q = 0; q < kAtabRatios; ++q) {
-        const int w = std::min(cap[q], (int)std::ceil((2.0 / th + 1.0) * (double)(1 << q)));
-        G.w[q] = w;
-        G.base[q] = (int32_t)nk;
-        nk += (int64_t)(2 * w + 1) * (2 * w + 1) * (2 * w + 1);
-    }
-    G.nkeys = (int32_t)nk;
-    int32_t *cnt = nullptr;
-    tr_status st;
-    if ((st = dalloc(c, (void **)&cnt, sizeof(int32_t) * (size_t)nk))) return st;
-    hipLaunchKernelGGL(k_atab_count, dim3(grid1(nk, 64)), dim3(64), 0, c->stream, G, ns, s, cnt);
-    std::vector<int32_t> h((size_t)nk);
-    if (hipMemcpyAsync(h.data(), cnt, sizeof(int32_t) * (size_t)nk, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-        hipStreamSynchronize(c->stream) != hipSuccess) {
-        dfree(cnt);
-        return fail(c, TR_EHIP, "angular table: counting failed");
-    }
-    int64_t tot = 0;
-    for (auto &v : h) {
-        const int32_t n = v;
-        v = (int32_t)tot;   // first pair of each entry
-        tot += n;
-    }
-    if (tot >= (1ll << 24)) {   // (first << 7) | pairs must fit an int: keep classifying instead
-        dfree(cnt);
+    double th = c->p.theta;
+    if (c->p.theta_if > 0.0) th = std::min(th, c->p.theta_if);
+    if (c->p.theta_src > 0.0) th = std::min(th, c->p.theta_src);
+    th = std::max(th, 0.05);
+    const double most = std::min(4.5e6, std::max(65536.0, 32.0 * (double)c->n_cells));
+    int root = 1;   // nodes as large as the root are never accepted
+    for (auto &t : c->topo) root = std::max(root, t.root_size);
+    for (int ratios = kAtabRatios; ratios > 0; --ratios) {
+        AtabGeom G{};
+        int64_t nk = 0;
+        for (int q = 0; q < kAtabRatios; ++q) {
+            G.base[q] = (int32_t)nk;
+            G.w[q] = -1;
+            if (q >= ratios || (1 << q) >= root) continue;
+            G.w[q] = (int)std::min(std::ceil((2.0 / th + 1.0) * (double)(1 << q)), std::floor((std::cbrt(most) - 1.0) / 2.0));
+            nk += (int64_t)(2 * G.w[q] + 1) * (2 * G.w[q] + 1) * (2 * G.w[q] + 1);
+        }
+        G.nkeys = (int32_t)nk;
+        if (nk == 0) return TR_OK;
+        const int waves = 4 * (int)std::min<int64_t>((nk + 255) / 256, (int64_t)c->n_cu * 16);
+        const int run = (int)((nk + waves - 1) / waves);
+        int64_t *sums = nullptr;
+        tr_status st;
+        if ((st = dalloc(c, (void **)&sums, sizeof(int64_t) * (size_t)waves))) return st;
+        auto launch = [&](int32_t *idx, int32_t *pool) {
+            hipLaunchKernelGGL(k_atab, dim3(waves / 4), dim3(256), 0, c->stream, G, ns, s, guard_tolerance(ns), run, sums,
+                               idx, pool, c->queue + 1);
+        };
+        launch(nullptr, nullptr);
+        std::vector<int64_t> h((size_t)waves);
+        if (hipMemcpyAsync(h.data(), sums, sizeof(int64_t) * (size_t)waves, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+            hipStreamSynchronize(c->stream) != hipSuccess) {
+            dfree(sums);
+            return fail(c, TR_EHIP, "angular table: counting failed");
+        }
+        int64_t tot = 0;
+        for (auto &v : h) {
+            const int64_t n = v;
+            v = tot;   // first pair of each run
+            tot += n;
+        }
+        if (tot >= (1ll << 26) - 64) {   // (first << 6) | (pairs - 1) must fit: without the largest ratio
+            dfree(sums);
+            continue;
+        }
+        if ((st = dalloc(c, (void **)&c->atab_pool, sizeof(int32_t) * (size_t)tot)) ||
+            (st = dalloc(c, (void **)&c->atab_idx, sizeof(int32_t) * (size_t)nk))) {
+            dfree(sums);
+            return st;
+        }
+        hipError_t e = hipMemcpyAsync(sums, h.data(), sizeof(int64_t) * (size_t)waves, hipMemcpyHostToDevice, c->stream);
+        if (e == hipSuccess) {
+            launch(c->atab_idx, c->atab_pool);
+            e = hipStreamSynchronize(c->stream);
+        }
+        dfree(sums);
+        if (e != hipSuccess) {
+            dfree(c->atab_idx);
+            dfree(c->atab_pool);
+            return fail(c, TR_EHIP, std::string("angular table: ") + hipGetErrorString(e));
+        }
+        c->atab = G;
         return TR_OK;
     }
-    if ((st = dalloc(c, (void **)&c->atab_pool, sizeof(int32_t) * (size_t)std::max<int64_t>(tot, 1))) ||
-        (st = dalloc(c, (void **)&c->atab_idx, sizeof(int32_t) * (size_t)nk))) {
-        dfree(cnt);
-        return st;
-    }
-    if (hipMemcpyAsync(cnt, h.data(), sizeof(int32_t) * (size_t)nk, hipMemcpyHostToDevice, c->stream) != hipSuccess) {
-        dfree(cnt);
-        return fail(c, TR_EHIP, "angular table: upload failed");
-    }
-    hipLaunchKernelGGL(k_atab_fill, dim3(grid1(nk, 64)), dim3(64), 0, c->stream, G, ns, s, cnt, c->atab_idx,
-                       c->atab_pool);
-    const hipError_t e = hipStreamSynchronize(c->stream);
-    dfree(cnt);
-    if (e != hipSuccess) return fail(c, TR_EHIP, std::string("angular table: ") + hipGetErrorString(e));
-    c->atab = G;
     return TR_OK;
 }
 
