@@ -17,6 +17,14 @@ constexpr double kJit0 = 4.1e-4, kJit1 = 7.3e-4, kJit2 = 2.3e-4;
 // ---------------------------------------------------------------------------
 __device__ inline int lane_id() { return (int)__lane_id(); }
 
+// v, computed where this is written and not moved into a branch on a lane value.
+template <typename Real>
+__device__ inline Real here(Real v)
+{
+    __asm__ volatile("" : "+v"(v));
+    return v;
+}
+
 __device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ inline uint64_t uniform(uint64_t v)
 {
@@ -401,14 +409,6 @@ __device__ inline int ang2pix_f(int ns, float x, float y, float z, float tol, bo
 // outer branch is the cubic with a double root at sqrt(3)/2 that equals A
 // at 1/2 and has leading coefficient a2.
 // ---------------------------------------------------------------------------
-// v, computed where this is written and not moved into a branch on a lane value.
-template <typename Real>
-__device__ inline Real here(Real v)
-{
-    __asm__ volatile("" : "+v"(v));
-    return v;
-}
-
 template <typename Real>
 __device__ inline Real wp_kernel(Real x)
 {

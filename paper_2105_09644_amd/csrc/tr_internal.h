@@ -16,7 +16,7 @@ constexpr int kAtabRatios = 5;    // angular-weight table: nodes of 1, 2, 4, 8 a
 constexpr unsigned kNoEntry = ~0u;
 constexpr int kMaxLevels = 24;
 constexpr int kListCap = 4096;         // accepted nodes listed per target, and
-constexpr int kListTargets = 1 << 15;  // targets walked and listed at a time (512 MB of lists)
+constexpr int kListTargets = 1 << 15;  // targets walked and listed at a time (1 GB of lists)
 constexpr int kWalkFront = 1024;       // frontier entries of a walk in LDS
 constexpr int kWalkPerCu = 5;          // workgroups per compute unit of the walk kernel
 constexpr int kGlobalList = 1 << 16;   // frontier / accepted-list entries of the fallback walk

@@ -397,8 +397,7 @@ struct SweepArgs {
     int32_t atab_w[kAtabRatios], atab_base[kAtabRatios];
 };
 
-// ray buffer rows: eps, A (recombinations), E (previous flux x volume), V
-enum { Q_EPS = 0, Q_A = 1, Q_E = 2, Q_V = 3 };
+// Ray buffer rows: eps, A (recombinations), E (previous flux x volume), V.
 
 // Where ray k's rows live: A, E and V of point i at b[k stride + oa + (0, 1, 2) nrm + i],
 // the emission at e[k estride + i].  Either one buffer with four rows per ray
@@ -1007,7 +1006,7 @@ template <typename Real, int G>
 __device__ __forceinline__ void march_batch(const SweepArgs &a, const RayRows<Real> &R, int myk, unsigned long long m0,
                                             unsigned long long m1, Real rcoef,
                                             const double *rd, const double *rd2, int nr, bool split, double &fsum,
-                                            float &cs_hi, float &cs_lo, double &n_f32, double &n_f64)
+                                            float &cs_hi, float &cs_lo, uint64_t &n_f32, uint64_t &n_f64)
 {
     const int lane = lane_id();
     const bool has = myk >= 0;
@@ -1027,14 +1026,14 @@ __device__ __forceinline__ void march_batch(const SweepArgs &a, const RayRows<Re
                 cs_hi = sh;
                 cs_lo += se + fl;
             }
-            n_f32 += ok ? 1.0 : 0.0;
+            n_f32 += __popcll(__ballot(ok));
             // the rays near an ionisation front, again in FP64
             const bool redo = has && near;
             if (__ballot(head && redo)) {
                 const double f = integrate_rays_group<Real, G>(R, redo ? myk : 0, m0, m1, redo, tmax, rd, rd2, nr,
                                                                a.nside, a.zeta_g, over, split);
                 if (head && redo) fsum += f;
-                n_f64 += head && redo ? 1.0 : 0.0;
+                n_f64 += __popcll(__ballot(head && redo));
             }
             return;
         }
@@ -1155,7 +1154,7 @@ struct Lattice {
     uint64_t mask;
     __device__ Lattice(int s_) : s(s_)
     {
-        const int lane = lane_id();
+        const int lane = here(lane_id());   // (not held in registers between nodes)
         ia = lane / (s * s);
         ib = (lane / s) % s;
         ic = lane % s;
@@ -1181,7 +1180,7 @@ struct Box {
 // k0 + np - 1 only, as local indices.
 template <bool PASS>
 __device__ __forceinline__ int classify_box(const Lattice &L, int ns, int npix, float guard_tol, const Box &box, int tx,
-                                            int ty, int tz, int k0, int np, int32_t *flag, double &guard_count, int &kc)
+                                            int ty, int tz, int k0, int np, int32_t *flag, uint64_t &guard_count, int &kc)
 {
     const int lane = lane_id();
     const float vx = fmaf(L.ca, box.step[0], box.o[0]);
@@ -1190,12 +1189,11 @@ __device__ __forceinline__ int classify_box(const Lattice &L, int ns, int npix, 
     bool unsure = false;
     int pix = ang2pix_f(ns, vx, vy, vz, guard_tol, unsure);
     unsure &= L.active;
-    if (__ballot(unsure)) {
-        if (unsure) {
+    if (const uint64_t again = __ballot(unsure)) {
+        guard_count += __popcll(again);
+        if (unsure)
             pix = subpoint_pix_d(ns, L.s, box.b[0], box.b[1], box.b[2], box.e[0], box.e[1], box.e[2], tx, ty, tz, L.ia,
                                  L.ib, L.ic);
-            guard_count += 1.0;
-        }
     }
     if ((unsigned)pix >= (unsigned)npix) {
         // cannot happen for a finite direction: reported, never written out of bounds
@@ -1223,13 +1221,13 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
                           const Real *rt, int nr,
                           Real rc_inv,
                           Real rcoef, int n, int cnt, int tx, int ty, int tz, int tsize, int k0, int np,
-                          double &guard_count, double &tab_count)
+                          uint64_t &guard_count, uint64_t &tab_count)
 {
     using R4 = typename R4T<Real>::T;
     const int lane = lane_id();
     const Real xe = (Real)0.86602540378443864676;
     // ---------------- phase 1 ----------------
-    int bx = 0, by = 0, bz = 0, ex = 1, ey = 1, ez = 1, lo = 0, nsup = 0, ie = 1;
+    int lo = 0, nsup = 0, ie = 1;
     Real d = 1, hinv = 1, wscale = 0, fb0 = 1, qa = 0, qe = 0, qv = 0, e0 = 0, e1 = 0;
     // emission spread over several points: mode 1 linear (a + b (i - le) on [le, le + ne)),
     // 2 a smoothing kernel scaled by ea, 3 the mass fall-back weights
@@ -1240,13 +1238,6 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     if (lane < cnt) {
         const int4 g = a.geo[n];
         const int size = g.w & kSizeMask;
-        bx = g.x; by = g.y; bz = g.z;
-        ex = ey = ez = size;
-        if (g.w & kPartialBit) {
-            const int4 o = a.olo[n], e = a.oext[n];
-            bx = o.x; by = o.y; bz = o.z;
-            ex = e.x; ey = e.y; ez = e.z;
-        }
         const R4 A = ((const R4 *)a.pA)[n];
         const R4 B = ((const R4 *)a.pB)[n];
         qa = B.x; qe = B.y; qv = B.z;
@@ -1255,11 +1246,8 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
             shx = nearest_copy_shift(2 * g.x + size - tx, per[0]);
             shy = nearest_copy_shift(2 * g.y + size - ty, per[1]);
             shz = nearest_copy_shift(2 * g.z + size - tz, per[2]);
-            bx += shx;
-            by += shy;
-            bz += shz;
         }
-        const int key = table_key(a, g.w, bx, by, bz, tx, ty, tz, tsize);
+        const int key = table_key(a, g.w, g.x + shx, g.y + shy, g.z + shz, tx, ty, tz, tsize);
         if (key >= 0) tab = (unsigned)a.atab_idx[key];
         const Real dxc = (A.x + (Real)shx) - (Real)0.5 * (Real)tx, dyc = (A.y + (Real)shy) - (Real)0.5 * (Real)ty,
                    dzc = (A.z + (Real)shz) - (Real)0.5 * (Real)tz;
@@ -1341,9 +1329,7 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     // ---------------- phase 2 ----------------
     const int ns = a.nside;
     const int nrm = a.nr_max;
-    const Lattice L(a.subsample);
     const Real inv_s3 = (Real)1 / (Real)(a.subsample * a.subsample * a.subsample);
-    const float inv_s = 1.0f / (float)a.subsample;
     // each below 256; bit 24: the node emits (two-point emission weights e0, e1)
     const bool emits = e0 != (Real)0 || e1 != (Real)0;
     const int packed = lo | (nsup << 8) | (ie << 16) | (emits ? 1 << 24 : 0);
@@ -1352,15 +1338,12 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     // the W_p normalisation, or (no support point: linear split) minus the
     // bracket weight of the lower point
     const Real wsf = wscale > (Real)0 ? wscale : -fb0;
-    // per node (lane = node): sub-box origin relative to the target and sub-box steps, FP32
-    const float ox = 0.5f * (float)(2 * bx - tx), oy = 0.5f * (float)(2 * by - ty), oz = 0.5f * (float)(2 * bz - tz);
-    const float sx = (float)ex * inv_s, sy = (float)ey * inv_s, sz = (float)ez * inv_s;
     // The table nodes' pairs laid end to end: node n's start at off; lane q of
     // perm holds the lane of the q-th table node, offc its start.
     const bool in_tab = tab != kNoEntry;
-    tab_count += in_tab ? 1.0 : 0.0;
     const uint64_t tmask = __ballot(in_tab);
     const int n_tab = (int)__popcll(tmask);
+    tab_count += n_tab;
     int ptot = 0;
     const int off = wave_excl_scan_dpp(in_tab ? (int)(tab & 63u) + 1 : 0, ptot);
     const uint64_t nmask = uniform(~tmask);
@@ -1397,11 +1380,30 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
             if (ready < 0) {
                 const int j = __ffsll((unsigned long long)rem) - 1;
                 rem &= rem - 1;
+                // (few nodes: their geometry is read again instead of held by every lane)
+                const int jn = rdlane(n, j);
+                const int4 jg = a.geo[jn];
+                const int jsize = jg.w & kSizeMask;
                 Box box;
-                box.o[0] = rdlane(ox, j); box.o[1] = rdlane(oy, j); box.o[2] = rdlane(oz, j);
-                box.step[0] = rdlane(sx, j); box.step[1] = rdlane(sy, j); box.step[2] = rdlane(sz, j);
-                box.b[0] = rdlane(bx, j); box.b[1] = rdlane(by, j); box.b[2] = rdlane(bz, j);
-                box.e[0] = rdlane(ex, j); box.e[1] = rdlane(ey, j); box.e[2] = rdlane(ez, j);
+                box.b[0] = jg.x; box.b[1] = jg.y; box.b[2] = jg.z;
+                box.e[0] = box.e[1] = box.e[2] = jsize;
+                if (jg.w & kPartialBit) {
+                    const int4 jo = a.olo[jn], je = a.oext[jn];
+                    box.b[0] = jo.x; box.b[1] = jo.y; box.b[2] = jo.z;
+                    box.e[0] = je.x; box.e[1] = je.y; box.e[2] = je.z;
+                }
+                if (per) {
+                    box.b[0] += nearest_copy_shift(2 * jg.x + jsize - tx, per[0]);
+                    box.b[1] += nearest_copy_shift(2 * jg.y + jsize - ty, per[1]);
+                    box.b[2] += nearest_copy_shift(2 * jg.z + jsize - tz, per[2]);
+                }
+                const Lattice L(a.subsample);
+                const float inv_s = 1.0f / (float)a.subsample;
+                const int tc[3] = {tx, ty, tz};
+                for (int q = 0; q < 3; ++q) {
+                    box.o[q] = 0.5f * (float)(2 * box.b[q] - tc[q]);
+                    box.step[q] = (float)box.e[q] * inv_s;
+                }
                 ready_nd = classify_box<PASS>(L, ns, a.npix, a.guard_tol, box, tx, ty, tz, k0, np, &a.queue[1],
                                               guard_count, ready_kc);
                 ready = j;
@@ -1526,7 +1528,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (blockIdx.x == 0 && threadIdx.x == 0) a.queue[0] = 0;   // the sweep of this chunk starts from its first target
     const uint64_t below = (1ull << lane) - 1ull;
-    double n_test = 0, n_acc = 0;
+    uint64_t n_test = 0, n_acc = 0;
     for (int i = (int)blockIdx.x * kWalkWaves + wave; i < a.n_chunk; i += (int)gridDim.x * kWalkWaves) {
         const int64_t item = a.item0 + i;
         const int64_t cell = a.targets ? a.targets[item] : (int64_t)a.order[item];
@@ -1576,7 +1578,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
                     nch = what == 2 ? tp.y : 0;
                     fc = tp.x;
                 }
-                n_test += valid ? 1.0 : 0.0;
+                n_test += min(64, nfr - base);
                 const uint64_t mt = __ballot(in_tab), mo = __ballot(other);
                 int tot = 0;
                 const int off = wave_excl_scan_dpp(nch, tot);
@@ -1600,7 +1602,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
         r.n_tab = nt;
         r.n_oth = no;
         r.skip = ovf ? 1 : 0;
-        n_acc += ovf || lane != 0 ? 0.0 : (double)(nt + no);
+        n_acc += ovf ? 0 : nt + no;
         if (lane == 0) {
             if (a.f32) {
                 const float4 A = ((const float4 *)a.pA)[tnode], B = ((const float4 *)a.pB)[tnode];
@@ -1613,8 +1615,6 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
             if (ovf) queue_overflow(a, false, item, r.out);
         }
     }
-    n_test = wave_sum(n_test);
-    n_acc = wave_sum(n_acc);
     if (lane == 0) {
         if (n_acc > 0) atomicAdd(&a.stats[0], (unsigned long long)n_acc);
         if (n_test > 0) atomicAdd(&a.stats[1], (unsigned long long)n_test);
@@ -1640,7 +1640,7 @@ __device__ inline void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 // every wave), or -1 after an overflow.
 template <int K>
 __device__ int walk_shared(const SweepArgs &a, int wave, const int *per, int tx, int ty, int tz, int *fr0, int *fr1,
-                           int *acc, int *sc, int fmax, int amax, double &n_test)
+                           int *acc, int *sc, int fmax, int amax, uint64_t &n_test)
 {
     const int lane = lane_id();
     int *cur = fr0, *nxt = fr1;
@@ -1662,7 +1662,7 @@ __device__ int walk_shared(const SweepArgs &a, int wave, const int *per, int tx,
                 nch = what == 2 ? tp.y : 0;
                 fc = tp.x;
             }
-            n_test += valid ? 1.0 : 0.0;
+            n_test += min(64, nfr - base);
             const uint64_t macc = __ballot(acc_it);
             const int cacc = (int)__popcll(macc);
             int tot = 0;
@@ -1742,7 +1742,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     int *fr0 = nullptr;   // fallback: frontiers of gfmax entries, then gamax accepted nodes
     if (FALLBACK) fr0 = a.glist + (size_t)blockIdx.x * (2 * (size_t)a.gfmax + a.gamax);
 
-    double n_acc = 0, n_test = 0, n_guard = 0, n_f32 = 0, n_f64 = 0, n_tab = 0, n_re = 0;
+    uint64_t n_acc = 0, n_test = 0, n_guard = 0, n_f32 = 0, n_f64 = 0, n_tab = 0, n_re = 0;   // (uniform)
     const int64_t n_items =
         FALLBACK ? min((int64_t)__hip_atomic_load(&a.queue[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), a.ovf_cap)
                  : a.n_chunk;
@@ -1849,7 +1849,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                 __syncthreads();
                 continue;
             }
-            n_acc += tid == 0 ? (double)nt : 0.0;
+            n_acc += wave == 0 ? nt : 0;
         }
         double ftarget = 0.0;   // this lane's share of the target's flux over the passes
         // The rays k0 .. k0 + np - 1: all of them, or (PASS) one pass of prays
@@ -1861,26 +1861,27 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             const int k0 = pass * prays, np = PASS ? min(prays, npix - k0) : npix;
             // ray buffer: zero emission, the target's own share of A, E, V
             {
-                // every ray starts from the same 4 (split: 3) N_R values: lane l holds entries l + 64 m
+                // every ray starts from the same values: point lane (and lane + 64) of each row
                 const Real inv_npix = (Real)1 / (Real)npix;
-                const int per_ray = (split ? 3 : 4) * nrm;
-                Real val[4 * kMaxRadial / 64];
-#pragma unroll
-                for (int m = 0; m < 4 * kMaxRadial / 64; ++m) {
-                    const int e = lane + 64 * m;
-                    const int row = e / nrm + (split ? 1 : 0), i = e - (e / nrm) * nrm;
-                    Real v = (Real)0;
-                    if (e < per_ray && row != Q_EPS && i < nr) {
-                        const Real mom = row == Q_A ? talpha : row == Q_E ? te : tv;
-                        v = mom * (wself[i] * inv_npix);
-                    }
-                    val[m] = v;
-                }
+                const Real w0 = lane < nr ? wself[lane] * inv_npix : (Real)0;
+                const Real w1 = lane + 64 < nr ? wself[lane + 64] * inv_npix : (Real)0;
                 for (int k = wave; k < np; k += WAVES) {
-                    Real *dst = buf + (size_t)k * a.stride_k;
-#pragma unroll
-                    for (int m = 0; m < 4 * kMaxRadial / 64; ++m)
-                        if (64 * m < per_ray && lane + 64 * m < per_ray) dst[lane + 64 * m] = val[m];
+                    Real *dst = buf + (size_t)k * a.stride_k + lane;
+                    if (!split) {
+                        if (lane < nrm) dst[0] = (Real)0;
+                        if (lane + 64 < nrm) dst[64] = (Real)0;
+                        dst += nrm;
+                    }
+                    if (lane < nrm) {
+                        dst[0] = talpha * w0;
+                        dst[nrm] = te * w0;
+                        dst[2 * nrm] = tv * w0;
+                    }
+                    if (lane + 64 < nrm) {
+                        dst[64] = talpha * w1;
+                        dst[nrm + 64] = te * w1;
+                        dst[2 * nrm + 64] = tv * w1;
+                    }
                 }
                 for (int e = tid; e < np * ew; e += WAVES * 64) emask[e] = 0ull;
                 // (the emission plane of split buffers is zero here: cleared when
@@ -1938,7 +1939,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                         nb[q] = q == 5 ? n[q] : (n[q] + (64 >> (q + 2)) - 1) >> (4 - q);
                         if (q + 2 > lg0) re += n[q];
                     }
-                    n_re += (wave == 0 && lane == 0) ? (double)re : 0.0;
+                    n_re += wave == 0 ? re : 0;
                 }
                 const int n_batch = nb[0] + nb[1] + nb[2] + nb[3] + nb[4] + nb[5];
                 for (int b = wave; b < n_batch; b += IW) {
@@ -2033,13 +2034,6 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
         }
     }
     // statistics
-    n_acc = wave_sum(n_acc);
-    n_test = wave_sum(n_test);
-    n_guard = wave_sum(n_guard);
-    n_f32 = wave_sum(n_f32);
-    n_f64 = wave_sum(n_f64);
-    n_tab = wave_sum(n_tab);
-    n_re = wave_sum(n_re);
     if (lane == 0) {
         if (n_acc > 0) atomicAdd(&a.stats[0], (unsigned long long)n_acc);
         if (n_test > 0) atomicAdd(&a.stats[1], (unsigned long long)n_test);
@@ -2076,9 +2070,13 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_kv_fallback(SweepArgs a
     sweep_body<Real, WAVES, LDSBUF, true, true>(a);
 }
 
-// FP32 ray buffers in LDS accumulated by compare-and-swap (8 and 16 waves)
+// FP32 ray buffers in LDS accumulated by compare-and-swap (4, 8 and 16 waves).
+// With 4 waves per target 6 targets are resident: 6 waves per SIMD in 80
+// registers (41 spilled, outside the inner loops) are faster than 4 without
+// spills, 169 against 195 ms on 128^3 at N_side 2: between its barriers a
+// target's waves wait for memory and LDS, and only other targets fill that.
 template <int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_cas(SweepArgs a)
+__global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 6 : 4) void k_sweep_cas(SweepArgs a)
 {
     sweep_body<float, WAVES, true, false, false, true>(a);
 }
@@ -2128,7 +2126,7 @@ __global__ __launch_bounds__(256) void k_atab(AtabGeom G, int ns, int s, float g
     const int wave = uniform((int)(blockIdx.x * 4 + (threadIdx.x >> 6))), lane = lane_id();
     const Lattice L(s);
     int64_t at = idx ? sums[wave] : 0;
-    double guard = 0;
+    uint64_t guard = 0;
     for (int key = wave * run; key < min((wave + 1) * run, G.nkeys); ++key) {
         int ri = 0;
 #pragma unroll
@@ -2535,6 +2533,7 @@ KernelFn pick_kernel_pass(int waves, bool fallback)
 
 KernelFn pick_kernel_cas(int waves, bool fallback)
 {
+    if (waves == 4) return fallback ? (KernelFn)k_sweep_cas_fallback<4> : (KernelFn)k_sweep_cas<4>;
     if (waves == 8) return fallback ? (KernelFn)k_sweep_cas_fallback<8> : (KernelFn)k_sweep_cas<8>;
     return fallback ? (KernelFn)k_sweep_cas_fallback<16> : (KernelFn)k_sweep_cas<16>;
 }
@@ -2585,7 +2584,11 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     int waves = waves_req;
     if (waves <= 0) {
         waves = c->tuned_waves[f32 ? 1 : 0];
-        if (waves <= 0) waves = npix >= 192 ? 16 : 8;   // the tuned picks at N_side 4 and 2
+        // From N_side 4 on one target's buffers fill the LDS: 16 waves on it.  Below, several
+        // targets are resident, and the fewer waves share one the better their phases overlap:
+        // FP32C 128^3 N_side 2, 6 targets of 4 waves 169 ms, 4 of 4 waves 195 ms, 2 of 8 waves
+        // 233 ms; the FP64 buffers leave room for 2 or 3 targets (61 ms with 4 or 8 waves)
+        if (waves <= 0) waves = npix >= 192 ? 16 : (f32 ? 4 : 8);
     }
     // the radial-kernel variants are built for 4 and 8 waves per target only
     const bool kv = !((c->p.eps_kernel == 0 || c->p.eps_kernel == 3) && (c->p.mass_kernel == 0 || c->p.mass_kernel == 5));
@@ -2634,7 +2637,8 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     // accumulation: compare-and-swap by default (FP32, LDS, 8 or 16 waves)
     {
         const int am = atom_req > 0 ? atom_req : (c->atommode > 0 ? c->atommode : c->tuned_atom[f32 ? 1 : 0]);
-        L.cas = f32 && L.ldsbuf && !kv && L.pass_rays == 0 && (waves == 8 || waves == 16) && (am > 0 ? am == 2 : true);
+        L.cas = f32 && L.ldsbuf && !kv && L.pass_rays == 0 &&
+                (waves == 8 || waves == 16 ? (am > 0 ? am == 2 : true) : waves == 4 && (am > 0 ? am == 2 : waves_req <= 0));
         if (L.cas) {
             L.fn = pick_kernel_cas(waves, false);
             L.fn_fb = pick_kernel_cas(waves, true);
@@ -2648,6 +2652,18 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     HIPCHK(hipFuncSetAttribute((const void *)L.fn_fb, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.lds));
     int occ = 0;
     HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void *)L.fn, waves * 64, L.lds));
+    // where both forms fit, the split one if more targets are resident with its smaller buffers
+    if (L.ldsbuf && fits4 && fits3) {
+        const size_t lds3 = sweep_lds_bytes(real, npix, stride3, nrm, waves, true);
+        int occ3 = 0;
+        HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ3, (const void *)L.fn, waves * 64, lds3));
+        if (occ3 > occ) {
+            occ = occ3;
+            L.lds = lds3;
+            L.split = true;
+            L.stride_k = stride3;
+        }
+    }
     if (occ <= 0) return fail(c, TR_EINVAL, "sweep kernel does not fit on a compute unit (LDS " + std::to_string(L.lds) + " B)");
     L.per_cu = tpc_req > 0 ? std::min(tpc_req, occ) : occ;
     // integration: by default a group of lanes per ray, so that a target's few
