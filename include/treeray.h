@@ -107,8 +107,9 @@ typedef struct {
     int32_t waves_per_target, targets_per_cu;   /* launch shape of the last sweep */
     int32_t buffer_in_lds;      /* where the last sweep kept its ray buffers: 1 LDS, 0 device memory,
                                    2 (FP32) the A, E, V rows in LDS and the emission rows in device memory,
-                                   3 LDS for part of the rays at a time (a target's rays in passes; the
-                                   emission rows in device memory when that saves a pass) */
+                                   3 LDS, with buffers for fewer than all rays (a target's rays that hold
+                                   emission are taken as many at a time as there are buffers; so with 2
+                                   where not all rays fit) */
     int32_t overflow;           /* nonzero if a walk list overflowed */
     int32_t integration_wave;   /* lanes that integrated one ray in the last sweep: 1, 4, 8, 16 or 64 */
     int32_t lds_cas;            /* 1 if the last sweep accumulated its LDS ray buffers by compare-and-swap */
@@ -202,8 +203,9 @@ tr_status tr_set_precision(tr_ctx *c, tr_precision prec);
  * in FP64 (Sec. 2.5; FP32C only, the FP64 form takes 3, 4, 5) and how the waves
  * of a target accumulate into a shared FP32 buffer in LDS at 8 or 16 waves
  * (0 = tuned or default, compare-and-swap; 1 = hardware atomic
- * adds; 2 = compare-and-swap loops on the values' bits; elsewhere hardware
- * atomics).  Zeros restore the tuned default.  Results do not depend on the
+ * adds; 2 = compare-and-swap loops on the values' bits) and at 4 waves (2 =
+ * compare-and-swap, also the default where 4 waves are the library's own
+ * choice; elsewhere hardware atomics).  Zeros restore the tuned default.  Results do not depend on the
  * shape beyond rounding. */
 tr_status tr_set_launch(tr_ctx *c, int32_t waves_per_target, int32_t targets_per_cu, int32_t buffer,
                         int32_t integration, int32_t atomics);

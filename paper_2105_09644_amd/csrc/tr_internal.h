@@ -13,9 +13,10 @@ namespace tr {
 constexpr int kBlock = 8;          // cells per block edge
 constexpr int kMaxRadial = 128;    // evaluation points per ray (two 64-bit masks)
 constexpr int kAtabRatios = 5;    // angular-weight table: nodes of 1, 2, 4, 8 and 16 target sizes
-constexpr unsigned kNoEntry = ~0u;
+constexpr unsigned kNoEntry = ~0u, kDynEntry = 1u << 31;   // no pairs; pairs in the chunk's pool
+constexpr int kDynBlock = 256;    // units of 4 pairs a walking wave takes from that pool at a time
 constexpr int kMaxLevels = 24;
-constexpr int kListCap = 4096;         // accepted nodes listed per target, and
+constexpr int kListCap = 3072;         // accepted nodes listed per target, and
 constexpr int kListTargets = 1 << 15;  // targets walked and listed at a time (1 GB of lists)
 constexpr int kWalkFront = 1024;       // frontier entries of a walk in LDS
 constexpr int kWalkPerCu = 5;          // workgroups per compute unit of the walk kernel

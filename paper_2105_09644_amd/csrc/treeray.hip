@@ -328,10 +328,10 @@ template <> struct R4T<float> { using T = float4; };
 template <> struct R4T<double> { using T = double4; };
 
 // One target of a chunk, written by k_walk for the sweep: doubled centre and
-// size, domain, how its accepted nodes were listed, output index, moments.
+// size, domain, accepted nodes and those that emit, output index, moments.
 struct TargetRec {
     int32_t tx, ty, tz, tsize;
-    int32_t dom, n_tab, n_oth, skip;   // skip: nothing to map (bad index, or queued for the fallback pass)
+    int32_t dom, n_acc, n_emit, pad;   // n_emit < 0: nothing to map (bad index, or queued for the fallback pass)
     int64_t out;
     double eps, alpha, e, v;
 };
@@ -353,11 +353,13 @@ struct SweepArgs {
     int64_t n_items;
     int64_t n_cells;
     // the chunk of the work items [item0, item0 + n_chunk) whose walks are
-    // listed: target i's accepted nodes inside the angular table's range at
-    // lists[i list_cap ..] upwards, the others from its last entry downwards
+    // listed: target i's accepted nodes at lists[i list_cap ..], each with where
+    // its (pixel, count) pairs are, and the places of those that emit at
+    // emit_at[i list_cap ..]
     int64_t item0;
     int32_t n_chunk, list_cap;
-    int32_t *lists;
+    int2 *lists;
+    uint16_t *emit_at;
     TargetRec *rec;
     double *f_out;
     uint8_t *ion_out;
@@ -365,7 +367,7 @@ struct SweepArgs {
     unsigned long long *stats;  // [0] accepted, [1] tested, [2] guard recomputes, [3] rays marched in
                                 // FP32, [4] of those marched again in FP64, [5] nodes from the table
     void *gbuf;              // ray buffers in global memory (when they do not fit in LDS)
-    void *ebuf;              // split LDS buffers: the emission rows, npix x nr_max per workgroup
+    void *ebuf;              // split LDS buffers: the emission rows, rays x nr_max per workgroup
     int32_t split;           // 1: A, E, V rows in LDS (stride_k = 3 nr_max + 1), emission rows in ebuf
     double theta2, theta_if2, theta_src2;   // squared opening angles (0: criterion off)
     float guard_tol;
@@ -385,16 +387,19 @@ struct SweepArgs {
     int64_t ovf_cap;
     int32_t *glist;
     int32_t gfmax, gamax;
-    int32_t pass_rays;   // > 0: the LDS ray buffers hold this many rays; a target's rays are mapped
-                         // and integrated in passes over consecutive pixel ranges
+    int32_t rays;        // ray buffers of a workgroup: a target's rays that hold emission are mapped and
+                         // integrated so many at a time
     // angular-weight table (NULL: none): for a node of 2^ri times the target's
     // size (ri < kAtabRatios) at offset o in target sizes from the target's
     // lower corner, |o_a| <= atab_w[ri], the entry
     // atab_idx[atab_base[ri] + ((o_x + w)(2w + 1) + o_y + w)(2w + 1) + o_z + w]
-    // = (first pair << 6) | (pairs - 1), each pair in atab_pool = pixel | count << 16
+    // = (first pair / 4 << 6) | (pairs - 1), each pair in atab_pool = pixel | count << 16;
+    // the pairs of the chunk's other nodes are in dyn_pool (kDynEntry set)
     const int32_t *atab_idx;
     const int32_t *atab_pool;
     int32_t atab_w[kAtabRatios], atab_base[kAtabRatios];
+    int32_t *dyn_pool;
+    int32_t dyn_units;   // its size in units of 4 pairs
 };
 
 // Ray buffer rows: eps, A (recombinations), E (previous flux x volume), V.
@@ -510,7 +515,25 @@ __device__ inline int nearest_copy_shift(int v, int L)
     return k * L;
 }
 
-// outermost emitting point of a ray
+// Shift of a node to its periodic copy closest to the target (by the cube's centre); per NULL: none
+__device__ inline void node_shift(const int *per, const int4 g, int tx, int ty, int tz, int sh[3])
+{
+    if (!per) return;
+    const int size = g.w & kSizeMask;
+    sh[0] = nearest_copy_shift(2 * g.x + size - tx, per[0]);
+    sh[1] = nearest_copy_shift(2 * g.y + size - ty, per[1]);
+    sh[2] = nearest_copy_shift(2 * g.z + size - tz, per[2]);
+}
+
+// distance of a node's (shifted) mass centre from the target
+template <typename Real, typename R4>
+__device__ inline Real centre_distance(const R4 A, const int sh[3], int tx, int ty, int tz)
+{
+    const Real dx = (A.x + (Real)sh[0]) - (Real)0.5 * (Real)tx, dy = (A.y + (Real)sh[1]) - (Real)0.5 * (Real)ty,
+               dz = (A.z + (Real)sh[2]) - (Real)0.5 * (Real)tz;
+    return fsqrt(dx * dx + dy * dy + dz * dz);
+}
+
 // Per ray, a mask of the points 1 .. N_R - 1 that received emission: ew words
 // (1 for N_R <= 64, else 2) of 64 bits, bit i of word w for point 64 w + i.
 __device__ inline void mask_or(unsigned long long *p, unsigned long long bits)
@@ -691,7 +714,7 @@ template <typename Real, int NH>
 __device__ double integrate_ray_wave(const RayRows<Real> &R, int k, const double *r, const double *inv2r, int nr,
                                      int top, int nside, int zeta_g, bool clear_eps)
 {
-    const int lane = lane_id();
+    const int lane = here(lane_id());   // (nothing derived from it is held between calls)
     const double inv4pi = 1.0 / (4.0 * kPi);
     const double ns = (double)nside;
     double al[2], fb[2], ph[2], rp[2], i2r[2], ep[2];
@@ -796,7 +819,7 @@ __device__ double integrate_rays_group(const RayRows<Real> &R, int k, unsigned l
                                        const double *r, const double *inv2r, int nr, int nside, int zeta_g,
                                        int &n_over, bool clear_eps)
 {
-    const int lane = lane_id();
+    const int lane = here(lane_id());   // (nothing derived from it is held between calls)
     const int sl = lane & (G - 1);
     const int g0 = lane - sl;   // first lane of the group
     const double inv4pi = 1.0 / (4.0 * kPi);
@@ -884,7 +907,7 @@ __device__ void integrate_rays_group_f32(const RayRows<float> &R, int k, unsigne
                                          float front_ratio, int &n_over, bool &near, float &f_hi, float &f_lo,
                                          bool clear_eps)
 {
-    const int lane = lane_id();
+    const int lane = here(lane_id());   // (nothing derived from it is held between calls)
     const int sl = lane & (G - 1);
     const int g0 = lane - sl;
     const uint64_t gmask = G == 64 ? ~0ull : ((1ull << G) - 1ull);
@@ -1008,7 +1031,7 @@ __device__ __forceinline__ void march_batch(const SweepArgs &a, const RayRows<Re
                                             const double *rd, const double *rd2, int nr, bool split, double &fsum,
                                             float &cs_hi, float &cs_lo, uint64_t &n_f32, uint64_t &n_f64)
 {
-    const int lane = lane_id();
+    const int lane = here(lane_id());   // (nothing derived from it is held between calls)
     const bool has = myk >= 0;
     const int tmax = wave_max_nonneg(mask_top(m0, m1));
     const bool head = (lane & (G - 1)) == 0;
@@ -1127,24 +1150,25 @@ __device__ inline Real emission_weight(int mode, int i, int io, int le, int ne, 
     return io == 0 ? fb : (Real)1 - fb;
 }
 
-// Maps cnt <= 64 accepted nodes, node n on lane < cnt, onto the target's rays;
-// executed by a whole wave in two phases.
-//  Phase 1, lane = node: loads the node, its mass-centre distance d, the
-//   W_p normalisation over the evaluation points in its support and the W_f,3
-//   bracket of its emission (App. A).
-//  Phase 2, lane = (node, pixel) pair: the pairs of all the nodes, laid end to
-//   end, are taken 64 at a time; each lane runs over its node's support points
-//   and adds its pixel's share of A, E and V to each.  A node has few pairs
-//   (mean 2.8 at N_side 2, 5.3 at N_side 4) and few points with a weight (3 to
-//   4), so one node at a time leaves most lanes idle: 154 to 200 vector
-//   instructions per node, against 11 to 27 for the same adds in pairs.
-//   A node's pairs come from the angular table, or from classifying its s^3
-//   sub-points (lane = sub-point; the share of pixel k is the count in k over
-//   s^3), which the whole wave does for one node at a time.
-// The evaluation points are r_i = c i^2; the lanes recompute them in
-// registers, so the loop over them makes no memory round trip besides its
-// atomics.
-// KV: the radial-kernel variants of App. A (otherwise two-point W_f,3 and W_p)
+// W_f,3 (App. A.3): the bracket r_i <= d < r_{i+1}, i >= 1, and its two weights
+// (beyond either end all on the end point).  Returns i.
+template <typename Real>
+__device__ inline int emission_bracket(const Real *rt, int nr, Real rc_inv, Real d, Real &u0, Real &u1)
+{
+    u0 = 1;
+    u1 = 0;
+    if (d >= rt[nr - 1]) return nr - 1;
+    if (!(d >= rt[1])) return 1;
+    int k = (int)fsqrt(d * rc_inv);
+    k = k < 1 ? 1 : (k > nr - 2 ? nr - 2 : k);
+    while (k > 1 && rt[k] > d) --k;
+    while (k < nr - 2 && rt[k + 1] <= d) ++k;
+    const Real ai = frcp(rt[k] * rt[k]), an = frcp(rt[k + 1] * rt[k + 1]), ad = frcp(d * d);
+    u0 = (ad - an) * frcp(ai - an);
+    u1 = (Real)1 - u0;
+    return k;
+}
+
 // A lane's place in the s^3 sub-point lattice of a node's box (lanes from s^3
 // on have none).
 struct Lattice {
@@ -1176,11 +1200,9 @@ struct Box {
 // The pixels of a box's sub-points, by a whole wave (lane = sub-point): FP32
 // with a guard band, FP64 inside it, so the FP64 classifier's pixel for every
 // sub-point.  Returns the number of distinct pixels; lane q of kc holds the
-// q-th and its sub-point count, pixel | count << 16.  PASS: the pixels k0 ..
-// k0 + np - 1 only, as local indices.
-template <bool PASS>
+// q-th and its sub-point count, pixel | count << 16.
 __device__ __forceinline__ int classify_box(const Lattice &L, int ns, int npix, float guard_tol, const Box &box, int tx,
-                                            int ty, int tz, int k0, int np, int32_t *flag, uint64_t &guard_count, int &kc)
+                                            int ty, int tz, int32_t *flag, uint64_t &guard_count, int &kc)
 {
     const int lane = lane_id();
     const float vx = fmaf(L.ca, box.step[0], box.o[0]);
@@ -1207,24 +1229,173 @@ __device__ __forceinline__ int classify_box(const Lattice &L, int ns, int npix, 
         const int k = __builtin_amdgcn_readlane(pix, first);
         const uint64_t m = __ballot(pix == k) & left;
         left &= ~m;
-        if (!PASS || (unsigned)(k - k0) < (unsigned)np) {
-            const int v = (k - k0) | ((int)__popcll(m) << 16);   // uniform
-            kc = lane == nd ? v : kc;
-            ++nd;
-        }
+        const int v = k | ((int)__popcll(m) << 16);   // uniform
+        kc = lane == nd ? v : kc;
+        ++nd;
     }
     return nd;
 }
 
-template <typename Real, int ATOMIC, bool KV, bool PASS>
-__device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned long long *emask, int ew, const int *per,
-                          const Real *rt, int nr,
-                          Real rc_inv,
-                          Real rcoef, int n, int cnt, int tx, int ty, int tz, int tsize, int k0, int np,
-                          uint64_t &guard_count, uint64_t &tab_count)
+// The box of a node for its sub-points; sh: the shift to its periodic copy.
+__device__ inline Box node_box(const SweepArgs &a, int n, const int4 g, const int sh[3], int tx, int ty, int tz)
+{
+    Box box;
+    const int size = g.w & kSizeMask;
+    box.b[0] = g.x; box.b[1] = g.y; box.b[2] = g.z;
+    box.e[0] = box.e[1] = box.e[2] = size;
+    if (g.w & kPartialBit) {
+        const int4 o = a.olo[n], e = a.oext[n];
+        box.b[0] = o.x; box.b[1] = o.y; box.b[2] = o.z;
+        box.e[0] = e.x; box.e[1] = e.y; box.e[2] = e.z;
+    }
+    const float inv_s = 1.0f / (float)a.subsample;
+    const int tc[3] = {tx, ty, tz};
+    for (int q = 0; q < 3; ++q) {
+        box.b[q] += sh[q];
+        box.o[q] = 0.5f * (float)(2 * box.b[q] - tc[q]);
+        box.step[q] = (float)box.e[q] * inv_s;
+    }
+    return box;
+}
+
+// The (node, pixel) pairs of up to 64 nodes, node n on a lane, its pairs at
+// entry (kNoEntry: none, or no node), laid end to end and handed out 64 at a
+// time.  CLASSIFY (fallback pass): then those of the lanes in todo, node by
+// node, each classified by the whole wave.
+template <bool CLASSIFY>
+struct PairStream {
+    // node on lane l: its pairs start at off; lane q of perm holds the lane of
+    // the q-th node with an entry, offc its start
+    const int lane;
+    unsigned entry;
+    int n_ent, off, perm, offc, ptot, b;
+    uint64_t todo;
+
+    __device__ __forceinline__ PairStream(int lane_, unsigned entry_, uint64_t todo_) : lane(lane_), entry(entry_), b(0), todo(todo_)
+    {
+        const bool has = entry != kNoEntry;
+        const uint64_t tmask = __ballot(has), nmask = uniform(~tmask);
+        n_ent = (int)__popcll(tmask);
+        off = wave_excl_scan_dpp(has ? (int)(entry & 63u) + 1 : 0, ptot);
+        const int rank_t = bits_below(tmask), rank_n = n_ent + bits_below(nmask);
+        perm = __builtin_amdgcn_ds_permute((has ? rank_t : rank_n) << 2, lane);
+        offc = __shfl(off, perm, 64);
+    }
+
+    // The next pairs: node (its lane) and kc = pixel | count << 16 (pixel < 2^16,
+    // count <= 64) on lanes below the returned number; 0: no more.
+    __device__ __forceinline__ int next(const SweepArgs &a, int n, const int *per, int tx, int ty, int tz,
+                                        uint64_t &guard_count, int &node, int &kc)
+    {
+        node = kc = 0;
+        if (b < ptot) {
+            // S: the positions 1 .. 63 where a node's pairs start, shifted by one; r0: the node of position 0
+            const int rel = offc - b;
+            const bool is_node = lane < n_ent;
+            const int r0 = (int)__popcll(__ballot(is_node && rel <= 0)) - 1;
+            const uint64_t bit = is_node && rel > 0 && rel < 64 ? 1ull << (rel - 1) : 0ull;
+            const uint64_t S = ((uint64_t)(unsigned)wave_or((int)(bit >> 32)) << 32) | (unsigned)wave_or((int)bit);
+            node = __shfl(perm, r0 + bits_below(S), 64);
+            const unsigned en = (unsigned)__shfl((int)entry, node, 64);
+            const int on = __shfl(off, node, 64);
+            const int fill = ptot - b < 64 ? ptot - b : 64;
+            if (lane < fill) {
+                const int32_t *const pool = en & kDynEntry ? a.dyn_pool : a.atab_pool;
+                kc = pool[(int)((en & ~kDynEntry) >> 6) * 4 + (b + lane - on)];
+            }
+            b += 64;
+            return fill;
+        }
+        if constexpr (CLASSIFY) {
+            if (todo == 0ull) return 0;
+            node = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            const int jn = rdlane(n, node);
+            const int4 g = a.geo[jn];
+            int sh[3] = {0, 0, 0};
+            node_shift(per, g, tx, ty, tz, sh);
+            return classify_box(Lattice(a.subsample), a.nside, a.npix, a.guard_tol, node_box(a, jn, g, sh, tx, ty, tz), tx,
+                                ty, tz, &a.queue[1], guard_count, kc);
+        }
+        return 0;
+    }
+};
+
+// The angular-table entry of the node on this lane (kNoEntry: none)
+__device__ inline unsigned table_entry(const SweepArgs &a, const int4 g, const int sh[3], int tx, int ty, int tz, int tsize)
+{
+    const int key = table_key(a, g.w, g.x + sh[0], g.y + sh[1], g.z + sh[2], tx, ty, tz, tsize);
+    return key >= 0 ? (unsigned)a.atab_idx[key] : kNoEntry;
+}
+
+// The points that the emitting nodes among cnt <= 64 (node n on lane < cnt,
+// its pairs at entry; CLASSIFY: the angular table is still to be asked) put emission on, marked in the masks of all rays.  Nothing else is deposited
+// yet: a ray without emission adds nothing to the flux, nor does what lies
+// beyond a ray's outermost emitting point, so the mapping that follows skips
+// both (with few sources most rays: 81% of the pairs on 64^3 N_side 4 with one
+// source, 60% on 128^3 N_side 2 with 16).  rt: the evaluation points.
+template <typename Real, bool CLASSIFY>
+__device__ void mark_nodes(const SweepArgs &a, unsigned long long *emask, int ew, const int *per, const Real *rt, int nr,
+                           Real rc_inv, int n, unsigned entry, int cnt, int tx, int ty, int tz, int tsize,
+                           uint64_t &guard_count)
 {
     using R4 = typename R4T<Real>::T;
-    const int lane = lane_id();
+    const int lane = here(lane_id());
+    int mark = 0;   // the bracket's lower point, bit 8: emission there, bit 9: on the next
+    if (lane < cnt) {
+        const R4 A = ((const R4 *)a.pA)[n];
+        int sh[3] = {0, 0, 0};
+        if (per || CLASSIFY) {
+            const int4 g = a.geo[n];
+            node_shift(per, g, tx, ty, tz, sh);
+            if (CLASSIFY) entry = table_entry(a, g, sh, tx, ty, tz, tsize);
+        }
+        if (A.w > (Real)0) {
+            const Real d = centre_distance<Real>(A, sh, tx, ty, tz);
+            Real u0, u1;
+            mark = emission_bracket<Real>(rt, nr, rc_inv, d, u0, u1);
+            mark |= (A.w * u0 != (Real)0 ? 256 : 0) | (A.w * u1 != (Real)0 ? 512 : 0);
+        }
+    }
+    PairStream<CLASSIFY> ps(lane, entry, CLASSIFY ? __ballot(lane < cnt && entry == kNoEntry) : 0ull);
+    for (;;) {
+        int node, kc;
+        const int fill = ps.next(a, n, per, tx, ty, tz, guard_count, node, kc);
+        if (fill == 0) break;
+        const int m = __shfl(mark, node, 64);
+        if (lane < fill && m >= 256)
+            mark_points(emask + (size_t)(kc & 0xffff) * ew, m & 255, (m & 256) != 0, (m & 512) != 0);
+    }
+}
+
+// Maps cnt <= 64 accepted nodes, node n on lane < cnt with its pairs at entry
+// (CLASSIFY: the angular table is still to be asked), onto the target's rays
+// that have a buffer; executed by a whole wave in two phases.
+//  Phase 1, lane = node: loads the node, its mass-centre distance d, the
+//   W_p normalisation over the evaluation points in its support and the W_f,3
+//   bracket of its emission (App. A).
+//  Phase 2, lane = (node, pixel) pair: the pairs of all the nodes; those on a
+//   ray with a buffer (rinfo: its index << 8 | its outermost emitting point, 0
+//   none) are collected 64 at a time, and each lane runs over its node's
+//   support points up to that point and adds its pixel's share of A, E and V
+//   to each.  A node has few pairs (mean 2.8 at N_side 2, 5.3 at N_side 4) and
+//   few points with a weight (3 to 4), so one node at a time leaves most lanes
+//   idle: 154 to 200 vector instructions per node, against 11 to 27 for the
+//   same adds in pairs.
+// The evaluation points are r_i = c i^2; the lanes recompute them in
+// registers, so the loop over them makes no memory round trip besides its
+// atomics.
+// KV: the radial-kernel variants of App. A (otherwise two-point W_f,3 and
+// W_p), whose emission may be spread; every ray has a buffer then, and cmask
+// (by buffer) is marked here.
+template <typename Real, int ATOMIC, bool KV, bool CLASSIFY>
+__device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, const unsigned *rinfo, unsigned long long *cmask,
+                          int ew, const int *per, const Real *rt, int nr, Real rc_inv, Real rcoef, int n,
+                          unsigned entry, int cnt, int tx, int ty, int tz, int tsize, uint64_t &guard_count,
+                          uint64_t &tab_count)
+{
+    using R4 = typename R4T<Real>::T;
+    const int lane = here(lane_id());
     const Real xe = (Real)0.86602540378443864676;
     // ---------------- phase 1 ----------------
     int lo = 0, nsup = 0, ie = 1;
@@ -1233,7 +1404,6 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     // 2 a smoothing kernel scaled by ea, 3 the mass fall-back weights
     int emode = 0, le = 0, ne = 0;
     Real ea = 0, eb = 0, qeps = 0;
-    unsigned tab = kNoEntry;   // the node's angular-table entry (none: classify its sub-points)
     const bool mg = KV && a.mass_gauss != 0;
     if (lane < cnt) {
         const int4 g = a.geo[n];
@@ -1241,17 +1411,10 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
         const R4 A = ((const R4 *)a.pA)[n];
         const R4 B = ((const R4 *)a.pB)[n];
         qa = B.x; qe = B.y; qv = B.z;
-        int shx = 0, shy = 0, shz = 0;   // periodic copy closest to the target (by the cube's centre)
-        if (per) {
-            shx = nearest_copy_shift(2 * g.x + size - tx, per[0]);
-            shy = nearest_copy_shift(2 * g.y + size - ty, per[1]);
-            shz = nearest_copy_shift(2 * g.z + size - tz, per[2]);
-        }
-        const int key = table_key(a, g.w, g.x + shx, g.y + shy, g.z + shz, tx, ty, tz, tsize);
-        if (key >= 0) tab = (unsigned)a.atab_idx[key];
-        const Real dxc = (A.x + (Real)shx) - (Real)0.5 * (Real)tx, dyc = (A.y + (Real)shy) - (Real)0.5 * (Real)ty,
-                   dzc = (A.z + (Real)shz) - (Real)0.5 * (Real)tz;
-        d = fsqrt(dxc * dxc + dyc * dyc + dzc * dzc);
+        int sh[3] = {0, 0, 0};
+        node_shift(per, g, tx, ty, tz, sh);
+        if (CLASSIFY) entry = table_entry(a, g, sh, tx, ty, tz, tsize);
+        d = centre_distance<Real>(A, sh, tx, ty, tz);
         const Real h = (Real)size;
         hinv = frcp(h);   // a power of two: exact
         const Real rl = d - xe * h, rh = d + xe * h;
@@ -1302,21 +1465,10 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
                 emode = 3;
             }
         } else if (A.w > (Real)0) {   // W_f,3 bracket r_i <= d < r_{i+1}, i >= 1
-            Real u0 = 1, u1 = 0;
-            if (d >= rt[nr - 1]) {
-                ie = nr - 1;
-            } else if (d >= rt[1]) {
-                int k = (int)fsqrt(d * rc_inv);
-                k = k < 1 ? 1 : (k > nr - 2 ? nr - 2 : k);
-                while (k > 1 && rt[k] > d) --k;
-                while (k < nr - 2 && rt[k + 1] <= d) ++k;
-                ie = k;
-                const Real ai = frcp(rt[ie] * rt[ie]), an = frcp(rt[ie + 1] * rt[ie + 1]), ad = frcp(d * d);
-                u0 = (ad - an) * frcp(ai - an);
-                u1 = (Real)1 - u0;
-                if (ek == K_F1 || ek == K_F2)
-                    two_point_variant(ek, rt, ie, (double)d, u0, u1);
-            }
+            Real u0, u1;
+            ie = emission_bracket<Real>(rt, nr, rc_inv, d, u0, u1);
+            if ((ek == K_F1 || ek == K_F2) && d >= rt[1] && d < rt[nr - 1])
+                two_point_variant(ek, rt, ie, (double)d, u0, u1);
             if (ek == K_F3N && sum > (Real)0)
                 n_point_f3(rt, l0, h0, (double)d, (double)h, emode, le, ne, ea, eb);
             if (emode != 1) {
@@ -1327,7 +1479,6 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     }
 
     // ---------------- phase 2 ----------------
-    const int ns = a.nside;
     const int nrm = a.nr_max;
     const Real inv_s3 = (Real)1 / (Real)(a.subsample * a.subsample * a.subsample);
     // each below 256; bit 24: the node emits (two-point emission weights e0, e1)
@@ -1338,102 +1489,61 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
     // the W_p normalisation, or (no support point: linear split) minus the
     // bracket weight of the lower point
     const Real wsf = wscale > (Real)0 ? wscale : -fb0;
-    // The table nodes' pairs laid end to end: node n's start at off; lane q of
-    // perm holds the lane of the q-th table node, offc its start.
-    const bool in_tab = tab != kNoEntry;
-    const uint64_t tmask = __ballot(in_tab);
-    const int n_tab = (int)__popcll(tmask);
-    tab_count += n_tab;
-    int ptot = 0;
-    const int off = wave_excl_scan_dpp(in_tab ? (int)(tab & 63u) + 1 : 0, ptot);
-    const uint64_t nmask = uniform(~tmask);
-    const int rank_t = bits_below(tmask), rank_n = n_tab + bits_below(nmask);
-    const int rank = in_tab ? rank_t : rank_n;
-    const int perm = __builtin_amdgcn_ds_permute(rank << 2, lane);
-    const int offc = __shfl(off, perm, 64);
-    uint64_t rem = (cnt < 64 ? (1ull << cnt) - 1ull : ~0ull) & nmask;   // nodes to classify
-    int ready = -1, ready_nd = 0, ready_kc = 0;   // a classified node (its pairs in lanes 0 ..) that found no room
-    for (int b = 0; b < ptot || rem != 0ull || ready >= 0; b += 64) {
-        // --- the next 64 pairs: node (its lane) and kc = pixel | count << 16 (pixel < 2^16, count <= 64) ---
-        int node = 0, kc = 0, fill = 0;
-        bool valid = false;
-        if (b < ptot) {
-            // S: the positions 1 .. 63 where a node's pairs start, shifted by one; r0: the node of position 0
-            const int rel = offc - b;
-            const bool is_node = lane < n_tab;
-            const int r0 = (int)__popcll(__ballot(is_node && rel <= 0)) - 1;
-            const uint64_t bit = is_node && rel > 0 && rel < 64 ? 1ull << (rel - 1) : 0ull;
-            const uint64_t S = ((uint64_t)(unsigned)wave_or((int)(bit >> 32)) << 32) | (unsigned)wave_or((int)bit);
-            node = __shfl(perm, r0 + bits_below(S), 64);
-            const unsigned tn = (unsigned)__shfl((int)tab, node, 64);
-            const int on = __shfl(off, node, 64);
-            fill = ptot - b < 64 ? ptot - b : 64;
-            valid = lane < fill;
-            if (valid) kc = a.atab_pool[(int)(tn >> 6) + (b + lane - on)];
-            if (PASS) {   // the pass's pixels only, as local ray indices
-                kc -= k0;
-                valid = valid && (unsigned)(kc & 0xffff) < (unsigned)np;
+    PairStream<CLASSIFY> ps(lane, entry, CLASSIFY ? __ballot(lane < cnt && entry == kNoEntry) : 0ull);
+    if (CLASSIFY) tab_count += ps.n_ent;
+    // pairs collected so far, lanes below qfill: kc with the node's lane above it (pixel 16 bits, count 7, lane 6)
+    int q = 0, qfill = 0;
+    for (;;) {
+        int node, kc;
+        const int got = ps.next(a, n, per, tx, ty, tz, guard_count, node, kc);
+        int batch = q, fill = qfill;
+        if (got > 0) {
+            // keep the pairs on a buffered ray that reach it below its outermost emitting point
+            const unsigned ri = lane < got ? rinfo[kc & 0xffff] : 0u;
+            const int pk = __shfl(packed, node, 64);
+            const bool keep = ri != 0u && ((int)(ri & 255u) >= (pk & 255) || ((pk >> 24) & 1));
+            const uint64_t km = __ballot(keep), nm = uniform(~km);
+            const int nk = (int)__popcll(km);
+            if (nk == 0) continue;
+            // the kept ones follow those collected (all lanes take part: a rotation of a partition)
+            const int rank_k = bits_below(km), rank_n = nk + bits_below(nm);
+            const int moved = __builtin_amdgcn_ds_permute(((qfill + (keep ? rank_k : rank_n)) & 63) << 2, kc | (node << 23));
+            batch = lane >= qfill ? moved : q;
+            fill = qfill + nk;
+            if (fill < 64) {
+                q = batch;
+                qfill = fill;
+                continue;
             }
-        }
-        // nodes without a table entry fill what is left of the 64
-        while (fill < 64 && (rem != 0ull || ready >= 0)) {
-            if (ready < 0) {
-                const int j = __ffsll((unsigned long long)rem) - 1;
-                rem &= rem - 1;
-                // (few nodes: their geometry is read again instead of held by every lane)
-                const int jn = rdlane(n, j);
-                const int4 jg = a.geo[jn];
-                const int jsize = jg.w & kSizeMask;
-                Box box;
-                box.b[0] = jg.x; box.b[1] = jg.y; box.b[2] = jg.z;
-                box.e[0] = box.e[1] = box.e[2] = jsize;
-                if (jg.w & kPartialBit) {
-                    const int4 jo = a.olo[jn], je = a.oext[jn];
-                    box.b[0] = jo.x; box.b[1] = jo.y; box.b[2] = jo.z;
-                    box.e[0] = je.x; box.e[1] = je.y; box.e[2] = je.z;
-                }
-                if (per) {
-                    box.b[0] += nearest_copy_shift(2 * jg.x + jsize - tx, per[0]);
-                    box.b[1] += nearest_copy_shift(2 * jg.y + jsize - ty, per[1]);
-                    box.b[2] += nearest_copy_shift(2 * jg.z + jsize - tz, per[2]);
-                }
-                const Lattice L(a.subsample);
-                const float inv_s = 1.0f / (float)a.subsample;
-                const int tc[3] = {tx, ty, tz};
-                for (int q = 0; q < 3; ++q) {
-                    box.o[q] = 0.5f * (float)(2 * box.b[q] - tc[q]);
-                    box.step[q] = (float)box.e[q] * inv_s;
-                }
-                ready_nd = classify_box<PASS>(L, ns, a.npix, a.guard_tol, box, tx, ty, tz, k0, np, &a.queue[1],
-                                              guard_count, ready_kc);
-                ready = j;
-            }
-            if (fill + ready_nd > 64) break;   // (a node has at most 64 pairs: it fits in the next 64)
-            const int kr = __shfl(ready_kc, (lane - fill) & 63, 64);
-            const bool mine = lane >= fill && lane < fill + ready_nd;
-            kc = mine ? kr : kc;
-            node = mine ? ready : node;
-            valid = valid || mine;
-            fill += ready_nd;
-            ready = -1;
+            q = moved;   // (what wrapped around, lanes below fill - 64)
+            qfill = fill - 64;
+            fill = 64;
+        } else {
+            if (fill == 0) break;
+            qfill = 0;
         }
         // --- deposit: this lane's pair over its node's support points lo .. lo + npt - 1 ---
+        const bool valid = lane < fill;
+        node = (batch >> 23) & 63;
+        kc = batch & 0x7fffff;
         const int npk = __shfl(packed, node, 64);
-        const int jlo = npk & 255, npt = valid ? (npk >> 8) & 255 : 0;
+        const int jlo = npk & 255;
+        const unsigned ri = valid ? rinfo[kc & 0xffff] : 0u;
+        const int npt = valid ? min((npk >> 8) & 255, (int)(ri & 255u) - jlo + 1) : 0;
         const Real jd = __shfl(d, node, 64), jhinv = __shfl(hinv, node, 64), jwf = __shfl(wsf, node, 64);
         const Real ja = __shfl(qa, node, 64), je = __shfl(qe, node, 64), jv = __shfl(qv, node, 64);
-        const int k = kc & 0xffff;
+        const int k = (int)(ri >> 8);
         const Real wk = (Real)(kc >> 16) * inv_s3;
         if (any_emits) {
-            // the pixel's share of the emission on the two bracket points, marked in the
-            // ray's mask (the spread forms go with A, E, V below)
+            // the pixel's share of the emission on the two bracket points (the spread forms
+            // go with A, E, V below)
             const Real je0 = __shfl(e0, node, 64), je1 = __shfl(e1, node, 64);
             if (valid && ((npk >> 24) & 1)) {
                 const int jie = (npk >> 16) & 255;
                 Real *row = &R.eps(k, jie);
                 if (je0 != (Real)0) buf_add<Real, 1>(row, wk * je0);
                 if (je1 != (Real)0) buf_add<Real, 1>(row + 1, wk * je1);
-                mark_points(emask + (size_t)k * ew, jie, je0 != (Real)0, je1 != (Real)0);
+                if (KV) mark_points(cmask + (size_t)k * ew, jie, je0 != (Real)0, je1 != (Real)0);
             }
         }
         const int jep = KV ? __shfl(epacked, node, 64) : 0;
@@ -1456,7 +1566,7 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, unsigned l
                                                       a.eps_kernel == K_G) * jqeps;
                 if (wq != (Real)0) {
                     buf_add<Real, 1>(&R.eps(k, jlo + io), wk * wq);
-                    mark_points(emask + (size_t)k * ew, jlo + io, true, false);
+                    mark_points(cmask + (size_t)k * ew, jlo + io, true, false);
                 }
             }
         }
@@ -1515,11 +1625,15 @@ __device__ inline void queue_overflow(const SweepArgs &a, bool fallback, int64_t
 
 // Breadth-first walks of a chunk's targets, a wave per target: one node per
 // lane, ballot and prefix scan to append the accepted nodes to the target's
-// list in device memory and the next frontier in LDS.  A walk is a chain of
+// list in device memory and the next frontier in LDS.  Each accepted node is
+// listed with its (pixel, count) pairs: its entry in the angular table, or its
+// sub-points are classified here and the pairs go to the chunk's pool, of
+// which a wave takes 256 units of 4 pairs at a time.  A walk is a chain of
 // dependent node reads (a level at a time), so it is bound by latency: in a
 // kernel of its own many walks hide each other's (5 workgroups of 4 waves per
 // compute unit by the frontiers' 32 KB), where inside the sweep one target's
-// walk held up the others' barrier.
+// walk held up the others' barrier; and the sweep is rid of the classifier,
+// whose FP64 guard costs it registers.
 constexpr int kWalkWaves = 4;
 __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
 {
@@ -1528,14 +1642,15 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (blockIdx.x == 0 && threadIdx.x == 0) a.queue[0] = 0;   // the sweep of this chunk starts from its first target
     const uint64_t below = (1ull << lane) - 1ull;
-    uint64_t n_test = 0, n_acc = 0;
+    uint64_t n_test = 0, n_acc = 0, n_tab = 0, n_guard = 0;
+    int dpos = 0, dend = 0;   // the wave's part of the pool of pairs, in units
     for (int i = (int)blockIdx.x * kWalkWaves + wave; i < a.n_chunk; i += (int)gridDim.x * kWalkWaves) {
         const int64_t item = a.item0 + i;
         const int64_t cell = a.targets ? a.targets[item] : (int64_t)a.order[item];
         TargetRec r{};
         r.out = a.targets ? item : cell;
         if (cell < 0 || cell >= a.n_cells) {
-            r.skip = 1;
+            r.n_emit = -1;
             if (lane == 0) {
                 a.f_out[r.out] = __longlong_as_double(0x7ff8000000000000ll);
                 if (a.ion_out) a.ion_out[r.out] = 0;
@@ -1554,44 +1669,77 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
         r.tz = 2 * tg.z + r.tsize;
         int per_ext[3] = {D.ext[0], D.ext[1], D.ext[2]};
         const int *per = a.periodic ? per_ext : nullptr;
-        int *const list = a.lists + (size_t)i * a.list_cap;
+        int2 *const list = a.lists + (size_t)i * a.list_cap;
+        uint16_t *const emit_at = a.emit_at + (size_t)i * a.list_cap;
         int *cur = front[wave][0], *nxt = front[wave][1];
         if (lane == 0) cur[0] = D.root;
-        int nfr = 1, nt = 0, no = 0;
+        int nfr = 1, na = 0, ne = 0;
         bool ovf = false;
         while (nfr > 0 && !ovf) {
             int nn = 0;
             for (int base = 0; base < nfr; base += 64) {
                 const bool valid = base + lane < nfr;
                 int n = 0, nch = 0, fc = 0;
-                bool in_tab = false, other = false;
+                int4 g{};
+                int sh[3] = {0, 0, 0};
+                unsigned entry = kNoEntry;
+                bool acc_it = false;
                 if (valid) {
                     n = cur[base + lane];
-                    const int4 g = a.geo[n];
+                    g = a.geo[n];
                     const int2 tp = a.topo[n];
-                    int sh[3];
                     const int what = test_node(a, per, g, tp.y == 0, r.tx, r.ty, r.tz, sh);
-                    if (what == 1) {
-                        in_tab = table_key(a, g.w, g.x + sh[0], g.y + sh[1], g.z + sh[2], r.tx, r.ty, r.tz, r.tsize) >= 0;
-                        other = !in_tab;
-                    }
+                    acc_it = what == 1;
+                    if (acc_it) entry = table_entry(a, g, sh, r.tx, r.ty, r.tz, r.tsize);
                     nch = what == 2 ? tp.y : 0;
                     fc = tp.x;
                 }
                 n_test += min(64, nfr - base);
-                const uint64_t mt = __ballot(in_tab), mo = __ballot(other);
+                const uint64_t macc = __ballot(acc_it), me = __ballot(acc_it && (g.w & kSrcBit) != 0);
                 int tot = 0;
                 const int off = wave_excl_scan_dpp(nch, tot);
-                const int ct = (int)__popcll(mt), co = (int)__popcll(mo);
-                if (nt + no + ct + co > a.list_cap || nn + tot > kWalkFront) {
+                const int ca = (int)__popcll(macc);
+                if (na + ca > a.list_cap || nn + tot > kWalkFront) {
                     ovf = true;
                     break;
                 }
-                if (in_tab) list[nt + (int)__popcll(mt & below)] = n;
-                if (other) list[a.list_cap - 1 - no - (int)__popcll(mo & below)] = n;
+                // the nodes without a table entry, one by one
+                uint64_t todo = __ballot(acc_it && entry == kNoEntry);
+                n_tab += ca - (int)__popcll(todo);
+                while (todo) {
+                    const int j = __ffsll((unsigned long long)todo) - 1;
+                    todo &= todo - 1;
+                    const int4 jg{rdlane(g.x, j), rdlane(g.y, j), rdlane(g.z, j), rdlane(g.w, j)};
+                    const int jsh[3] = {rdlane(sh[0], j), rdlane(sh[1], j), rdlane(sh[2], j)};
+                    int kc = 0;
+                    const int nd = classify_box(Lattice(a.subsample), a.nside, a.npix, a.guard_tol,
+                                                node_box(a, rdlane(n, j), jg, jsh, r.tx, r.ty, r.tz), r.tx, r.ty, r.tz,
+                                                &a.queue[1], n_guard, kc);
+                    const int need = (nd + 3) >> 2;
+                    if (dpos + need > dend) {
+                        int q = 0;
+                        if (lane == 0) q = atomicAdd(&a.queue[4], kDynBlock);
+                        dpos = uniform(q);
+                        dend = dpos + kDynBlock;
+                        if (dpos < 0 || dend > a.dyn_units) {   // the pool is used up: the fallback pass
+                            dpos = dend = 0;
+                            ovf = true;
+                            break;
+                        }
+                    }
+                    if (lane < nd) a.dyn_pool[(size_t)dpos * 4 + lane] = kc;
+                    if (lane == j) entry = kDynEntry | (unsigned)dpos << 6 | (unsigned)(nd - 1);
+                    dpos += need;
+                }
+                if (ovf) break;
+                if (acc_it) {
+                    const int at = na + (int)__popcll(macc & below);
+                    list[at] = int2{n, (int)entry};
+                    if (g.w & kSrcBit) emit_at[ne + (int)__popcll(me & below)] = (uint16_t)at;
+                }
                 for (int c = 0; c < nch; ++c) nxt[nn + off + c] = fc + c;
-                nt += ct;
-                no += co;
+                na += ca;
+                ne += (int)__popcll(me);
                 nn += tot;
             }
             int *t = cur;
@@ -1599,10 +1747,9 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
             nxt = t;
             nfr = nn;
         }
-        r.n_tab = nt;
-        r.n_oth = no;
-        r.skip = ovf ? 1 : 0;
-        n_acc += ovf ? 0 : nt + no;
+        r.n_acc = na;
+        r.n_emit = ovf ? -1 : ne;
+        n_acc += ovf ? 0 : na;
         if (lane == 0) {
             if (a.f32) {
                 const float4 A = ((const float4 *)a.pA)[tnode], B = ((const float4 *)a.pB)[tnode];
@@ -1618,6 +1765,8 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
     if (lane == 0) {
         if (n_acc > 0) atomicAdd(&a.stats[0], (unsigned long long)n_acc);
         if (n_test > 0) atomicAdd(&a.stats[1], (unsigned long long)n_test);
+        if (n_guard > 0) atomicAdd(&a.stats[2], (unsigned long long)n_guard);
+        if (n_tab > 0) atomicAdd(&a.stats[5], (unsigned long long)n_tab);
     }
 }
 
@@ -1697,22 +1846,31 @@ __device__ int walk_shared(const SweepArgs &a, int wave, const int *per, int tx,
     }
 }
 
+// One target as the sweep holds it (the same on every lane).
+struct Target {
+    int dom, tsize, tx, ty, tz, na, ne;   // accepted nodes and, of them, those that emit (< 0: nothing to map)
+    int64_t o, list;                      // output index, first place in the lists
+};
+
 // The sweep of one launch over the listed targets of a chunk.  FALLBACK: the
 // second pass over the items whose walks did not fit in the lists, walked here
 // by the whole workgroup with lists in device memory.
-template <typename Real, int WAVES, bool LDSBUF, bool FALLBACK, bool KV, bool CAS = false, bool PASS = false>
+template <typename Real, int WAVES, bool LDSBUF, bool FALLBACK, bool KV, bool CAS = false>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 {
+    using R4 = typename R4T<Real>::T;
     constexpr int ATOMIC = CAS ? 2 : 1;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar loops over waves' work
-    const int nrm = a.nr_max, npix = a.npix;
-    // rays held at once (all of them, or a.pass_rays per pass)
-    const int prays = PASS && a.pass_rays > 0 ? a.pass_rays : npix;
-    const int npass = PASS ? (npix + prays - 1) / prays : 1;
-    const size_t buf_elems = (size_t)prays * a.stride_k;
+    const int nrm = a.nr_max, npix = a.npix, rays = a.rays;
+    const int ew = uniform(1 + (nrm > 64));   // words of a ray's mask of emitting points (1 or 2)
+    const size_t buf_elems = (size_t)rays * a.stride_k;
     char *p = smem;
+    unsigned long long *const emask = (unsigned long long *)p;   // the masks of all rays, marked before the mapping
+    p += (size_t)npix * ew * 8;
+    unsigned long long *const cmask = (unsigned long long *)p;   // those of the rays with a buffer
+    p += (size_t)rays * ew * 8;
     Real *buf;
     if constexpr (LDSBUF) {
         buf = (Real *)p;
@@ -1722,7 +1880,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     }
     // split: three rows (A, E, V) per ray in buf, the emission rows in device memory
     const bool split = LDSBUF && a.split != 0;
-    Real *const eplane = split ? (Real *)a.ebuf + (size_t)blockIdx.x * npix * nrm : buf;
+    Real *const eplane = split ? (Real *)a.ebuf + (size_t)blockIdx.x * rays * nrm : buf;
     const RayRows<Real> R{buf, eplane, a.stride_k, split ? nrm : a.stride_k, split ? 0 : nrm, nrm};
     Real *rt = (Real *)p;
     p += ((nrm * sizeof(Real) + 15) / 16) * 16;
@@ -1732,13 +1890,11 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     p += nrm * sizeof(double);
     double *rd2 = (double *)p;  // 1 / (2 r_i)
     p += nrm * sizeof(double);
-    int *sc = (int *)p;
-    p += S_COUNT * sizeof(int);
     double *red = (double *)p;
     p += WAVES * sizeof(double);
-    // per ray: the mask of its points that hold emission (ew words)
-    const int ew = nrm > 64 ? 2 : 1;
-    unsigned long long *const emask = (unsigned long long *)p;
+    int *sc = (int *)p;
+    p += S_COUNT * sizeof(int);
+    unsigned *const rinfo = (unsigned *)p;   // per ray: its buffer << 8 | its outermost emitting point, 0: no buffer
     int *fr0 = nullptr;   // fallback: frontiers of gfmax entries, then gamax accepted nodes
     if (FALLBACK) fr0 = a.glist + (size_t)blockIdx.x * (2 * (size_t)a.gfmax + a.gamax);
 
@@ -1749,66 +1905,133 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     int32_t *const next_item = &a.queue[FALLBACK ? 2 : 0];
     // the claim of the next item, by one thread after everyone has read the last one
     auto claim = [&]() {
-        if (tid == 0) sc[S_NEXT] = atomicAdd(next_item, 1);
+        if (threadIdx.x == 0) sc[S_NEXT] = atomicAdd(next_item, 1);
     };
     claim();
+    if (!FALLBACK && blockIdx.x == 0 && tid == 0) a.queue[4] = 0;   // the next chunk's walks start an empty pool of pairs
+    for (int e = tid; e < npix * ew; e += WAVES * 64) emask[e] = 0ull;
     __syncthreads();
     int cached_dom = -1, cached_tsize = -1;   // whose radial tables the LDS holds
+    Target t{};
+    Real teps = 0;
+    double flux_unit = 0, ftarget = 0;   // ftarget: this lane's share of the target's flux
+    bool have = false;
+    // One round: the emission marks of the next target (beside the last waves'
+    // integration of the current one), the current one's flux, then the next
+    // one's buffers, mapping and integration.
     for (;;) {
+        // (the lane's number anew in each part: what is derived from it is not held in registers
+        // through the others, where 80 a lane let 6 waves share a SIMD)
+        const int tid = here((int)threadIdx.x), lane = tid & 63;
         const int64_t item = uniform(sc[S_NEXT]);   // the same on every lane: scalar loads below
-        if (item >= n_items) break;
-        int dom, tsize, tx, ty, tz, nt = 0, no = 0;
-        int64_t o;
-        Real teps, talpha, te, tv;
-        const int32_t *list = nullptr;
+        const bool more = item < n_items;
+        Target x{};
+        x.ne = -1;
+        if (more) {
+            if (!FALLBACK) {
+                const TargetRec &r = a.rec[item];
+                x.dom = uniform(r.dom);
+                x.tsize = uniform(r.tsize);
+                x.tx = uniform(r.tx);
+                x.ty = uniform(r.ty);
+                x.tz = uniform(r.tz);
+                x.na = uniform(r.n_acc);
+                x.ne = uniform(r.n_emit);
+                x.o = r.out;
+                x.list = item * a.list_cap;
+            } else {
+                const int64_t it = a.ovf[item];   // (its cell index was checked when it was queued)
+                const int64_t cell = a.targets ? a.targets[it] : (int64_t)a.order[it];
+                x.o = a.targets ? it : cell;
+                x.dom = uniform(a.cell_dom[cell]);
+                const int4 tg = a.geo[uniform(a.cell_node[cell])];
+                x.tsize = tg.w & kSizeMask;
+                x.tx = 2 * tg.x + x.tsize;
+                x.ty = 2 * tg.y + x.tsize;
+                x.tz = 2 * tg.z + x.tsize;
+                // the walk, by all waves
+                __syncthreads();
+                if (tid == 0) {
+                    for (int q = S_PMEET; q <= S_POVF; ++q) sc[q] = 0;
+                    fr0[0] = a.doms[x.dom].root;
+                }
+                wait_stores();
+                __syncthreads();
+                int *const acc = fr0 + 2 * (size_t)a.gfmax;
+                x.na = walk_shared<WAVES>(a, wave, a.periodic ? a.doms[x.dom].ext : nullptr, x.tx, x.ty, x.tz, fr0,
+                                          fr0 + a.gfmax, acc, sc, a.gfmax, a.gamax, n_test);
+                x.ne = x.na;   // (any of them may emit)
+                n_acc += wave == 0 && x.na > 0 ? x.na : 0;
+            }
+            if (!KV) {
+                // the points that will hold emission, by the waves from the last on (the first
+                // are the last to leave the integration); at least 16 nodes on a wave
+                const DomDev &D = a.doms[x.dom];
+                const int share = min(64, max(16, (x.ne + WAVES - 1) / WAVES));
+                const Real *rtg;
+                if constexpr (sizeof(Real) == 4) rtg = a.r32 + D.r_off;
+                else rtg = a.r64 + D.r_off;
+                for (int e0 = (WAVES - 1 - wave) * share; e0 < x.ne; e0 += WAVES * share) {
+                    const int cnt = min(share, x.ne - e0);
+                    int2 v{0, (int)kNoEntry};
+                    if (lane < cnt) {
+                        if (FALLBACK) v.x = fr0[2 * (size_t)a.gfmax + e0 + lane];
+                        else v = a.lists[x.list + a.emit_at[x.list + e0 + lane]];
+                    }
+                    mark_nodes<Real, FALLBACK>(a, emask, ew, a.periodic ? D.ext : nullptr, rtg, D.nr, (Real)D.rc_inv, v.x,
+                                               (unsigned)v.y, cnt, x.tx, x.ty, x.tz, x.tsize, n_guard);
+                }
+            }
+        }
+        if (have) {
+            const double f = wave_sum(ftarget);
+            if (lane == 0) red[wave] = f;
+        }
+        __syncthreads();
+        if (have && tid == 0) {
+            double f = 0.0;
+            for (int w = 0; w < WAVES; ++w) f += red[w];
+            const double rtp = 0.5 * (double)t.tsize;
+            f += 3.0 * (double)teps / (4.0 * kPi * rtp * rtp);
+            a.f_out[t.o] = f * flux_unit;
+            if (a.ion_out) a.ion_out[t.o] = f > 0.0 ? 1 : 0;
+        }
+        if (!more) break;
+        t = x;
+        have = t.ne >= 0;
+        ftarget = 0.0;
+        if (!have) {   // a bad index, or a walk that did not fit
+            if (FALLBACK && tid == 0) queue_overflow(a, true, item, t.o);
+            claim();   // (everyone has read the last one)
+            __syncthreads();
+            continue;
+        }
+        const DomDev &D = a.doms[t.dom];
+        const int nr = D.nr;
+        const int *per = a.periodic ? D.ext : nullptr;
+        const Real rc_inv = (Real)D.rc_inv;
+        const Real rcoef = (Real)(1.0 / D.rc_inv);
+        flux_unit = D.flux_unit;
+        Real talpha, te, tv;
         if (!FALLBACK) {
             const TargetRec &r = a.rec[item];
-            dom = uniform(r.dom);
-            tsize = uniform(r.tsize);
-            tx = uniform(r.tx);
-            ty = uniform(r.ty);
-            tz = uniform(r.tz);
-            nt = uniform(r.n_tab);
-            no = uniform(r.n_oth);
-            o = r.out;
             teps = (Real)r.eps;
             talpha = (Real)r.alpha;
             te = (Real)r.e;
             tv = (Real)r.v;
-            list = a.lists + (size_t)item * a.list_cap;
-            if (uniform(r.skip)) {
-                __syncthreads();
-                claim();
-                __syncthreads();
-                continue;
-            }
         } else {
-            using R4 = typename R4T<Real>::T;
-            const int64_t it = a.ovf[item];   // (its cell index was checked when it was queued)
-            const int64_t cell = a.targets ? a.targets[it] : (int64_t)a.order[it];
-            o = a.targets ? it : cell;
-            dom = a.cell_dom[cell];
-            const int tnode = a.cell_node[cell];
-            const int4 tg = a.geo[tnode];
-            tsize = tg.w & kSizeMask;
-            tx = 2 * tg.x + tsize;
-            ty = 2 * tg.y + tsize;
-            tz = 2 * tg.z + tsize;
+            const int64_t it = a.ovf[item];
+            const int tnode = uniform(a.cell_node[a.targets ? a.targets[it] : (int64_t)a.order[it]]);
             const R4 tA = ((const R4 *)a.pA)[tnode], tB = ((const R4 *)a.pB)[tnode];
             teps = tA.w;
             talpha = tB.x;
             te = tB.y;
             tv = tB.z;
         }
-        const DomDev &D = a.doms[dom];
-        const int nr = D.nr;
-        const int *per = a.periodic ? D.ext : nullptr;
-        const Real rc_inv = (Real)D.rc_inv;
-        const Real rcoef = (Real)(1.0 / D.rc_inv);
 
         // evaluation points and the self-term weights (W_p at d = 0, h = cell size):
         // kept in LDS while consecutive targets share the domain and cell size
-        if (dom != cached_dom) {
+        if (t.dom != cached_dom) {
             for (int i = tid; i < nr; i += WAVES * 64) {
                 const double rv = a.r64[D.r_off + i];
                 rd[i] = rv;
@@ -1818,50 +2041,47 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             }
             __syncthreads();
         }
-        if (dom != cached_dom || tsize != cached_tsize) {
+        if (t.dom != cached_dom || t.tsize != cached_tsize) {
             if (wave == 0) {
                 Real w0 = 0, w1 = 0;
-                if (lane < nr) w0 = smooth_kernel<Real>(KV && a.mass_gauss != 0, rt[lane] / (Real)tsize);
-                if (lane + 64 < nr) w1 = smooth_kernel<Real>(KV && a.mass_gauss != 0, rt[lane + 64] / (Real)tsize);
+                if (lane < nr) w0 = smooth_kernel<Real>(KV && a.mass_gauss != 0, rt[lane] / (Real)t.tsize);
+                if (lane + 64 < nr) w1 = smooth_kernel<Real>(KV && a.mass_gauss != 0, rt[lane + 64] / (Real)t.tsize);
                 const Real sum = wave_sum(w0 + w1);
                 if (lane < nr) wself[lane] = w0 / sum;
                 if (lane + 64 < nr) wself[lane + 64] = w1 / sum;
             }
             __syncthreads();
-            cached_dom = dom;
-            cached_tsize = tsize;
+            cached_dom = t.dom;
+            cached_tsize = t.tsize;
         }
-        if (FALLBACK) {
-            // the walk, by all waves
-            if (tid == 0) {
-                for (int q = S_PMEET; q <= S_POVF; ++q) sc[q] = 0;
-                fr0[0] = D.root;
+        // The rays with emission (KV: all rays), as many at a time as there are buffers
+        for (int r0 = 0;; r0 += rays) {
+            const int tid = here((int)threadIdx.x), lane = tid & 63;
+            // every wave numbers them (the same values); those of this pass get a buffer and a copy of their mask
+            int ns = 0;
+            for (int base = 0; base < npix; base += 64) {
+                const int k = base + lane;
+                unsigned long long m0 = 0ull, m1 = 0ull;
+                if (!KV && k < npix) {
+                    m0 = emask[(size_t)k * ew];
+                    if (ew > 1) m1 = emask[(size_t)k * ew + 1];
+                }
+                const int top = KV ? (k < npix ? nr - 1 : 0) : mask_top(m0, m1);
+                const uint64_t on = __ballot(top > 0);
+                const int i = ns + bits_below(on) - r0;
+                const bool mine = top > 0 && i >= 0 && i < rays;
+                if (k < npix) rinfo[k] = mine ? (unsigned)(i << 8 | top) : 0u;
+                if (mine) {
+                    cmask[(size_t)i * ew] = m0;
+                    if (ew > 1) cmask[(size_t)i * ew + 1] = m1;
+                }
+                ns += (int)__popcll(on);
             }
-            wait_stores();
-            __syncthreads();
-            int *const acc = fr0 + 2 * (size_t)a.gfmax;
-            nt = walk_shared<WAVES>(a, wave, per, tx, ty, tz, fr0, fr0 + a.gfmax, acc, sc, a.gfmax, a.gamax, n_test);
-            list = acc;
-            if (nt < 0) {
-                __syncthreads();
-                if (tid == 0) queue_overflow(a, true, item, o);
-                claim();
-                __syncthreads();
-                continue;
-            }
-            n_acc += wave == 0 ? nt : 0;
-        }
-        double ftarget = 0.0;   // this lane's share of the target's flux over the passes
-        // The rays k0 .. k0 + np - 1: all of them, or (PASS) one pass of prays
-        // consecutive pixels at a time, the passes looping back here.  Without
-        // passes there is no loop, so the body compiles as straight-line code.
-        int pass = 0;
-    next_pass:
-        {
-            const int k0 = pass * prays, np = PASS ? min(prays, npix - k0) : npix;
-            // ray buffer: zero emission, the target's own share of A, E, V
+            const int np = min(rays, ns - r0);
+            const bool last = r0 + rays >= ns;
+            // their buffers: zero emission, the target's own share of A, E, V, the same on every
+            // ray (point lane, and lane + 64, of each row)
             {
-                // every ray starts from the same values: point lane (and lane + 64) of each row
                 const Real inv_npix = (Real)1 / (Real)npix;
                 const Real w0 = lane < nr ? wself[lane] * inv_npix : (Real)0;
                 const Real w1 = lane + 64 < nr ? wself[lane + 64] * inv_npix : (Real)0;
@@ -1883,36 +2103,38 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                         dst[2 * nrm + 64] = tv * w1;
                     }
                 }
-                for (int e = tid; e < np * ew; e += WAVES * 64) emask[e] = 0ull;
                 // (the emission plane of split buffers is zero here: cleared when
                 // allocated and, entry by entry, by the march that reads it)
             }
             __syncthreads();
-            if (pass == 0) claim();   // (visible to all after the mapping)
+            if (r0 == 0) claim();   // (visible to all after the mapping)
+            // the next target's marks start from zero
+            if (last)
+                for (int e = tid; e < npix * ew; e += WAVES * 64) emask[e] = 0ull;
 
-            // --- every wave maps an equal share of the table nodes and of the others, in
-            // rounds of at most 64 nodes (62 on average: each share is rounded; classifying
-            // a node takes a wave ten times as long as mapping one from the table, so the
-            // shares are equal in both).  A share is every nc-th node of the walk: its nodes
-            // come level by level, so those of a batch have supports of similar length, but
-            // from all directions: siblings side by side would meet on the same rays' points
-            // (3.3 lanes on one point at N_side 2, 2.0 at N_side 4, against 1.6 and 1.1) ---
-            {
-                const int rounds = (nt + no + 62 * WAVES - 1) / (62 * WAVES);
+            // --- every wave maps an equal share of the nodes, in rounds of at most 64.  A share
+            // is every nc-th node of the walk: its nodes come level by level, so those of a
+            // batch have supports of similar length, but from all directions: siblings side by
+            // side would meet on the same rays' points (3.3 lanes on one point at N_side 2, 2.0
+            // at N_side 4, against 1.6 and 1.1) ---
+            if (np > 0) {
+                const int lane = here(lane_id());
+                const int rounds = (t.na + 64 * WAVES - 1) / (64 * WAVES);
                 const int nc = max(rounds, 1) * WAVES;
-                for (int r = 0; r < rounds; ++r) {
-                    const int ct = r * WAVES + wave, co = nc - 1 - ct;
-                    const int mt = (nt - ct + nc - 1) / nc, mo = (no - co + nc - 1) / nc;
-                    const int cnt = mt + mo;
-                    int n = 0;
-                    if (lane < cnt) n = lane < mo ? list[a.list_cap - 1 - co - nc * lane] : list[ct + nc * (lane - mo)];
-                    map_nodes<Real, ATOMIC, KV, PASS>(a, R, emask, ew, per, rt, nr, rc_inv, rcoef, n, cnt, tx, ty, tz,
-                                                      tsize, k0, np, n_guard, n_tab);
+                for (int c = wave; c < nc; c += WAVES) {
+                    const int cnt = (t.na - c + nc - 1) / nc;
+                    int2 v{0, (int)kNoEntry};
+                    if (lane < cnt) {
+                        if (FALLBACK) v.x = fr0[2 * (size_t)a.gfmax + c + nc * lane];
+                        else v = a.lists[t.list + c + nc * lane];
+                    }
+                    map_nodes<Real, ATOMIC, KV, FALLBACK>(a, R, rinfo, cmask, ew, per, rt, nr, rc_inv, rcoef, v.x,
+                                                          (unsigned)v.y, cnt, t.tx, t.ty, t.tz, t.tsize, n_guard, n_tab);
                 }
             }
             __syncthreads();
 
-            // --- per-ray integration and the sum over rays (rays without emission give 0) ---
+            // --- per-ray integration and the sum over rays (KV: rays without emission give 0) ---
             constexpr int IW = WAVES;
             double fsum = 0.0;
             float cs_hi = 0.0f, cs_lo = 0.0f;   // compensated FP32 sum of this lane's FP32-marched rays
@@ -1923,13 +2145,14 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                 // class share a batch of 64 / g rays of g lanes; the batches, widest
                 // class first and pixel order within a class, are dealt round robin
                 // over the waves.
+                const int lane = here(lane_id());
                 const int lg0 = 31 - __clz(a.int_group);
                 int nb[6];   // batches of classes 2 .. 7 (class 7: a ray each)
                 {
                     int n[6] = {0, 0, 0, 0, 0, 0};
                     for (int base = 0; base < np; base += 64) {
                         int tp;
-                        const int c = ray_class(emask, ew, np, lg0, base + lane, tp);
+                        const int c = ray_class(cmask, ew, np, lg0, base + lane, tp);
 #pragma unroll
                         for (int q = 0; q < 6; ++q) n[q] += (int)__popcll(__ballot(c == q + 2));
                     }
@@ -1956,7 +2179,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                     int myk = -1, mytp = 0, run = 0;
                     for (int base = 0; base < np && run < bi * ng + ng; base += 64) {
                         int tp;
-                        const int c = ray_class(emask, ew, np, lg0, base + lane, tp);
+                        const int c = ray_class(cmask, ew, np, lg0, base + lane, tp);
                         const uint64_t m = __ballot(c == cls);
                         const int n = (int)__popcll(m), w = want - run;
                         const bool mine = w >= 0 && w < n;
@@ -1976,8 +2199,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                     // the ray's mask, for its group's lanes to find their emitting points
                     unsigned long long m0 = 0ull, m1 = 0ull;
                     if (myk >= 0) {
-                        m0 = emask[(size_t)myk * ew];
-                        if (ew > 1) m1 = emask[(size_t)myk * ew + 1];
+                        m0 = cmask[(size_t)myk * ew];
+                        if (ew > 1) m1 = cmask[(size_t)myk * ew + 1];
                     }
                     switch (cls) {
                         case 2: march_batch<Real, 4>(a, R, myk, m0, m1, rcoef, rd, rd2, nr, split, fsum, cs_hi, cs_lo, n_f32, n_f64); break;
@@ -1993,7 +2216,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                 for (int base = 0; base < np; base += 64) {
                     int t = 0;
                     if (base + lane < np)
-                        t = mask_top(emask[(size_t)(base + lane) * ew], ew > 1 ? emask[(size_t)(base + lane) * ew + 1] : 0ull);
+                        t = mask_top(cmask[(size_t)(base + lane) * ew], ew > 1 ? cmask[(size_t)(base + lane) * ew + 1] : 0ull);
                     uint64_t m = __ballot(t > 0);
                     while (m) {
                         const int l = __ffsll((unsigned long long)m) - 1;
@@ -2011,26 +2234,13 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             } else {
                 // a lane per ray: ray k on lane k % 64 of wave (k / 64) % IW
                 for (int k = wave * 64 + lane; k < np; k += 64 * IW) {
-                    const int t = mask_top(emask[(size_t)k * ew], ew > 1 ? emask[(size_t)k * ew + 1] : 0ull);
+                    const int t = mask_top(cmask[(size_t)k * ew], ew > 1 ? cmask[(size_t)k * ew + 1] : 0ull);
                     if (t > 0) fsum += integrate_ray<Real>(R, k, rd, rd2, nr, t, a.nside, a.zeta_g, split);
                 }
             }
             ftarget += fsum + ((double)cs_hi + (double)cs_lo);
-        }
-        if (PASS && ++pass < npass) {
-            __syncthreads();   // the next pass re-initialises the buffers
-            goto next_pass;
-        }
-        const double fsum = wave_sum(ftarget);
-        if (lane == 0) red[wave] = fsum;
-        __syncthreads();
-        if (tid == 0) {
-            double f = 0.0;
-            for (int w = 0; w < WAVES; ++w) f += red[w];
-            const double rtp = 0.5 * (double)tsize;
-            f += 3.0 * (double)teps / (4.0 * kPi * rtp * rtp);
-            a.f_out[o] = f * D.flux_unit;
-            if (a.ion_out) a.ion_out[o] = f > 0.0 ? 1 : 0;
+            if (last) break;
+            __syncthreads();   // the next pass takes the buffers
         }
     }
     // statistics
@@ -2072,9 +2282,11 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_kv_fallback(SweepArgs a
 
 // FP32 ray buffers in LDS accumulated by compare-and-swap (4, 8 and 16 waves).
 // With 4 waves per target 6 targets are resident: 6 waves per SIMD in 80
-// registers (41 spilled, outside the inner loops) are faster than 4 without
-// spills, 169 against 195 ms on 128^3 at N_side 2: between its barriers a
+// registers (44 spilled, outside the inner loops) are faster than 4 without
+// spills (169 against 195 ms on 128^3 at N_side 2): between its barriers a
 // target's waves wait for memory and LDS, and only other targets fill that.
+// With 8 waves 80 registers bring 3 targets instead of 2, but cost as much (93
+// against 91 ms on the adaptive grid at N_side 4).
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 6 : 4) void k_sweep_cas(SweepArgs a)
 {
@@ -2085,18 +2297,6 @@ template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_cas_fallback(SweepArgs a)
 {
     sweep_body<float, WAVES, true, true, false, true>(a);
-}
-
-// LDS ray buffers for part of a target's rays at a time (passes)
-template <typename Real, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_pass(SweepArgs a)
-{
-    sweep_body<Real, WAVES, true, false, false, false, true>(a);
-}
-template <typename Real, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_pass_fallback(SweepArgs a)
-{
-    sweep_body<Real, WAVES, true, true, false, false, true>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -2111,8 +2311,8 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_pass_fallback(SweepArgs
 // offset, in units of the target's size, with the classifier the sweep itself
 // uses: relative sub-point positions scale exactly with the size, so a table
 // entry holds exactly what the sweep would compute for that node.  A wave
-// takes a contiguous run of offsets: first (idx NULL) it counts their pairs,
-// then, with the runs' first pairs known, it writes them.  A wave per offset
+// takes a contiguous run of offsets: first (idx NULL) it counts their pairs (in
+// units of 4), then, with the runs' first units known, it writes them.  A wave per offset
 // classifies in FP32 with the FP64 guard band: 1.2 ms for 4.8 million offsets
 // where a thread per offset in FP64 took 1 ms for 0.6 million.
 // ---------------------------------------------------------------------------
@@ -2152,12 +2352,12 @@ __global__ __launch_bounds__(256) void k_atab(AtabGeom G, int ns, int s, float g
             box.step[q] = (float)(1 << ri) * (1.0f / (float)s);
         }
         int kc = 0;
-        const int nd = classify_box<false>(L, ns, 12 * ns * ns, guard_tol, box, 1, 1, 1, 0, 0, flag, guard, kc);
+        const int nd = classify_box(L, ns, 12 * ns * ns, guard_tol, box, 1, 1, 1, flag, guard, kc);
         if (idx) {
-            if (lane < nd) pool[at + lane] = kc;
+            if (lane < nd) pool[at * 4 + lane] = kc;
             if (lane == 0) idx[key] = (int32_t)(((unsigned)at << 6) | (unsigned)(nd - 1));
         }
-        at += nd;
+        at += (nd + 3) >> 2;
     }
     if (!idx && lane == 0) sums[wave] = at;
 }
@@ -2353,8 +2553,11 @@ struct tr_ctx {
     size_t gbuf_bytes = 0;
     void *ebuf = nullptr;   // emission rows of split LDS buffers
     size_t ebuf_bytes = 0;
-    int32_t *lists = nullptr;            // the listed walks of a chunk of targets and their records
+    int2 *lists = nullptr;               // the listed walks of a chunk of targets, their records, the pool
+    uint16_t *emit_at = nullptr;         // of pairs of the nodes outside the angular table
     TargetRec *rec = nullptr;
+    int32_t *dyn_pool = nullptr;
+    int32_t dyn_units = 0;
     int64_t list_targets = 0;
     int32_t *glist = nullptr;            // walk lists of the fallback pass
     int32_t *ovf = nullptr;              // items queued for it
@@ -2442,7 +2645,9 @@ void free_domains(tr_ctx *c)
     dfree(c->ebuf);
     c->ebuf_bytes = 0;
     dfree(c->lists);
+    dfree(c->emit_at);
     dfree(c->rec);
+    dfree(c->dyn_pool);
     c->list_targets = 0;
     dfree(c->glist);
     dfree(c->ovf);
@@ -2491,20 +2696,21 @@ tr_status dalloc(tr_ctx *c, void **p, size_t bytes)
     return TR_OK;
 }
 
-// LDS bytes of one sweep workgroup (must mirror the carve-up in k_sweep)
-size_t sweep_lds_bytes(size_t real, int npix, int stride_k, int nrm, int waves, bool ldsbuf)
+// LDS bytes of one sweep workgroup with buffers for `rays` rays (must mirror the carve-up in sweep_body)
+size_t sweep_lds_bytes(size_t real, int npix, int rays, int stride_k, int nrm, int waves, bool ldsbuf)
 {
-    size_t b = 0;
-    if (ldsbuf) b += (((size_t)npix * stride_k * real + 15) / 16) * 16;
+    const size_t ew = nrm > 64 ? 2 : 1;
+    size_t b = ((size_t)npix + rays) * 8 * ew;
+    if (ldsbuf) b += (((size_t)rays * stride_k * real + 15) / 16) * 16;
     b += 2 * (((size_t)nrm * real + 15) / 16) * 16;
     b += 2 * (size_t)nrm * 8;
-    b += S_COUNT * 4;
     b += (size_t)waves * 8;
-    b += (size_t)npix * 8 * (nrm > 64 ? 2 : 1);
+    b += S_COUNT * 4;
+    b += (size_t)npix * 4;
     return b;
 }
 
-constexpr size_t kLdsMax = 160 * 1024;
+constexpr size_t kLdsMax = 160 * 1024, kLdsGranule = 1280;
 
 using KernelFn = void (*)(SweepArgs);
 
@@ -2519,15 +2725,6 @@ KernelFn pick_kernel_kv(int waves, bool ldsbuf, bool fallback)
         if (fallback) return ldsbuf ? (KernelFn)k_sweep_kv_fallback<Real, 8, true> : (KernelFn)k_sweep_kv_fallback<Real, 8, false>;
         return ldsbuf ? (KernelFn)k_sweep_kv<Real, 8, true> : (KernelFn)k_sweep_kv<Real, 8, false>;
     }
-    return nullptr;
-}
-
-template <typename Real>
-KernelFn pick_kernel_pass(int waves, bool fallback)
-{
-    if (waves == 4) return fallback ? (KernelFn)k_sweep_pass_fallback<Real, 4> : (KernelFn)k_sweep_pass<Real, 4>;
-    if (waves == 8) return fallback ? (KernelFn)k_sweep_pass_fallback<Real, 8> : (KernelFn)k_sweep_pass<Real, 8>;
-    if (waves == 16) return fallback ? (KernelFn)k_sweep_pass_fallback<Real, 16> : (KernelFn)k_sweep_pass<Real, 16>;
     return nullptr;
 }
 
@@ -2566,7 +2763,7 @@ struct LaunchPlan {
     bool ldsbuf = true;
     bool cas = false;   // FP32 LDS buffers accumulated by compare-and-swap
     bool split = false; // A, E, V rows in LDS, emission rows in device memory
-    int pass_rays = 0;  // > 0: four rows per ray in LDS for this many rays at a time (passes)
+    int rays = 0;       // ray buffers of a workgroup
     int intm = 1;   // integration: 1 a lane per ray, 2 a wave per ray, 3/4/5 a group of 4/8/16 lanes,
                     // 6/7/8 the same groups with the FP32 march (FP32 buffers only)
 };
@@ -2584,95 +2781,93 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     int waves = waves_req;
     if (waves <= 0) {
         waves = c->tuned_waves[f32 ? 1 : 0];
-        // From N_side 4 on one target's buffers fill the LDS: 16 waves on it.  Below, several
-        // targets are resident, and the fewer waves share one the better their phases overlap:
-        // FP32C 128^3 N_side 2, 6 targets of 4 waves 169 ms, 4 of 4 waves 195 ms, 2 of 8 waves
-        // 233 ms; the FP64 buffers leave room for 2 or 3 targets (61 ms with 4 or 8 waves)
-        if (waves <= 0) waves = npix >= 192 ? 16 : (f32 ? 4 : 8);
+        // Several targets are resident, and the fewer waves share one the better their phases
+        // overlap (128^3 N_side 2 FP32C, 16 sources: 6 targets of 4 waves 158 ms, 2 of 8 waves
+        // 202 ms), as long as a target's rays with emission fit its share of the buffers at once:
+        // with many sources most rays hold emission, and 8 waves on fewer targets save passes
+        // (N_side 4, FP32C / FP64: one source on 64^3, 4 waves 14.3 / 19.5 ms, 8 waves 19.0 /
+        // 21.0 ms; 200 / 60 sources on an adaptive grid 97 / 35 ms against 82 / 30 ms; N_side 2
+        // FP64, one source 8.2 against 10.3 ms, 1000 sources 69 against 63 ms).  In FP32 below
+        // N_side 4 all rays' buffers fit 6 targets (the emission rows in device memory).
+        if (waves <= 0) {
+            const int64_t few = (int64_t)(npix >= 192 ? 8 : 16) * c->n_dom;
+            waves = (f32 && npix < 192) || c->n_src_dev <= few ? 4 : 8;
+        }
     }
     // the radial-kernel variants are built for 4 and 8 waves per target only
     const bool kv = !((c->p.eps_kernel == 0 || c->p.eps_kernel == 3) && (c->p.mass_kernel == 0 || c->p.mass_kernel == 5));
     if (kv) waves = waves <= 4 ? 4 : 8;
     L.waves = waves;
     int bm = buf_req > 0 ? buf_req : c->tuned_buf[f32 ? 1 : 0];
-    // four rows per ray in LDS (odd stride: ray k of lane k hits distinct banks); else, in
-    // FP32, the A, E, V rows in LDS and the emission rows in device memory; else all in
-    // device memory
-    const int stride4 = 4 * nrm + 1, stride3 = 3 * nrm + 1;
-    const bool fits4 = sweep_lds_bytes(real, npix, stride4, nrm, waves, true) <= kLdsMax;
-    const bool fits3 = f32 && !kv && sweep_lds_bytes(real, npix, stride3, nrm, waves, true) <= kLdsMax;
-    // else (FP64, or radial-kernel variants) the rays in LDS for as many as fit, with four rows
-    // per ray or (fewer passes) the split rows, a target's rays mapped and integrated in
-    // passes over equal pixel ranges
-    int pass_rays = 0;
-    bool pass_split = false;
-    if (!fits4 && !fits3 && bm != 2 && !kv && (waves == 4 || waves == 8 || waves == 16)) {
-        auto passes = [&](int stride) {   // passes of the largest ray count that fits (0: none)
-            for (int r = npix - 1; r >= 16; --r)
-                if (sweep_lds_bytes(real, r, stride, nrm, waves, true) <= kLdsMax) return (npix + r - 1) / r;
-            return 0;
-        };
-        const int n4 = passes(stride4), n3 = kv ? 0 : passes(stride3);
-        const int n = n3 > 0 && (n4 == 0 || n3 < n4) ? n3 : n4;
-        if (n > 0) {
-            pass_rays = (npix + n - 1) / n;
-            pass_split = n == n3 && n3 != n4;
-        }
-    }
-    if (bm == 1 && !fits4 && !fits3 && pass_rays == 0)
-        return fail(c, TR_EINVAL, "ray buffers do not fit in LDS for this N_PIX and N_R");
-    L.ldsbuf = bm == 2 ? false : (fits4 || fits3 || pass_rays > 0);
-    L.pass_rays = L.ldsbuf && !fits4 && !fits3 ? pass_rays : 0;
-    L.split = L.ldsbuf && !fits4 && (fits3 || (L.pass_rays > 0 && pass_split));
-    L.stride_k = L.split ? stride3 : stride4;
-    L.lds = sweep_lds_bytes(real, L.pass_rays > 0 ? L.pass_rays : npix, L.stride_k, nrm, waves, L.ldsbuf);
     if (kv) {
-        L.fn = f32 ? pick_kernel_kv<float>(waves, L.ldsbuf, false) : pick_kernel_kv<double>(waves, L.ldsbuf, false);
-        L.fn_fb = f32 ? pick_kernel_kv<float>(waves, L.ldsbuf, true) : pick_kernel_kv<double>(waves, L.ldsbuf, true);
+        L.fn = f32 ? pick_kernel_kv<float>(waves, bm != 2, false) : pick_kernel_kv<double>(waves, bm != 2, false);
     } else {
-        L.fn = f32 ? pick_kernel<float>(waves, L.ldsbuf, false) : pick_kernel<double>(waves, L.ldsbuf, false);
-        L.fn_fb = f32 ? pick_kernel<float>(waves, L.ldsbuf, true) : pick_kernel<double>(waves, L.ldsbuf, true);
+        L.fn = f32 ? pick_kernel<float>(waves, bm != 2, false) : pick_kernel<double>(waves, bm != 2, false);
     }
-    if (!L.fn || !L.fn_fb) return fail(c, TR_EINVAL, "waves per target must be 1, 2, 4, 8 or 16");
-    // accumulation: compare-and-swap by default (FP32, LDS, 8 or 16 waves)
+    if (!L.fn) return fail(c, TR_EINVAL, "waves per target must be 1, 2, 4, 8 or 16");
+    // accumulation: compare-and-swap by default (FP32, LDS; 4 waves where they are the default pick)
     {
         const int am = atom_req > 0 ? atom_req : (c->atommode > 0 ? c->atommode : c->tuned_atom[f32 ? 1 : 0]);
-        L.cas = f32 && L.ldsbuf && !kv && L.pass_rays == 0 &&
+        L.cas = f32 && bm != 2 && !kv &&
                 (waves == 8 || waves == 16 ? (am > 0 ? am == 2 : true) : waves == 4 && (am > 0 ? am == 2 : waves_req <= 0));
-        if (L.cas) {
-            L.fn = pick_kernel_cas(waves, false);
-            L.fn_fb = pick_kernel_cas(waves, true);
+        if (L.cas) L.fn = pick_kernel_cas(waves, false);
+    }
+    // Ray buffers: a target's rays that hold emission (KV: all) are mapped and integrated as
+    // many at a time as there are buffers.  Four rows per ray (odd stride: ray k of lane k hits
+    // distinct banks), or in FP32 the A, E, V rows in LDS and the emission rows in device memory
+    // where that holds more rays.  As many targets share a compute unit as the registers allow,
+    // fewer while that leaves a target less than 32 buffers; below 16 for one target alone, all
+    // buffers are in device memory.
+    const int stride4 = 4 * nrm + 1, stride3 = 3 * nrm + 1;
+    int occ = 0;
+    const size_t fixed = sweep_lds_bytes(real, npix, 0, stride4, nrm, waves, true);
+    if (bm != 2 && fixed < kLdsMax) {
+        HIPCHK(hipFuncSetAttribute((const void *)L.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
+        HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void *)L.fn, waves * 64, 0));
+        if (tpc_req > 0) occ = std::min(occ, tpc_req);
+        for (; occ >= 1; --occ) {
+            const size_t room = kLdsMax / (size_t)occ / kLdsGranule * kLdsGranule;
+            auto fit = [&](int stride) {
+                int r = npix;
+                if (sweep_lds_bytes(real, npix, r, stride, nrm, waves, true) > room) {
+                    r = room <= fixed + 16 ? 0 : (int)((room - fixed - 16) / ((size_t)stride * real + 8 * (nrm > 64 ? 2 : 1)));
+                    r = std::min(r, npix);
+                }
+                return r;
+            };
+            const int r4 = fit(stride4), r3 = f32 && !kv ? fit(stride3) : 0;
+            L.split = r4 < npix && r3 > r4;
+            L.rays = L.split ? r3 : r4;
+            if (L.rays >= std::min(npix, occ > 1 ? 32 : 16)) break;
         }
     }
-    if (L.pass_rays > 0) {   // (hardware atomics)
-        L.fn = f32 ? pick_kernel_pass<float>(waves, false) : pick_kernel_pass<double>(waves, false);
-        L.fn_fb = f32 ? pick_kernel_pass<float>(waves, true) : pick_kernel_pass<double>(waves, true);
+    L.ldsbuf = occ >= 1;
+    if (bm == 1 && !L.ldsbuf) return fail(c, TR_EINVAL, "ray buffers do not fit in LDS for this N_PIX and N_R");
+    if (!L.ldsbuf) {
+        L.rays = npix;
+        L.split = false;
+        L.cas = false;
+        L.fn = kv ? (f32 ? pick_kernel_kv<float>(waves, false, false) : pick_kernel_kv<double>(waves, false, false))
+                  : (f32 ? pick_kernel<float>(waves, false, false) : pick_kernel<double>(waves, false, false));
     }
+    L.fn_fb = L.cas ? pick_kernel_cas(waves, true)
+                    : kv ? (f32 ? pick_kernel_kv<float>(waves, L.ldsbuf, true) : pick_kernel_kv<double>(waves, L.ldsbuf, true))
+                         : (f32 ? pick_kernel<float>(waves, L.ldsbuf, true) : pick_kernel<double>(waves, L.ldsbuf, true));
+    L.stride_k = L.split ? stride3 : stride4;
+    L.lds = sweep_lds_bytes(real, npix, L.rays, L.stride_k, nrm, waves, L.ldsbuf);
+    if (L.lds > kLdsMax)
+        return fail(c, TR_EINVAL, "sweep kernel does not fit on a compute unit (LDS " + std::to_string(L.lds) + " B)");
     HIPCHK(hipFuncSetAttribute((const void *)L.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.lds));
     HIPCHK(hipFuncSetAttribute((const void *)L.fn_fb, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.lds));
-    int occ = 0;
     HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void *)L.fn, waves * 64, L.lds));
-    // where both forms fit, the split one if more targets are resident with its smaller buffers
-    if (L.ldsbuf && fits4 && fits3) {
-        const size_t lds3 = sweep_lds_bytes(real, npix, stride3, nrm, waves, true);
-        int occ3 = 0;
-        HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ3, (const void *)L.fn, waves * 64, lds3));
-        if (occ3 > occ) {
-            occ = occ3;
-            L.lds = lds3;
-            L.split = true;
-            L.stride_k = stride3;
-        }
-    }
     if (occ <= 0) return fail(c, TR_EINVAL, "sweep kernel does not fit on a compute unit (LDS " + std::to_string(L.lds) + " B)");
     L.per_cu = tpc_req > 0 ? std::min(tpc_req, occ) : occ;
-    // integration: by default a group of lanes per ray, so that a target's few
-    // emitting rays share a wave (rays with more emitting points than the group
-    // has lanes take a wave): 16 lanes from N_side 4 on, where a ray crosses
-    // more nodes, else 8
+    // integration: by default groups of at least 4 lanes per ray, so that a target's few
+    // emitting rays share a wave (a ray with more emitting points gets a wider group): against
+    // groups of at least 8 or 16 lanes 2 to 15% faster at N_side 4, equal at N_side 2
     const int im = int_req > 0 ? int_req : c->tuned_int[f32 ? 1 : 0];
     // (FP32 buffers march in FP32 by default, the FP64 form in FP64)
-    L.intm = im > 0 ? im : (npix >= 192 ? 5 : 4) + (f32 ? 3 : 0);
+    L.intm = im > 0 ? im : 3 + (f32 ? 3 : 0);
     if (L.intm >= 6 && !f32) L.intm -= 3;
     L.chunk = std::min<int64_t>(n_items, kListTargets);
     L.blocks = (int)std::min<int64_t>((int64_t)c->n_cu * L.per_cu, L.chunk);
@@ -2680,10 +2875,18 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     if (c->list_targets < L.chunk) {
         drop_graph(c);
         dfree(c->lists);
+        dfree(c->emit_at);
         dfree(c->rec);
+        dfree(c->dyn_pool);
         c->list_targets = 0;
-        if (dalloc(c, (void **)&c->lists, sizeof(int32_t) * (size_t)L.chunk * kListCap) ||
-            dalloc(c, (void **)&c->rec, sizeof(TargetRec) * (size_t)L.chunk))
+        // pairs outside the table: 4% of some 1000 nodes of about 3 (N_side 2) to 12 (N_side 8)
+        // pairs; room for 1024 a target up to N_side 4, 4096 beyond, and a block for every wave
+        c->dyn_units = (int32_t)std::min<int64_t>(
+            (1 << 25) - 1, L.chunk * (c->p.nside <= 4 ? 256 : 1024) + (int64_t)c->n_cu * kWalkPerCu * kWalkWaves * kDynBlock);
+        if (dalloc(c, (void **)&c->lists, sizeof(int2) * (size_t)L.chunk * kListCap) ||
+            dalloc(c, (void **)&c->emit_at, sizeof(uint16_t) * (size_t)L.chunk * kListCap) ||
+            dalloc(c, (void **)&c->rec, sizeof(TargetRec) * (size_t)L.chunk) ||
+            dalloc(c, (void **)&c->dyn_pool, 16 * (size_t)c->dyn_units))
             return TR_ENOMEM;
         c->list_targets = L.chunk;
     }
@@ -2703,7 +2906,7 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     // n_cu x min(per_cu, kFallbackPerCu) workgroups)
     const size_t nblk = (size_t)std::max<int64_t>(L.blocks, (int64_t)c->n_cu * std::min(L.per_cu, kFallbackPerCu));
     if (!L.ldsbuf) {
-        const size_t need = nblk * npix * L.stride_k * real;
+        const size_t need = nblk * L.rays * L.stride_k * real;
         if (need > c->gbuf_bytes) {
             drop_graph(c);
             dfree(c->gbuf);
@@ -2713,7 +2916,7 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
         }
     }
     if (L.split) {
-        const size_t need = nblk * npix * nrm * real;
+        const size_t need = nblk * L.rays * nrm * real;
         if (need > c->ebuf_bytes) {
             drop_graph(c);
             dfree(c->ebuf);
@@ -2763,7 +2966,7 @@ tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_o
     a.gbuf = c->gbuf;
     a.ebuf = c->ebuf;
     a.split = L.split ? 1 : 0;
-    a.pass_rays = L.pass_rays;
+    a.rays = L.rays;
     a.theta2 = c->p.theta * c->p.theta;
     a.theta_if2 = c->p.theta_if > 0.0 ? c->p.theta_if * c->p.theta_if : 0.0;
     a.theta_src2 = c->p.theta_src > 0.0 ? c->p.theta_src * c->p.theta_src : 0.0;
@@ -2773,6 +2976,9 @@ tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_o
     a.subsample = c->p.subsample;
     a.f32 = c->p.precision == TR_FP32C ? 1 : 0;
     a.lists = c->lists;
+    a.emit_at = c->emit_at;
+    a.dyn_pool = c->dyn_pool;
+    a.dyn_units = c->dyn_units;
     a.rec = c->rec;
     a.list_cap = kListCap;
     a.nr_max = c->nr_max;
@@ -2797,7 +3003,7 @@ tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_o
         a.atab_base[q] = c->atab.base[q];
     }
     (void)hipGetLastError();   // a stale error of an earlier, unrelated call is not ours
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, c->stream, c->queue, (int64_t)4, 0);
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, c->stream, c->queue, (int64_t)8, 0);
     hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, c->stream, c->stats, (int64_t)8);
     if (timed) HIPCHK(hipEventRecord(c->ev0, c->stream));
     // the targets a chunk at a time: their walks, then their mapping and integration
@@ -2811,10 +3017,7 @@ tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_o
     // the targets whose walks did not fit in the lists, again with longer lists per workgroup
     // (it ends at once when none was queued)
     {
-        a.list_cap = 0;   // (their lists hold every node in walk order)
-        const size_t lds = sweep_lds_bytes(c->p.precision == TR_FP32C ? 4 : 8, L.pass_rays > 0 ? L.pass_rays : a.npix,
-                                           L.stride_k, c->nr_max, L.waves, L.ldsbuf);
-        hipLaunchKernelGGL(L.fn_fb, dim3(c->n_cu * std::min(L.per_cu, kFallbackPerCu)), dim3(L.waves * 64), lds,
+        hipLaunchKernelGGL(L.fn_fb, dim3(c->n_cu * std::min(L.per_cu, kFallbackPerCu)), dim3(L.waves * 64), L.lds,
                            c->stream, a);
     }
     HIPCHK(hipGetLastError());
@@ -2824,7 +3027,7 @@ tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_o
     }
     c->last_waves = L.waves;
     c->last_tpc = L.per_cu;
-    c->last_lds = L.ldsbuf ? (L.pass_rays > 0 ? 3 : (L.split ? 2 : 1)) : 0;
+    c->last_lds = L.ldsbuf ? (L.split ? 2 : (L.rays < a.npix ? 3 : 1)) : 0;
     c->last_intw = lanes_per_ray(L.intm);
     c->last_int32 = L.intm >= 6 ? 1 : 0;
     c->last_cas = L.cas ? 1 : 0;
@@ -2946,14 +3149,14 @@ tr_status build_angular_table(tr_ctx *c)
         int64_t tot = 0;
         for (auto &v : h) {
             const int64_t n = v;
-            v = tot;   // first pair of each run
+            v = tot;   // first unit (4 pairs) of each run
             tot += n;
         }
-        if (tot >= (1ll << 26) - 64) {   // (first << 6) | (pairs - 1) must fit: without the largest ratio
+        if (tot >= 1ll << 25) {   // (first unit << 6) | (pairs - 1) below kDynEntry: without the largest ratio
             dfree(sums);
             continue;
         }
-        if ((st = dalloc(c, (void **)&c->atab_pool, sizeof(int32_t) * (size_t)tot)) ||
+        if ((st = dalloc(c, (void **)&c->atab_pool, sizeof(int32_t) * 4 * (size_t)tot)) ||
             (st = dalloc(c, (void **)&c->atab_idx, sizeof(int32_t) * (size_t)nk))) {
             dfree(sums);
             return st;
@@ -3535,28 +3738,31 @@ tr_status tr_autotune(tr_ctx *c, double *best_ms)
         return true;
     };
     // waves and buffer place with the default integration, then the integration form
+    // (4 waves accumulate by compare-and-swap only when asked to)
+    int ba = 0;
     for (int bm = 1; bm <= 2; ++bm)
         for (int w : cand) {
+            const int am = w == 4 && bm == 1 && c->p.precision == TR_FP32C ? 2 : 0;
             double ms;
-            if (timed(w, bm, 0, ms) && ms < best) {
+            if (timed(w, bm, 0, ms, am) && ms < best) {
                 best = ms;
                 bw = w;
                 bb = bm;
                 bi = 0;
+                ba = am;
             }
         }
     if (bw > 0)
         for (int im : {1, 2, 3, 4, 5, 6, 7, 8}) {
             if (im >= 6 && c->p.precision != TR_FP32C) break;
             double ms;
-            if (timed(bw, bb, im, ms) && ms < best) {
+            if (timed(bw, bb, im, ms, ba) && ms < best) {
                 best = ms;
                 bi = im;
             }
         }
-    // and the accumulation form where there is a choice (FP32 buffers in LDS, 8 or 16 waves)
-    int ba = 0;
-    if (bw >= 8 && bb == 1 && c->p.precision == TR_FP32C)
+    // and the accumulation form where there is a choice (FP32 buffers in LDS, 4, 8 or 16 waves)
+    if (bw >= 4 && bb == 1 && c->p.precision == TR_FP32C)
         for (int am : {1, 2}) {
             double ms;
             if (timed(bw, bb, bi, ms, am) && ms < best) {
