@@ -233,7 +233,7 @@ const char *tr_last_error(const tr_ctx *c);
  *  - dom_offsets: host array of n_domains + 1 strictly increasing entries,
  *    dom_offsets[0] = 0 (every domain non-empty).
  *  - n_domains: 1 .. 64 (TR_EINVAL beyond: the library's static scratch holds
- *    the radix-select state of 64 domains, about 67 KB per device, kept
+ *    the radix-select state of 64 domains, about 0.5 MB per device, kept
  *    until the process ends).
  *  - delta_dev: device array of n_domains doubles (caller-owned), written
  *    asynchronously on hip_stream (NULL: the default stream).

@@ -472,12 +472,13 @@ __device__ inline void buf_add(Real *p, Real v)
     }
 }
 
-// Three adds at once (A, E, V of one ray point): in the compare-and-swap form
-// the three reads and then the three swaps are in flight together.  Lanes that
-// meet on a point meet on all three rows and lose there to the same lane, so
-// the three are repeated together; one that is through adds zero.
+// Three adds at once (A, E, V of one ray point): wk x0, wk x1, wk x2.  In the
+// compare-and-swap form the three reads and then the three swaps are in flight
+// together, each sum rounded once.  Lanes that meet on a point meet on all
+// three rows and lose there to the same lane, so the three are repeated
+// together; one that is through adds zero.
 template <typename Real, int AM>
-__device__ inline void buf_add3(Real *p0, Real v0, Real *p1, Real v1, Real *p2, Real v2)
+__device__ inline void buf_add3(Real wk, Real *p0, Real x0, Real *p1, Real x1, Real *p2, Real x2)
 {
     if constexpr (AM == 2 && sizeof(Real) == 4) {
         unsigned *q0 = (unsigned *)p0, *q1 = (unsigned *)p1, *q2 = (unsigned *)p2;
@@ -485,23 +486,23 @@ __device__ inline void buf_add3(Real *p0, Real v0, Real *p1, Real v1, Real *p2, 
         unsigned o1 = __hip_atomic_load(q1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         unsigned o2 = __hip_atomic_load(q2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         for (;;) {
-            const unsigned r0 = lds_swap(q0, o0, __float_as_uint(__uint_as_float(o0) + v0));
-            const unsigned r1 = lds_swap(q1, o1, __float_as_uint(__uint_as_float(o1) + v1));
-            const unsigned r2 = lds_swap(q2, o2, __float_as_uint(__uint_as_float(o2) + v2));
+            const unsigned n0 = __float_as_uint(fmaf(wk, x0, __uint_as_float(o0)));
+            const unsigned n1 = __float_as_uint(fmaf(wk, x1, __uint_as_float(o1)));
+            const unsigned n2 = __float_as_uint(fmaf(wk, x2, __uint_as_float(o2)));
+            const unsigned r0 = lds_swap(q0, o0, n0), r1 = lds_swap(q1, o1, n1), r2 = lds_swap(q2, o2, n2);
             const bool d0 = r0 == o0, d1 = r1 == o1, d2 = r2 == o2;
             if (d0 && d1 && d2) break;
-            // (a row that is through holds o + v now)
-            o0 = d0 ? __float_as_uint(__uint_as_float(o0) + v0) : r0;
-            o1 = d1 ? __float_as_uint(__uint_as_float(o1) + v1) : r1;
-            o2 = d2 ? __float_as_uint(__uint_as_float(o2) + v2) : r2;
-            v0 = d0 ? 0.0f : v0;
-            v1 = d1 ? 0.0f : v1;
-            v2 = d2 ? 0.0f : v2;
+            o0 = d0 ? n0 : r0;   // (a row that is through holds its sum now)
+            o1 = d1 ? n1 : r1;
+            o2 = d2 ? n2 : r2;
+            x0 = d0 ? 0.0f : x0;
+            x1 = d1 ? 0.0f : x1;
+            x2 = d2 ? 0.0f : x2;
         }
     } else {
-        buf_add<Real, AM>(p0, v0);
-        buf_add<Real, AM>(p1, v1);
-        buf_add<Real, AM>(p2, v2);
+        buf_add<Real, AM>(p0, wk * x0);
+        buf_add<Real, AM>(p1, wk * x1);
+        buf_add<Real, AM>(p2, wk * x2);
     }
 }
 
@@ -1560,7 +1561,7 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, const unsi
         for (int io = 0; io < npt; ++io, ++row, fi += (Real)1) {
             const Real ws = here(smooth_kernel<Real>(mg, (rcoef * (fi * fi) - jd) * jhinv) * jwf);
             const Real w = jwf > (Real)0 ? ws : (io == 0 ? jfb : (Real)1 - jfb);
-            buf_add3<Real, ATOMIC>(row, wk * (w * ja), row + nrm, wk * (w * je), row + 2 * nrm, wk * (w * jv));
+            buf_add3<Real, ATOMIC>(wk, row, w * ja, row + nrm, w * je, row + 2 * nrm, w * jv);
             if (KV && jemode != 0) {   // the emission row
                 const Real wq = emission_weight<Real>(jemode, jlo + io, io, jle, jne, jea, jeb, jfb, rcoef, jd, jhinv,
                                                       a.eps_kernel == K_G) * jqeps;
@@ -2300,11 +2301,6 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_cas_fallback(SweepArgs 
 }
 
 // ---------------------------------------------------------------------------
-// a9. delta_cell per domain.  The median is the lower median of the domain's
-// previous flux, found exactly by an 8-pass radix select over the IEEE bit
-// patterns (non-negative doubles order like their bits).
-// ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
 // Angular-weight table (Sec. 2.3 "Mapping nodes onto rays").  A node's
 // angular weights depend only on its box relative to the target; for nodes of
 // 1, 2, 4, ... times the target's size they are tabulated once per context by
@@ -2362,135 +2358,190 @@ __global__ __launch_bounds__(256) void k_atab(AtabGeom G, int ns, int s, float g
     if (!idx && lane == 0) sums[wave] = at;
 }
 
-// The domain of a cell: from the per-cell array of a context, or from the
-// cell ranges of at most kStaticDomains domains (the entry point without a
-// context), found by bisection.
+// ---------------------------------------------------------------------------
+// a9. delta_cell per domain.  The median is the lower median of the domain's
+// previous flux, found exactly by a radix select over the IEEE bit patterns
+// (non-negative doubles order like their bits), 11 bits at a time: a pass
+// reads every cell once, so the six passes and the final one are bound by
+// memory (8M cells: 64 MB a pass, which stay in the last-level cache).  A
+// block takes a contiguous run of cells, so it looks a domain up once and not
+// for every cell, and counts in LDS, in four copies of the histogram (the top
+// bits of neighbouring values are mostly equal, and lanes that meet on a bin
+// are served one by one); the last block to finish picks every domain's bin.
+// 8M cells of 7 domains: 1316 us with 8 bits a pass, a lookup per cell and a
+// launch for every pick; see the table of measurements for the present time.
+// ---------------------------------------------------------------------------
+constexpr int kSelBits = 11, kSelBins = 1 << kSelBits, kSelPasses = 6, kSelCopies = 4, kSelThreads = 512;
+__host__ __device__ inline int select_shift(int pass) { return pass < 5 ? 64 - kSelBits * (pass + 1) : 0; }
+
+// Cell ranges of the domains: from a context's records, or (the entry point
+// without a context) at most kStaticDomains of them by value.
 constexpr int kStaticDomains = 64;
 struct DomByArray {
-    const int32_t *cell_dom;
-    __device__ int operator()(int64_t c) const { return cell_dom[c]; }
+    const DomDev *doms;
+    int32_t n;
+    __device__ int64_t begin(int d) const { return doms[d].cell_off; }
 };
 struct DomByRanges {
     int32_t n;
     int64_t off[kStaticDomains + 1];   // domain d holds cells [off[d], off[d+1])
-    __device__ int operator()(int64_t c) const
-    {
-        int lo = 0, hi = n - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (off[mid] <= c) lo = mid;
-            else hi = mid - 1;
-        }
-        return lo;
+    __device__ int64_t begin(int d) const { return off[d]; }
+};
+template <typename Doms>
+__device__ inline int domain_of(const Doms &D, int64_t c)
+{
+    int lo = 0, hi = D.n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (D.begin(mid) <= c) lo = mid;
+        else hi = mid - 1;
     }
+    return lo;
+}
+
+// The radix select's state: per domain a histogram, the median's bit prefix,
+// the rank still to skip and (for delta_cell) the running maximum; the number
+// of blocks done with the pass.
+struct SelectState {
+    unsigned *hist;
+    unsigned long long *prefix, *rank, *dmax;
+    unsigned *done;
 };
 
-template <typename DomOf>
-__global__ void k_hist(int64_t n_cells, const double *__restrict__ f, DomOf dom_of,
-                       const unsigned long long *__restrict__ prefix, int shift, unsigned int *__restrict__ hist)
+template <typename Doms>
+__global__ void k_select_init(Doms D, int64_t n_cells, SelectState st)
 {
-    __shared__ unsigned int h[256];
-    const int64_t b0 = (int64_t)blockIdx.x * blockDim.x;
-    const int64_t c = b0 + threadIdx.x;
-    const int64_t last = (b0 + blockDim.x - 1 < n_cells ? b0 + blockDim.x - 1 : n_cells - 1);
-    const int dom0 = dom_of(b0), dom1 = dom_of(last);
-    const bool one = dom0 == dom1;   // whole block in one domain: count in LDS first
-    for (int i = threadIdx.x; i < 256; i += blockDim.x) h[i] = 0;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < D.n * kSelBins) st.hist[i] = 0;
+    if (i == 0) *st.done = 0;
+    if (i < D.n) {
+        const int64_t n = (i + 1 < D.n ? D.begin(i + 1) : n_cells) - D.begin(i);
+        st.rank[i] = (unsigned long long)((n - 1) / 2);   // lower median
+        st.prefix[i] = 0ull;
+        st.dmax[i] = 0ull;
+    }
+}
+
+// A block's run of cells: [lo, hi)
+__device__ inline void block_run(int64_t n_cells, int64_t &lo, int64_t &hi)
+{
+    int64_t per = (n_cells + gridDim.x - 1) / gridDim.x;
+    per = (per + 63) / 64 * 64;
+    lo = (int64_t)blockIdx.x * per;
+    hi = lo + per < n_cells ? lo + per : n_cells;
+}
+
+template <typename Doms>
+__global__ __launch_bounds__(kSelThreads) void k_select(Doms D, int64_t n_cells, const double *__restrict__ f, int pass,
+                                                        SelectState st)
+{
+    __shared__ unsigned h[kSelCopies * kSelBins];
+    __shared__ int is_last;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int shift = select_shift(pass), bits = pass < 5 ? kSelBits : 64 - 5 * kSelBits;
+    const unsigned digit_mask = (1u << bits) - 1u;
+    const unsigned long long above = pass == 0 ? 0ull : ~0ull << (shift + bits);
+    for (int i = tid; i < kSelCopies * kSelBins; i += kSelThreads) h[i] = 0;
     __syncthreads();
-    if (c < n_cells) {
-        const int dom = dom_of(c);
-        const unsigned long long key = (unsigned long long)__double_as_longlong(f[c]);
-        const unsigned long long mask = (shift >= 56) ? 0ull : (~0ull << (shift + 8));
-        if ((key & mask) == prefix[dom]) {
-            const unsigned int digit = (unsigned int)((key >> shift) & 255ull);
-            if (one) atomicAdd(&h[digit], 1u);
-            else atomicAdd(&hist[dom * 256 + digit], 1u);
+    int64_t lo, hi;
+    block_run(n_cells, lo, hi);
+    unsigned *const mine = h + (lane & (kSelCopies - 1));   // copies interleaved: a bin's four counts in four banks
+    for (int d = lo < hi ? domain_of(D, lo) : 0; lo < hi; ++d) {
+        const int64_t de = d + 1 < D.n ? D.begin(d + 1) : n_cells;
+        const int64_t end = de < hi ? de : hi;
+        const unsigned long long prefix = st.prefix[d];
+        auto count = [&](double v) {
+            const unsigned long long key = (unsigned long long)__double_as_longlong(v);
+            if ((key & above) == prefix) atomicAdd(&mine[kSelCopies * ((unsigned)(key >> shift) & digit_mask)], 1u);
+        };
+        int64_t c = lo + tid;
+        for (; c + 3 * kSelThreads < end; c += 4 * kSelThreads) {
+            const double v0 = f[c], v1 = f[c + kSelThreads], v2 = f[c + 2 * kSelThreads], v3 = f[c + 3 * kSelThreads];
+            count(v0);
+            count(v1);
+            count(v2);
+            count(v3);
         }
+        for (; c < end; c += kSelThreads) count(f[c]);
+        __syncthreads();
+        for (int i = tid; i < kSelBins; i += kSelThreads) {
+            unsigned v = 0;
+            for (int q = 0; q < kSelCopies; ++q) {
+                v += h[kSelCopies * i + q];
+                h[kSelCopies * i + q] = 0;
+            }
+            if (v) atomicAdd(&st.hist[d * kSelBins + i], v);
+        }
+        __syncthreads();
+        lo = end;
     }
+    // the last block to get here picks the bins (its counts are all in: every
+    // block's are before its own increment)
+    __threadfence();
     __syncthreads();
-    if (one)
-        for (int i = threadIdx.x; i < 256; i += blockDim.x)
-            if (h[i]) atomicAdd(&hist[dom0 * 256 + i], h[i]);
-}
-
-__global__ void k_select(int n_dom, int shift, unsigned int *hist, unsigned long long *prefix,
-                         unsigned long long *rank)
-{
-    const int dom = blockIdx.x * blockDim.x + threadIdx.x;
-    if (dom >= n_dom) return;
-    unsigned long long k = rank[dom];
-    unsigned long long cum = 0;
-    int b = 0;
-    for (; b < 256; ++b) {
-        const unsigned int h = hist[dom * 256 + b];
-        if (cum + h > k) break;
-        cum += h;
-    }
-    if (b > 255) b = 255;
-    rank[dom] = k - cum;
-    prefix[dom] |= ((unsigned long long)b) << shift;
-    for (int q = 0; q < 256; ++q) hist[dom * 256 + q] = 0;
-}
-
-__global__ void k_rank_init(int n_dom, const DomDev *__restrict__ doms, unsigned long long *rank,
-                            unsigned long long *prefix, unsigned long long *dmax)
-{
-    const int d = blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= n_dom) return;
-    rank[d] = (unsigned long long)((doms[d].n_cells - 1) / 2);   // lower median
-    prefix[d] = 0ull;
-    dmax[d] = 0ull;
-}
-
-__global__ void k_rank_init_ranges(DomByRanges R, unsigned long long *rank, unsigned long long *prefix,
-                                   unsigned long long *dmax)
-{
-    const int d = blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= R.n) return;
-    rank[d] = (unsigned long long)((R.off[d + 1] - R.off[d] - 1) / 2);   // lower median
-    prefix[d] = 0ull;
-    dmax[d] = 0ull;
-}
-
-template <typename DomOf>
-__global__ void k_delta(int64_t n_cells, const double *__restrict__ fn, const double *__restrict__ fo,
-                        DomOf dom_of, const unsigned long long *__restrict__ med,
-                        unsigned long long *__restrict__ dmax)
-{
-    __shared__ unsigned long long wmax[16];
-    const int64_t b0 = (int64_t)blockIdx.x * blockDim.x;
-    const int64_t c = b0 + threadIdx.x;
-    const int64_t last = (b0 + blockDim.x - 1 < n_cells ? b0 + blockDim.x - 1 : n_cells - 1);
-    const int dom0 = dom_of(b0);
-    const bool one = dom0 == dom_of(last);
-    unsigned long long key = 0;   // bits of a non-negative double order like the value
-    int dom = dom0;
-    if (c < n_cells) {
-        dom = dom_of(c);
-        const double m = __longlong_as_double((long long)med[dom]);
-        const double old = fo[c];
-        const double norm = old > m ? old : m;
-        const double diff = fabs(fn[c] - old);
-        double dl;
-        if (norm > 0.0) dl = diff / norm;
-        else dl = diff > 0.0 ? INFINITY : 0.0;
-        if (!(dl == dl)) dl = INFINITY;
-        key = (unsigned long long)__double_as_longlong(dl);
-    }
-    if (!one) {
-        if (c < n_cells) atomicMax(&dmax[dom], key);
-        return;
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long y = __shfl_xor(key, o, 64);
-        key = y > key ? y : key;
-    }
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = key;
+    if (tid == 0) is_last = atomicAdd(st.done, 1u) == gridDim.x - 1;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long mx = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) mx = wmax[w] > mx ? wmax[w] : mx;
-        atomicMax(&dmax[dom0], mx);
+    if (!is_last) return;
+    __threadfence();
+    // a wave per domain, 32 bins a lane
+    constexpr int kPer = kSelBins / 64;
+    for (int d = tid >> 6; d < D.n; d += kSelThreads / 64) {
+        unsigned *const hd = st.hist + (size_t)d * kSelBins + lane * kPer;
+        unsigned v[kPer], sum = 0;
+        for (int q = 0; q < kPer; ++q) {
+            v[q] = __hip_atomic_load(&hd[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sum += v[q];
+        }
+        int tot = 0;
+        const unsigned long long k = st.rank[d];
+        unsigned long long cum = (unsigned)wave_excl_scan_dpp((int)sum, tot);   // (a domain has fewer than 2^31 cells)
+        if (k >= cum && k < cum + sum) {   // one lane
+            int q = 0;
+            while (cum + v[q] <= k) cum += v[q++];
+            st.rank[d] = k - cum;
+            st.prefix[d] |= (unsigned long long)(lane * kPer + q) << shift;
+        }
+        for (int q = 0; q < kPer; ++q) hd[q] = 0;
+    }
+    if (tid == 0) *st.done = 0;
+}
+
+template <typename Doms>
+__global__ __launch_bounds__(kSelThreads) void k_delta(Doms D, int64_t n_cells, const double *__restrict__ fn,
+                                                       const double *__restrict__ fo, SelectState st)
+{
+    __shared__ unsigned long long wmax[kSelThreads / 64];
+    const int tid = threadIdx.x;
+    int64_t lo, hi;
+    block_run(n_cells, lo, hi);
+    for (int d = lo < hi ? domain_of(D, lo) : 0; lo < hi; ++d) {
+        const int64_t de = d + 1 < D.n ? D.begin(d + 1) : n_cells;
+        const int64_t end = de < hi ? de : hi;
+        const double m = __longlong_as_double((long long)st.prefix[d]);
+        unsigned long long mx = 0;   // bits of a non-negative double order like the value
+        for (int64_t c = lo + tid; c < end; c += kSelThreads) {
+            const double old = fo[c];
+            const double norm = old > m ? old : m;
+            const double diff = fabs(fn[c] - old);
+            double dl;
+            if (norm > 0.0) dl = diff / norm;
+            else dl = diff > 0.0 ? INFINITY : 0.0;
+            if (!(dl == dl)) dl = INFINITY;
+            const unsigned long long key = (unsigned long long)__double_as_longlong(dl);
+            mx = key > mx ? key : mx;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            const unsigned long long y = __shfl_xor(mx, o, 64);
+            mx = y > mx ? y : mx;
+        }
+        if ((tid & 63) == 0) wmax[tid >> 6] = mx;
+        __syncthreads();
+        if (tid == 0) {
+            for (int w = 1; w < kSelThreads / 64; ++w) mx = wmax[w] > mx ? wmax[w] : mx;
+            atomicMax(&st.dmax[d], mx);
+        }
+        __syncthreads();
+        lo = end;
     }
 }
 
@@ -2502,10 +2553,10 @@ __global__ void k_store_delta(int n_dom, const unsigned long long *__restrict__ 
 }
 
 // Scratch of the entry point without allocation (tr_delta_noalloc): per
-// domain a 256-bin histogram, the median's bit prefix, the rank still to
-// skip and the running maximum.  One copy per device, held until the
+// domain a histogram, the median's bit prefix, the rank still to skip and
+// the running maximum.  One copy per device, held until the
 // process ends; every call on a device shares it.
-constexpr size_t kStaticScratchWords = (size_t)kStaticDomains * 128 + 3 * kStaticDomains;
+constexpr size_t kStaticScratchWords = (size_t)kStaticDomains * (kSelBins / 2) + 3 * kStaticDomains + 1;
 static __device__ __align__(256) unsigned long long scratch[kStaticScratchWords];
 
 }  // namespace tr
@@ -2567,7 +2618,7 @@ struct tr_ctx {
     AtabGeom atab{};
     // delta scratch
     unsigned int *hist = nullptr;
-    unsigned long long *dprefix = nullptr, *drank = nullptr, *dmax = nullptr;
+    unsigned long long *dprefix = nullptr, *drank = nullptr, *dmax = nullptr;   // (drank: a word more, the blocks done)
     double *solve_tmp = nullptr;
     int64_t solve_tmp_n = 0;
     // state
@@ -3396,9 +3447,9 @@ tr_status tr_set_domains(tr_ctx *c, int32_t n_domains, const tr_domain *doms)
     if ((s = dalloc(c, &c->packA, 32 * (size_t)g))) return s;
     if ((s = dalloc(c, &c->packB, 32 * (size_t)g))) return s;
     if ((s = dalloc(c, (void **)&c->ndot, sizeof(double) * (size_t)ncell))) return s;
-    if ((s = dalloc(c, (void **)&c->hist, sizeof(unsigned int) * 256 * (size_t)n_domains))) return s;
+    if ((s = dalloc(c, (void **)&c->hist, sizeof(unsigned int) * kSelBins * (size_t)n_domains))) return s;
     if ((s = dalloc(c, (void **)&c->dprefix, sizeof(unsigned long long) * n_domains))) return s;
-    if ((s = dalloc(c, (void **)&c->drank, sizeof(unsigned long long) * n_domains))) return s;
+    if ((s = dalloc(c, (void **)&c->drank, sizeof(unsigned long long) * (n_domains + 1)))) return s;
     if ((s = dalloc(c, (void **)&c->dmax, sizeof(unsigned long long) * n_domains))) return s;
     c->sxyz.assign(n_domains, {});
     c->sq.assign(n_domains, {});
@@ -3479,24 +3530,22 @@ tr_status enqueue_build(tr_ctx *c, const double *n_h, const double *f_prev, int3
     return TR_OK;
 }
 
-// Enqueues delta_cell per domain into c->dmax (capturable).
+// Enqueues delta_cell per domain into st.dmax (capturable, no errors checked).
+template <typename Doms>
+void launch_delta(const Doms &D, int64_t n_cells, const double *f_new, const double *f_old, const SelectState &st, int n_cu,
+                  hipStream_t stream)
+{
+    const unsigned blocks = (unsigned)std::min<int64_t>((n_cells + 4 * kSelThreads - 1) / (4 * kSelThreads), 4 * (int64_t)n_cu);
+    hipLaunchKernelGGL(k_select_init<Doms>, dim3(grid1((int64_t)D.n * kSelBins)), dim3(256), 0, stream, D, n_cells, st);
+    for (int pass = 0; pass < kSelPasses; ++pass)
+        hipLaunchKernelGGL(k_select<Doms>, dim3(blocks), dim3(kSelThreads), 0, stream, D, n_cells, f_old, pass, st);
+    hipLaunchKernelGGL(k_delta<Doms>, dim3(blocks), dim3(kSelThreads), 0, stream, D, n_cells, f_new, f_old, st);
+}
+
 tr_status enqueue_delta(tr_ctx *c, const double *f_new, const double *f_old)
 {
-    const int nd = c->n_dom;
-    const int64_t ncell = c->n_cells;
-    hipLaunchKernelGGL(k_rank_init, dim3(grid1(nd, 64)), dim3(64), 0, c->stream, nd, c->doms, c->drank, c->dprefix,
-                       c->dmax);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid1(256 * nd)), dim3(256), 0, c->stream, (int32_t *)c->hist,
-                       (int64_t)256 * nd, 0);
-    const DomByArray by{c->cell_dom};
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(k_hist<DomByArray>, dim3(grid1(ncell)), dim3(256), 0, c->stream, ncell, f_old, by,
-                           c->dprefix, shift, c->hist);
-        hipLaunchKernelGGL(k_select, dim3(grid1(nd, 64)), dim3(64), 0, c->stream, nd, shift, c->hist, c->dprefix,
-                           c->drank);
-    }
-    hipLaunchKernelGGL(k_delta<DomByArray>, dim3(grid1(ncell)), dim3(256), 0, c->stream, ncell, f_new, f_old, by,
-                       c->dprefix, c->dmax);
+    const SelectState st{c->hist, c->dprefix, c->drank, c->dmax, (unsigned *)(c->drank + c->n_dom)};
+    launch_delta(DomByArray{c->doms, c->n_dom}, c->n_cells, f_new, f_old, st, c->n_cu, c->stream);
     HIPCHK(hipGetLastError());
     return TR_OK;
 }
@@ -3838,22 +3887,18 @@ tr_status tr_delta_noalloc(const double *f_new, const double *f_old, const int64
     void *sp = nullptr;
     const hipError_t e = static_scratch(dev, &sp);
     if (e != hipSuccess) return fail_free(TR_EHIP, std::string("hipGetSymbolAddress: ") + hipGetErrorString(e));
-    unsigned int *hist = (unsigned int *)sp;
-    unsigned long long *prefix = (unsigned long long *)sp + (size_t)kStaticDomains * 128;
+    unsigned *hist = (unsigned *)sp;
+    unsigned long long *prefix = (unsigned long long *)sp + (size_t)kStaticDomains * (kSelBins / 2);
     unsigned long long *rank = prefix + kStaticDomains, *dmax = rank + kStaticDomains;
+    const SelectState sel{hist, prefix, rank, dmax, (unsigned *)(dmax + kStaticDomains)};
     hipStream_t st = (hipStream_t)stream;
     const int nd = n_domains;
+    int n_cu = 0;
+    if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return fail_free(TR_EHIP, "hipDeviceGetAttribute failed");
     (void)hipGetLastError();
     // the last call's contents stay in the scratch: everything read is set here first
-    hipLaunchKernelGGL(k_rank_init_ranges, dim3(1), dim3(64), 0, st, R, rank, prefix, dmax);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid1(256 * nd)), dim3(256), 0, st, (int32_t *)hist, (int64_t)256 * nd, 0);
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(k_hist<DomByRanges>, dim3(grid1(ncell)), dim3(256), 0, st, ncell, f_old, R, prefix, shift,
-                           hist);
-        hipLaunchKernelGGL(k_select, dim3(1), dim3(64), 0, st, nd, shift, hist, prefix, rank);
-    }
-    hipLaunchKernelGGL(k_delta<DomByRanges>, dim3(grid1(ncell)), dim3(256), 0, st, ncell, f_new, f_old, R, prefix,
-                       dmax);
+    launch_delta(R, ncell, f_new, f_old, sel, n_cu, st);
     hipLaunchKernelGGL(k_store_delta, dim3(1), dim3(64), 0, st, nd, dmax, delta_dev);
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return fail_free(TR_EHIP, std::string("launch failed: ") + hipGetErrorString(le));
