@@ -1179,7 +1179,7 @@ struct Lattice {
     uint64_t mask;
     __device__ Lattice(int s_) : s(s_)
     {
-        const int lane = here(lane_id());   // (not held in registers between nodes)
+        const int lane = lane_id();
         ia = lane / (s * s);
         ib = (lane / s) % s;
         ic = lane % s;
@@ -1425,18 +1425,18 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, const unsi
         int h0 = (int)fsqrt(rh * rc_inv) + 1;
         h0 = h0 > nr - 1 ? nr - 1 : h0;
         Real sum = 0;
-        int first = h0 + 1, npos = 0;   // the points with a weight (contiguous: the kernel is positive inside its support)
-        for (int i = l0; i <= h0; ++i) {
-            const Real v = smooth_kernel<Real>(mg, (rcoef * (Real)(i * i) - d) * hinv);
+        int end = 0, npos = 0;   // the points with a weight (contiguous: the kernel is positive inside its support)
+        Real fi = (Real)l0;
+        for (int i = l0; i <= h0; ++i, fi += (Real)1) {
+            const Real v = smooth_kernel<Real>(mg, (rcoef * (fi * fi) - d) * hinv);
             sum += v;
-            if (v > (Real)0) {
-                first = i < first ? i : first;
-                ++npos;
-            }
+            const bool pos = v > (Real)0;
+            end = pos ? i : end;
+            npos += pos ? 1 : 0;
         }
         if (sum > (Real)0) {
             wscale = frcp(sum);
-            lo = KV ? l0 : first;   // (an emission variant may use a point that rounding leaves outside)
+            lo = KV ? l0 : end - npos + 1;   // (an emission variant may use a point that rounding leaves outside)
             nsup = KV ? h0 - l0 + 1 : npos;
         } else if (d >= rt[nr - 1]) {   // no point in the support: linear split over the bracket
             lo = nr - 1;
@@ -1643,6 +1643,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (blockIdx.x == 0 && threadIdx.x == 0) a.queue[0] = 0;   // the sweep of this chunk starts from its first target
     const uint64_t below = (1ull << lane) - 1ull;
+    const Lattice L(a.subsample);
     uint64_t n_test = 0, n_acc = 0, n_tab = 0, n_guard = 0;
     int dpos = 0, dend = 0;   // the wave's part of the pool of pairs, in units
     for (int i = (int)blockIdx.x * kWalkWaves + wave; i < a.n_chunk; i += (int)gridDim.x * kWalkWaves) {
@@ -1713,7 +1714,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
                     const int4 jg{rdlane(g.x, j), rdlane(g.y, j), rdlane(g.z, j), rdlane(g.w, j)};
                     const int jsh[3] = {rdlane(sh[0], j), rdlane(sh[1], j), rdlane(sh[2], j)};
                     int kc = 0;
-                    const int nd = classify_box(Lattice(a.subsample), a.nside, a.npix, a.guard_tol,
+                    const int nd = classify_box(L, a.nside, a.npix, a.guard_tol,
                                                 node_box(a, rdlane(n, j), jg, jsh, r.tx, r.ty, r.tz), r.tx, r.ty, r.tz,
                                                 &a.queue[1], n_guard, kc);
                     const int need = (nd + 3) >> 2;
