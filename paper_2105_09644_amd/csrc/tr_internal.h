@@ -12,7 +12,8 @@ namespace tr {
 
 constexpr int kBlock = 8;          // cells per block edge
 constexpr int kMaxRadial = 128;    // evaluation points per ray (two 64-bit masks)
-constexpr int kAtabRatios = 5;    // angular-weight table: nodes of 1, 2, 4, 8 and 16 target sizes
+constexpr int kAtabRatios = 6;    // angular-weight table: nodes of 1, 2, 4, ... 32 target sizes
+constexpr int kAtabShell = 4;     // from 16 on only where the walk accepts them
 constexpr unsigned kNoEntry = ~0u, kDynEntry = 1u << 31;   // no pairs; pairs in the chunk's pool
 constexpr int kDynBlock = 256;    // units of 4 pairs a walking wave takes from that pool at a time
 constexpr int kMaxLevels = 24;

@@ -2309,12 +2309,18 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_cas_fallback(SweepArgs 
 // uses: relative sub-point positions scale exactly with the size, so a table
 // entry holds exactly what the sweep would compute for that node.  A wave
 // takes a contiguous run of offsets: first (idx NULL) it counts their pairs (in
-// units of 4), then, with the runs' first units known, it writes them.  A wave per offset
-// classifies in FP32 with the FP64 guard band: 1.2 ms for 4.8 million offsets
-// where a thread per offset in FP64 took 1 ms for 0.6 million.
+// units of 4), then, with the runs' first units known, it writes them.  A wave
+// per offset classifies in FP32 with the FP64 guard band: 1.2 ms for 4.8
+// million offsets where a thread per offset in FP64 took 1 ms for 0.6 million.
+// For the larger nodes only the offsets where the walk accepts one are filled:
+// not so near that it opens them, nor so far that it has accepted their parent.
+// A larger leaf cell may be nearer, or the parent's angle smaller; such nodes
+// are classified by the walk.
 // ---------------------------------------------------------------------------
 struct AtabGeom {
     int32_t w[kAtabRatios], base[kAtabRatios], nkeys;
+    double near2, far2;   // from kAtabShell on: squared distances of the centre, in node sizes, inside which the
+                          // walk opens a node and beyond which it has accepted its parent
 };
 
 __global__ __launch_bounds__(256) void k_atab(AtabGeom G, int ns, int s, float guard_tol, int run, int64_t *__restrict__ sums,
@@ -2322,39 +2328,53 @@ __global__ __launch_bounds__(256) void k_atab(AtabGeom G, int ns, int s, float g
 {
     const int wave = uniform((int)(blockIdx.x * 4 + (threadIdx.x >> 6))), lane = lane_id();
     const Lattice L(s);
+    const float inv_s = 1.0f / (float)s;
     int64_t at = idx ? sums[wave] : 0;
     uint64_t guard = 0;
-    for (int key = wave * run; key < min((wave + 1) * run, G.nkeys); ++key) {
-        int ri = 0;
+    const int end = min((wave + 1) * run, G.nkeys);
+    for (int k0 = wave * run; k0 < end; k0 += 64) {
+        // 64 offsets, one a lane
+        const int key = k0 + lane;
+        int ri = 0, w = G.w[0], k = key - G.base[0];
 #pragma unroll
         for (int q = 1; q < kAtabRatios; ++q)
-            if (G.w[q] >= 0 && key >= G.base[q]) ri = q;
-        int w = G.w[0], k = key - G.base[0];
-#pragma unroll
-        for (int q = 1; q < kAtabRatios; ++q)
-            if (ri == q) {
+            if (G.w[q] >= 0 && key >= G.base[q]) {
+                ri = q;
                 w = G.w[q];
                 k = key - G.base[q];
             }
         const int n = 2 * w + 1;
-        Box box;
-        box.b[2] = k % n - w;
-        k /= n;
-        box.b[1] = k % n - w;
-        box.b[0] = k / n - w;
-        for (int q = 0; q < 3; ++q) {
-            box.e[q] = 1 << ri;
-            // a unit target with its lower corner at the origin: twice its centre is (1, 1, 1)
-            box.o[q] = 0.5f * (float)(2 * box.b[q] - 1);
-            box.step[q] = (float)(1 << ri) * (1.0f / (float)s);
+        const int oz = k % n - w, oy = (k / n) % n - w, ox = k / (n * n) - w;
+        bool want = key < end;
+        if (want && ri >= kAtabShell) {
+            // twice the centre's offset from the target's, in target sizes
+            const double cx = 2 * ox + (1 << ri) - 1, cy = 2 * oy + (1 << ri) - 1, cz = 2 * oz + (1 << ri) - 1;
+            const double d2 = (cx * cx + cy * cy + cz * cz) / (double)(4 << (2 * ri));
+            want = d2 >= G.near2 && d2 <= G.far2;
         }
-        int kc = 0;
-        const int nd = classify_box(L, ns, 12 * ns * ns, guard_tol, box, 1, 1, 1, flag, guard, kc);
-        if (idx) {
-            if (lane < nd) pool[at * 4 + lane] = kc;
-            if (lane == 0) idx[key] = (int32_t)(((unsigned)at << 6) | (unsigned)(nd - 1));
+        unsigned entry = kNoEntry;
+        for (uint64_t todo = __ballot(want); todo; todo &= todo - 1) {
+            const int j = __ffsll((unsigned long long)todo) - 1;
+            const int jr = rdlane(ri, j);
+            Box box;
+            box.b[0] = rdlane(ox, j);
+            box.b[1] = rdlane(oy, j);
+            box.b[2] = rdlane(oz, j);
+            for (int q = 0; q < 3; ++q) {
+                box.e[q] = 1 << jr;
+                // a unit target with its lower corner at the origin: twice its centre is (1, 1, 1)
+                box.o[q] = 0.5f * (float)(2 * box.b[q] - 1);
+                box.step[q] = (float)(1 << jr) * inv_s;
+            }
+            int kc = 0;
+            const int nd = classify_box(L, ns, 12 * ns * ns, guard_tol, box, 1, 1, 1, flag, guard, kc);
+            if (idx) {
+                if (lane < nd) pool[at * 4 + lane] = kc;
+                if (lane == j) entry = (unsigned)at << 6 | (unsigned)(nd - 1);
+            }
+            at += (nd + 3) >> 2;
         }
-        at += (nd + 3) >> 2;
+        if (idx && key < end) idx[key] = (int32_t)entry;
     }
     if (!idx && lane == 0) sums[wave] = at;
 }
@@ -3151,15 +3171,16 @@ tr_status upload_gauss_legendre(tr_ctx *c)
 float guard_tolerance(int nside) { return 1e-5f * std::max(2.0f, (float)nside); }
 
 // The angular-weight table of the context's N_side and s: for nodes of r = 1,
-// 2, 4, 8, 16 target sizes the offsets up to (2/theta + 1) r target sizes per
+// 2, 4, ... 32 target sizes the offsets up to (2/theta + 1) r target sizes per
 // axis (every node accepted at the smallest opening angle lies inside); nodes
-// outside classify their sub-points.  Classifying a node in the sweep takes
-// about 150 vector instructions of a wave more than reading its entry, and
-// building an entry twice that: a ratio gets at most 32 entries per cell
-// (a target accepts about 50 nodes of each of the middle ratios), so that the
-// table has paid for itself within about two sweeps, at least 65536 and at
-// most 4.5 million (theta 0.5 needs 4.2 million at r = 16; the next would
-// need 33 million, half a GB, for 4% of the nodes).
+// outside are classified by the walk.  Classifying a node takes about 180
+// vector instructions of a wave more than reading its entry, and building an
+// entry twice that: a ratio gets at most 32 entries per cell (a target accepts
+// about 50 nodes of each of the middle ratios), so that the table has paid for
+// itself within about two sweeps, at least 65536 and at most 16 million (theta
+// 0.5 needs 1.8 million at r = 16 and 14.7 million at r = 32, 0.4 to 0.6 GB,
+// which takes the walks of 128^3 from 55 to 33 ms, built in 5 ms; r = 64 would take 8 times
+// that for under 1% of the nodes).
 tr_status build_angular_table(tr_ctx *c)
 {
     const int s = c->p.subsample, ns = c->p.nside;
@@ -3167,18 +3188,28 @@ tr_status build_angular_table(tr_ctx *c)
     if (c->p.theta_if > 0.0) th = std::min(th, c->p.theta_if);
     if (c->p.theta_src > 0.0) th = std::min(th, c->p.theta_src);
     th = std::max(th, 0.05);
-    const double most = std::min(4.5e6, std::max(65536.0, 32.0 * (double)c->n_cells));
+    const double most = std::min(1.6e7, std::max(65536.0, 32.0 * (double)c->n_cells));
     int root = 1;   // nodes as large as the root are never accepted
     for (auto &t : c->topo) root = std::max(root, t.root_size);
+    // accepted: size < theta d; its parent was not: its centre within 2 size / th, and the node's
+    // within half the parent's diagonal of that (both with a margin)
+    const double near = 0.999 / std::max(c->p.theta, 0.05), far = 1.001 * (2.0 / th + 0.8660254037844386);
+    const double shell = 4.0 / 3.0 * kPi * (far * far * far - near * near * near);   // in node volumes
     for (int ratios = kAtabRatios; ratios > 0; --ratios) {
         AtabGeom G{};
+        G.near2 = near * near;
+        G.far2 = far * far;
         int64_t nk = 0;
         for (int q = 0; q < kAtabRatios; ++q) {
             G.base[q] = (int32_t)nk;
             G.w[q] = -1;
             if (q >= ratios || (1 << q) >= root) continue;
-            G.w[q] = (int)std::min(std::ceil((2.0 / th + 1.0) * (double)(1 << q)), std::floor((std::cbrt(most) - 1.0) / 2.0));
-            nk += (int64_t)(2 * G.w[q] + 1) * (2 * G.w[q] + 1) * (2 * G.w[q] + 1);
+            double w = std::ceil((2.0 / th + 1.0) * (double)(1 << q));
+            if (q < kAtabShell) w = std::min(w, std::floor((std::cbrt(most) - 1.0) / 2.0));
+            const double keys = (2.0 * w + 1.0) * (2.0 * w + 1.0) * (2.0 * w + 1.0);
+            if (q >= kAtabShell && (shell * (double)(1 << (3 * q)) > most || keys > 4e7)) continue;
+            G.w[q] = (int)w;
+            nk += (int64_t)keys;
         }
         G.nkeys = (int32_t)nk;
         if (nk == 0) return TR_OK;
