@@ -2390,9 +2390,11 @@ __global__ __launch_bounds__(256) void k_atab(AtabGeom G, int ns, int s, float g
 // bits of neighbouring values are mostly equal, and lanes that meet on a bin
 // are served one by one); the last block to finish picks every domain's bin.
 // 8M cells of 7 domains: 1316 us with 8 bits a pass, a lookup per cell and a
-// launch for every pick; see the table of measurements for the present time.
+// launch for every pick, 189 us now (26 us a pass, 29 us the final one; two
+// blocks a compute unit 223 us, 512 threads a block 195 us: each block's fence
+// writes an L2 back).
 // ---------------------------------------------------------------------------
-constexpr int kSelBits = 11, kSelBins = 1 << kSelBits, kSelPasses = 6, kSelCopies = 4, kSelThreads = 512;
+constexpr int kSelBits = 11, kSelBins = 1 << kSelBits, kSelPasses = 6, kSelCopies = 4, kSelThreads = 1024;
 __host__ __device__ inline int select_shift(int pass) { return pass < 5 ? 64 - kSelBits * (pass + 1) : 0; }
 
 // Cell ranges of the domains: from a context's records, or (the entry point
@@ -2497,13 +2499,18 @@ __global__ __launch_bounds__(kSelThreads) void k_select(Doms D, int64_t n_cells,
         lo = end;
     }
     // the last block to get here picks the bins (its counts are all in: every
-    // block's are before its own increment)
-    __threadfence();
+    // wave's adds have completed before its block's increment).  One thread
+    // fences for its block: a device fence writes the XCD's L2 back, which
+    // took 140 of a pass's 157 us when all 8 waves of 1024 blocks did it
+    wait_stores();
     __syncthreads();
-    if (tid == 0) is_last = atomicAdd(st.done, 1u) == gridDim.x - 1;
+    if (tid == 0) {
+        __threadfence();
+        is_last = atomicAdd(st.done, 1u) == gridDim.x - 1;
+        if (is_last) __threadfence();
+    }
     __syncthreads();
     if (!is_last) return;
-    __threadfence();
     // a wave per domain, 32 bins a lane
     constexpr int kPer = kSelBins / 64;
     for (int d = tid >> 6; d < D.n; d += kSelThreads / 64) {
@@ -3570,7 +3577,7 @@ void launch_delta(const Doms &D, int64_t n_cells, const double *f_new, const dou
     const unsigned blocks = (unsigned)std::min<int64_t>((n_cells + 4 * kSelThreads - 1) / (4 * kSelThreads), 4 * (int64_t)n_cu);
     hipLaunchKernelGGL(k_select_init<Doms>, dim3(grid1((int64_t)D.n * kSelBins)), dim3(256), 0, stream, D, n_cells, st);
     for (int pass = 0; pass < kSelPasses; ++pass)
-        hipLaunchKernelGGL(k_select<Doms>, dim3(blocks), dim3(kSelThreads), 0, stream, D, n_cells, f_old, pass, st);
+        hipLaunchKernelGGL(k_select<Doms>, dim3(std::min(blocks, (unsigned)n_cu)), dim3(kSelThreads), 0, stream, D, n_cells, f_old, pass, st);
     hipLaunchKernelGGL(k_delta<Doms>, dim3(blocks), dim3(kSelThreads), 0, stream, D, n_cells, f_new, f_old, st);
 }
 

@@ -615,3 +615,46 @@ def test_target_chunks(T, orc, theta):
             g, j = out.cpu().numpy(), ion.cpu().numpy()
         assert np.all(np.isnan(g[bad])) and np.all(j[bad] == 0)
         compare(g[ok], j[ok], f0[tg[ok]], i0[tg[ok]], tol, name=f"chunks theta {theta} prec {prec}")
+
+
+@pytest.mark.parametrize("nside,waves", [(8, 0), (8, 4), (16, 8)])
+def test_more_emitting_rays_than_buffers(T, orc, nside, waves):
+    """Sources on a tenth of the cells: nearly every one of the 768 or 3072 rays
+    holds emission, more than the workgroup has buffers for, so FP32C maps
+    and marches the rays in several passes."""
+    P = W.small_lognormal(16, n_src=400, seed=70, nside=nside, n_radial=40)
+    tg = np.sort(np.random.default_rng(71).choice(P.total_cells(), 70, replace=False))
+    f0, i0 = orc_sweep(orc, P, thin=True, targets=tg)
+    for am in (1, 2):
+        g0, j0, st = gpu_sweep(T, P, T.TR_FP32C, thin=True, targets=tg, launch=(waves, 0, 0, 0, am))
+        compare(g0, j0, f0, i0, TOL32, name=f"{nside} passes waves {waves} atomics {am}")
+
+
+def test_delta_edges(T, orc):
+    """The exact lower median of every domain: one, two and odd counts of
+    cells around a wave, a block's run and its unrolled loop; ties, zeros,
+    denormals and values that differ in the last bit, in neighbouring domains."""
+    rng = np.random.default_rng(80)
+    sizes = [1, 2, 3, 63, 64, 65, 511, 513, 2047, 2049, 5000, 40007, 1, 300000]
+    old, new = [], []
+    for q, n in enumerate(sizes):
+        kind = q % 4
+        if kind == 0:
+            v = rng.integers(0, 3, n).astype(np.float64)                       # ties and zeros
+        elif kind == 1:
+            v = 1.0 + rng.integers(0, 50, n) * np.finfo(np.float64).eps        # the last bits
+        elif kind == 2:
+            v = rng.integers(0, 1 << 20, n) * 5e-324                           # denormals
+        else:
+            v = np.exp(40.0 * rng.standard_normal(n))
+        old.append(v)
+        new.append(v * (1.0 + 0.1 * rng.standard_normal(n)) if kind != 2 else v + 5e-324 * rng.integers(0, 9, n))
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    fo, fn = np.concatenate(old), np.abs(np.concatenate(new))
+    out = torch.full((len(sizes),), -1.0, dtype=torch.float64, device="cuda")
+    T.delta_noalloc(torch.tensor(fn, device="cuda"), torch.tensor(fo, device="cuda"), off, out)
+    got = out.cpu().numpy()
+    for d in range(len(sizes)):
+        ref = orc.delta_cell(fn[off[d]:off[d + 1]], fo[off[d]:off[d + 1]])
+        # a division and a difference: an ulp each
+        assert got[d] == ref or got[d] == pytest.approx(ref, rel=1e-15, abs=0.0), (d, got[d], ref)
