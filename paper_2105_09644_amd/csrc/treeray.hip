@@ -5,9 +5,10 @@
 //   k_cell_quantities      eps, alpha, e of every cell (eqs. os:ems, os:abs, os:erd)
 //   k_reduce_level         FP64 bottom-up node moments, one launch per tree level
 //   k_pack                 node records for the sweep (FP64 or FP32, SoA)
-//   k_sweep                per target: walk + node->ray mapping + per-ray
+//   k_walk                 the accepted nodes of every target and their pixel pairs
+//   k_sweep                per target: node->ray mapping + per-ray
 //                          On-the-Spot integration + sum over rays (Sec. 2.3-2.5)
-//   k_hist / k_select / k_delta   delta_cell with an exact radix-select median
+//   k_select / k_delta     delta_cell with an exact radix-select median
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -2285,7 +2286,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_kv_fallback(SweepArgs a
 // FP32 ray buffers in LDS accumulated by compare-and-swap (4, 8 and 16 waves).
 // With 4 waves per target 6 targets are resident: 6 waves per SIMD in 80
 // registers (44 spilled, outside the inner loops) are faster than 4 without
-// spills (169 against 195 ms on 128^3 at N_side 2): between its barriers a
+// spills (120 against 134 ms on 128^3 at N_side 2): between its barriers a
 // target's waves wait for memory and LDS, and only other targets fill that.
 // With 8 waves 80 registers bring 3 targets instead of 2, but cost as much (93
 // against 91 ms on the adaptive grid at N_side 4).
@@ -2861,16 +2862,18 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     if (waves <= 0) {
         waves = c->tuned_waves[f32 ? 1 : 0];
         // Several targets are resident, and the fewer waves share one the better their phases
-        // overlap (128^3 N_side 2 FP32C, 16 sources: 6 targets of 4 waves 158 ms, 2 of 8 waves
-        // 202 ms), as long as a target's rays with emission fit its share of the buffers at once:
+        // overlap (128^3 N_side 2 FP32C, 16 sources: 6 targets of 4 waves 120 ms, 2 of 8 waves
+        // 164 ms), as long as a target's rays with emission fit its share of the buffers at once:
         // with many sources most rays hold emission, and 8 waves on fewer targets save passes
-        // (N_side 4, FP32C / FP64: one source on 64^3, 4 waves 14.3 / 19.5 ms, 8 waves 19.0 /
-        // 21.0 ms; 200 / 60 sources on an adaptive grid 97 / 35 ms against 82 / 30 ms; N_side 2
-        // FP64, one source 8.2 against 10.3 ms, 1000 sources 69 against 63 ms).  In FP32 below
-        // N_side 4 all rays' buffers fit 6 targets (the emission rows in device memory).
+        // (N_side 4, FP32C / FP64: one source on 64^3, 4 waves 13.5 / 18.2 ms, 8 waves 18.2 /
+        // 20.1 ms; 200 / 60 sources on an adaptive grid 80 / 31.5 ms against 69 / 27.5 ms; N_side 2
+        // FP64, one source 7.9 against 10.0 ms, 1000 sources 63.5 against 60.0 ms).  In FP32 below
+        // N_side 4 all rays' buffers fit 6 targets (the emission rows in device memory).  A list of
+        // no more targets than a few a compute unit has nothing to overlap with: 8 waves finish
+        // each sooner (1000 targets of 128^3 with their build 0.66 against 0.62 ms).
         if (waves <= 0) {
             const int64_t few = (int64_t)(npix >= 192 ? 8 : 16) * c->n_dom;
-            waves = (f32 && npix < 192) || c->n_src_dev <= few ? 4 : 8;
+            waves = n_items > 4 * (int64_t)c->n_cu && ((f32 && npix < 192) || c->n_src_dev <= few) ? 4 : 8;
         }
     }
     // the radial-kernel variants are built for 4 and 8 waves per target only
