@@ -3252,7 +3252,11 @@ tr_status build_angular_table(tr_ctx *c)
         if ((st = dalloc(c, (void **)&c->atab_pool, sizeof(int32_t) * 4 * (size_t)tot)) ||
             (st = dalloc(c, (void **)&c->atab_idx, sizeof(int32_t) * (size_t)nk))) {
             dfree(sums);
-            return st;
+            dfree(c->atab_pool);
+            dfree(c->atab_idx);
+            if (ratios == 1) return st;
+            (void)hipGetLastError();   // no memory for it: without the largest ratio
+            continue;
         }
         hipError_t e = hipMemcpyAsync(sums, h.data(), sizeof(int64_t) * (size_t)waves, hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) {
