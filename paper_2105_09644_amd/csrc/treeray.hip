@@ -369,6 +369,8 @@ struct SweepArgs {
                                 // FP32, [4] of those marched again in FP64, [5] nodes from the table
     void *gbuf;              // ray buffers in global memory (when they do not fit in LDS)
     void *ebuf;              // split LDS buffers: the emission rows, rays x nr_max per workgroup
+    unsigned char *mbuf;     // marks and ray numbers in device memory: mask_slab_bytes per workgroup
+    int64_t mbuf_stride;
     int32_t split;           // 1: A, E, V rows in LDS (stride_k = 3 nr_max + 1), emission rows in ebuf
     double theta2, theta_if2, theta_src2;   // squared opening angles (0: criterion off)
     float guard_tol;
@@ -1773,6 +1775,13 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
     }
 }
 
+// Bytes of a workgroup's marks and ray numbers in device memory (MEMMASK): the
+// masks of all rays, of the rays with a buffer (in LDS when the buffers are), and the rays' buffers
+__host__ __device__ inline size_t mask_slab_bytes(int npix, int rays, int ew, bool ldsbuf)
+{
+    return (((size_t)npix + (ldsbuf ? 0 : rays)) * 8 * ew + (size_t)npix * 4 + 255) / 256 * 256;
+}
+
 // LDS words of a sweep workgroup: its next work item, and (fallback pass) the
 // shared walk's meetings, the next frontier's length (three by level), the
 // accepted count, an overflow
@@ -1857,12 +1866,16 @@ struct Target {
 
 // The sweep of one launch over the listed targets of a chunk.  FALLBACK: the
 // second pass over the items whose walks did not fit in the lists, walked here
-// by the whole workgroup with lists in device memory.
-template <typename Real, int WAVES, bool LDSBUF, bool FALLBACK, bool KV, bool CAS = false>
+// by the whole workgroup with lists in device memory.  WIDE: ray buffers in LDS,
+// but the marks and numbers of all rays in device memory, as they always are
+// beside ray buffers there: 12 to 20 bytes a ray, which from N_side 32 on
+// (12288 rays) leave LDS no room for buffers or do not fit at all.
+template <typename Real, int WAVES, bool LDSBUF, bool FALLBACK, bool KV, bool CAS = false, bool WIDE = false>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 {
     using R4 = typename R4T<Real>::T;
     constexpr int ATOMIC = CAS ? 2 : 1;
+    constexpr bool MEMMASK = WIDE || !LDSBUF;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar loops over waves' work
@@ -1870,10 +1883,22 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     const int ew = uniform(1 + (nrm > 64));   // words of a ray's mask of emitting points (1 or 2)
     const size_t buf_elems = (size_t)rays * a.stride_k;
     char *p = smem;
-    unsigned long long *const emask = (unsigned long long *)p;   // the masks of all rays, marked before the mapping
-    p += (size_t)npix * ew * 8;
-    unsigned long long *const cmask = (unsigned long long *)p;   // those of the rays with a buffer
-    p += (size_t)rays * ew * 8;
+    unsigned long long *emask;   // the masks of all rays, marked before the mapping
+    unsigned long long *cmask;   // those of the rays with a buffer
+    unsigned *rinfo;             // per ray: its buffer << 8 | its outermost emitting point, 0: no buffer
+    if constexpr (MEMMASK) {
+        emask = (unsigned long long *)(a.mbuf + (size_t)blockIdx.x * (size_t)a.mbuf_stride);
+        rinfo = (unsigned *)(emask + ((size_t)npix + (LDSBUF ? 0 : rays)) * ew);
+    } else {
+        emask = (unsigned long long *)p;
+        p += (size_t)npix * ew * 8;
+    }
+    if constexpr (LDSBUF) {
+        cmask = (unsigned long long *)p;
+        p += (size_t)rays * ew * 8;
+    } else {
+        cmask = emask + (size_t)npix * ew;
+    }
     Real *buf;
     if constexpr (LDSBUF) {
         buf = (Real *)p;
@@ -1897,7 +1922,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     p += WAVES * sizeof(double);
     int *sc = (int *)p;
     p += S_COUNT * sizeof(int);
-    unsigned *const rinfo = (unsigned *)p;   // per ray: its buffer << 8 | its outermost emitting point, 0: no buffer
+    if constexpr (!MEMMASK) rinfo = (unsigned *)p;
     int *fr0 = nullptr;   // fallback: frontiers of gfmax entries, then gamax accepted nodes
     if (FALLBACK) fr0 = a.glist + (size_t)blockIdx.x * (2 * (size_t)a.gfmax + a.gamax);
 
@@ -2060,7 +2085,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
         // The rays with emission (KV: all rays), as many at a time as there are buffers
         for (int r0 = 0;; r0 += rays) {
             const int tid = here((int)threadIdx.x), lane = tid & 63;
-            // every wave numbers them (the same values); those of this pass get a buffer and a copy of their mask
+            // every wave numbers them (the same values); those of this pass get a buffer and a copy of their
+            // mask (in device memory one wave writes each)
             int ns = 0;
             for (int base = 0; base < npix; base += 64) {
                 const int k = base + lane;
@@ -2072,13 +2098,14 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                 const int top = KV ? (k < npix ? nr - 1 : 0) : mask_top(m0, m1);
                 const uint64_t on = __ballot(top > 0);
                 const int i = ns + bits_below(on) - r0;
+                ns += (int)__popcll(on);
+                if (MEMMASK && (base >> 6) % WAVES != wave) continue;
                 const bool mine = top > 0 && i >= 0 && i < rays;
                 if (k < npix) rinfo[k] = mine ? (unsigned)(i << 8 | top) : 0u;
                 if (mine) {
                     cmask[(size_t)i * ew] = m0;
                     if (ew > 1) cmask[(size_t)i * ew + 1] = m1;
                 }
-                ns += (int)__popcll(on);
             }
             const int np = min(rays, ns - r0);
             const bool last = r0 + rays >= ns;
@@ -2300,6 +2327,20 @@ template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_cas_fallback(SweepArgs a)
 {
     sweep_body<float, WAVES, true, true, false, true>(a);
+}
+
+// Ray buffers in LDS, marks and ray numbers in device memory (4, 8 and 16
+// waves; FP32 buffers by compare-and-swap)
+template <typename Real, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_wide(SweepArgs a)
+{
+    sweep_body<Real, WAVES, true, false, false, sizeof(Real) == 4, true>(a);
+}
+
+template <typename Real, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_wide_fallback(SweepArgs a)
+{
+    sweep_body<Real, WAVES, true, true, false, sizeof(Real) == 4, true>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -2633,6 +2674,8 @@ struct tr_ctx {
     size_t gbuf_bytes = 0;
     void *ebuf = nullptr;   // emission rows of split LDS buffers
     size_t ebuf_bytes = 0;
+    unsigned char *mbuf = nullptr;   // marks and ray numbers that are not in LDS
+    size_t mbuf_bytes = 0;
     int2 *lists = nullptr;               // the listed walks of a chunk of targets, their records, the pool
     uint16_t *emit_at = nullptr;         // of pairs of the nodes outside the angular table
     TargetRec *rec = nullptr;
@@ -2724,6 +2767,8 @@ void free_domains(tr_ctx *c)
     c->gbuf_bytes = 0;
     dfree(c->ebuf);
     c->ebuf_bytes = 0;
+    dfree(c->mbuf);
+    c->mbuf_bytes = 0;
     dfree(c->lists);
     dfree(c->emit_at);
     dfree(c->rec);
@@ -2777,20 +2822,24 @@ tr_status dalloc(tr_ctx *c, void **p, size_t bytes)
 }
 
 // LDS bytes of one sweep workgroup with buffers for `rays` rays (must mirror the carve-up in sweep_body)
-size_t sweep_lds_bytes(size_t real, int npix, int rays, int stride_k, int nrm, int waves, bool ldsbuf)
+size_t sweep_lds_bytes(size_t real, int npix, int rays, int stride_k, int nrm, int waves, bool ldsbuf, bool wide)
 {
     const size_t ew = nrm > 64 ? 2 : 1;
-    size_t b = ((size_t)npix + rays) * 8 * ew;
-    if (ldsbuf) b += (((size_t)rays * stride_k * real + 15) / 16) * 16;
+    size_t b = 0;
+    if (ldsbuf) b += (size_t)rays * 8 * ew + (((size_t)rays * stride_k * real + 15) / 16) * 16;
     b += 2 * (((size_t)nrm * real + 15) / 16) * 16;
     b += 2 * (size_t)nrm * 8;
     b += (size_t)waves * 8;
     b += S_COUNT * 4;
-    b += (size_t)npix * 4;
+    if (ldsbuf && !wide) b += (size_t)npix * (8 * ew + 4);
     return b;
 }
 
 constexpr size_t kLdsMax = 160 * 1024, kLdsGranule = 1280;
+// N_side 32 and 64: marks and ray numbers in device memory (at N_side 16 they
+// take 36 or 60 KB of LDS; N_side 32 would take 144 or 240 KB)
+constexpr int kWidePix = 12 * 32 * 32;
+constexpr size_t kSlabBytes = (size_t)16 << 30;   // most for the ray buffers in device memory
 
 using KernelFn = void (*)(SweepArgs);
 
@@ -2806,6 +2855,14 @@ KernelFn pick_kernel_kv(int waves, bool ldsbuf, bool fallback)
         return ldsbuf ? (KernelFn)k_sweep_kv<Real, 8, true> : (KernelFn)k_sweep_kv<Real, 8, false>;
     }
     return nullptr;
+}
+
+template <typename Real>
+KernelFn pick_kernel_wide(int waves, bool fallback)
+{
+    if (waves == 4) return fallback ? (KernelFn)k_sweep_wide_fallback<Real, 4> : (KernelFn)k_sweep_wide<Real, 4>;
+    if (waves == 8) return fallback ? (KernelFn)k_sweep_wide_fallback<Real, 8> : (KernelFn)k_sweep_wide<Real, 8>;
+    return fallback ? (KernelFn)k_sweep_wide_fallback<Real, 16> : (KernelFn)k_sweep_wide<Real, 16>;
 }
 
 KernelFn pick_kernel_cas(int waves, bool fallback)
@@ -2839,9 +2896,11 @@ struct LaunchPlan {
     KernelFn fn = nullptr, fn_fb = nullptr;
     int waves = 0, blocks = 0, per_cu = 0, stride_k = 0;
     int64_t chunk = 0;   // targets walked and listed at a time
+    int64_t mbuf_stride = 0;
     size_t lds = 0;
     bool ldsbuf = true;
     bool cas = false;   // FP32 LDS buffers accumulated by compare-and-swap
+    bool wide = false;  // ray buffers in LDS, marks and ray numbers in device memory
     bool split = false; // A, E, V rows in LDS, emission rows in device memory
     int rays = 0;       // ray buffers of a workgroup
     int intm = 1;   // integration: 1 a lane per ray, 2 a wave per ray, 3/4/5 a group of 4/8/16 lanes,
@@ -2894,6 +2953,14 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
                 (waves == 8 || waves == 16 ? (am > 0 ? am == 2 : true) : waves == 4 && (am > 0 ? am == 2 : waves_req <= 0));
         if (L.cas) L.fn = pick_kernel_cas(waves, false);
     }
+    // from N_side 32 on the marks of all rays are in device memory; the radial-kernel variants and
+    // 1 or 2 waves have their ray buffers there too
+    L.wide = npix >= kWidePix && bm != 2 && !kv && waves >= 4;
+    const bool lds_ok = bm != 2 && (npix < kWidePix || L.wide);
+    if (L.wide) {
+        L.cas = f32;
+        L.fn = f32 ? pick_kernel_wide<float>(waves, false) : pick_kernel_wide<double>(waves, false);
+    }
     // Ray buffers: a target's rays that hold emission (KV: all) are mapped and integrated as
     // many at a time as there are buffers.  Four rows per ray (odd stride: ray k of lane k hits
     // distinct banks), or in FP32 the A, E, V rows in LDS and the emission rows in device memory
@@ -2902,8 +2969,8 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     // buffers are in device memory.
     const int stride4 = 4 * nrm + 1, stride3 = 3 * nrm + 1;
     int occ = 0;
-    const size_t fixed = sweep_lds_bytes(real, npix, 0, stride4, nrm, waves, true);
-    if (bm != 2 && fixed < kLdsMax) {
+    const size_t fixed = sweep_lds_bytes(real, npix, 0, stride4, nrm, waves, true, L.wide);
+    if (lds_ok && fixed < kLdsMax) {
         HIPCHK(hipFuncSetAttribute((const void *)L.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
         HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void *)L.fn, waves * 64, 0));
         if (tpc_req > 0) occ = std::min(occ, tpc_req);
@@ -2911,7 +2978,7 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
             const size_t room = kLdsMax / (size_t)occ / kLdsGranule * kLdsGranule;
             auto fit = [&](int stride) {
                 int r = npix;
-                if (sweep_lds_bytes(real, npix, r, stride, nrm, waves, true) > room) {
+                if (sweep_lds_bytes(real, npix, r, stride, nrm, waves, true, L.wide) > room) {
                     r = room <= fixed + 16 ? 0 : (int)((room - fixed - 16) / ((size_t)stride * real + 8 * (nrm > 64 ? 2 : 1)));
                     r = std::min(r, npix);
                 }
@@ -2926,17 +2993,19 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     L.ldsbuf = occ >= 1;
     if (bm == 1 && !L.ldsbuf) return fail(c, TR_EINVAL, "ray buffers do not fit in LDS for this N_PIX and N_R");
     if (!L.ldsbuf) {
-        L.rays = npix;
+        L.rays = std::min(npix, kWidePix);
+        L.wide = false;
         L.split = false;
         L.cas = false;
         L.fn = kv ? (f32 ? pick_kernel_kv<float>(waves, false, false) : pick_kernel_kv<double>(waves, false, false))
                   : (f32 ? pick_kernel<float>(waves, false, false) : pick_kernel<double>(waves, false, false));
     }
-    L.fn_fb = L.cas ? pick_kernel_cas(waves, true)
+    L.fn_fb = L.wide ? (f32 ? pick_kernel_wide<float>(waves, true) : pick_kernel_wide<double>(waves, true))
+                    : L.cas ? pick_kernel_cas(waves, true)
                     : kv ? (f32 ? pick_kernel_kv<float>(waves, L.ldsbuf, true) : pick_kernel_kv<double>(waves, L.ldsbuf, true))
                          : (f32 ? pick_kernel<float>(waves, L.ldsbuf, true) : pick_kernel<double>(waves, L.ldsbuf, true));
     L.stride_k = L.split ? stride3 : stride4;
-    L.lds = sweep_lds_bytes(real, npix, L.rays, L.stride_k, nrm, waves, L.ldsbuf);
+    L.lds = sweep_lds_bytes(real, npix, L.rays, L.stride_k, nrm, waves, L.ldsbuf, L.wide);
     if (L.lds > kLdsMax)
         return fail(c, TR_EINVAL, "sweep kernel does not fit on a compute unit (LDS " + std::to_string(L.lds) + " B)");
     HIPCHK(hipFuncSetAttribute((const void *)L.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.lds));
@@ -2944,6 +3013,8 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void *)L.fn, waves * 64, L.lds));
     if (occ <= 0) return fail(c, TR_EINVAL, "sweep kernel does not fit on a compute unit (LDS " + std::to_string(L.lds) + " B)");
     L.per_cu = tpc_req > 0 ? std::min(tpc_req, occ) : occ;
+    if (!L.ldsbuf)   // (N_side 32: 6 to 50 MB a workgroup)
+        while (L.per_cu > 1 && (size_t)c->n_cu * L.per_cu * L.rays * L.stride_k * real > kSlabBytes) --L.per_cu;
     // integration: by default groups of at least 4 lanes per ray, so that a target's few
     // emitting rays share a wave (a ray with more emitting points gets a wider group): against
     // groups of at least 8 or 16 lanes 2 to 15% faster at N_side 4, equal at N_side 2
@@ -2997,6 +3068,17 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
             c->gbuf_bytes = need;
         }
     }
+    if (!L.ldsbuf || L.wide) {
+        L.mbuf_stride = (int64_t)mask_slab_bytes(npix, L.rays, nrm > 64 ? 2 : 1, L.ldsbuf);
+        const size_t need = nblk * (size_t)L.mbuf_stride;
+        if (need > c->mbuf_bytes) {
+            drop_graph(c);
+            dfree(c->mbuf);
+            c->mbuf_bytes = 0;
+            if (dalloc(c, (void **)&c->mbuf, need)) return TR_ENOMEM;
+            c->mbuf_bytes = need;
+        }
+    }
     if (L.split) {
         const size_t need = nblk * L.rays * nrm * real;
         if (need > c->ebuf_bytes) {
@@ -3047,6 +3129,8 @@ tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_o
     a.stats = c->stats;
     a.gbuf = c->gbuf;
     a.ebuf = c->ebuf;
+    a.mbuf = c->mbuf;
+    a.mbuf_stride = L.mbuf_stride;
     a.split = L.split ? 1 : 0;
     a.rays = L.rays;
     a.theta2 = c->p.theta * c->p.theta;

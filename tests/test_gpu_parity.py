@@ -658,3 +658,34 @@ def test_delta_edges(T, orc):
         ref = orc.delta_cell(fn[off[d]:off[d + 1]], fo[off[d]:off[d + 1]])
         # a division and a difference: an ulp each
         assert got[d] == ref or got[d] == pytest.approx(ref, rel=1e-15, abs=0.0), (d, got[d], ref)
+
+
+@pytest.mark.parametrize("nside,n_radial,n_src,prec,launch,over", [
+    (32, 48, 3, 0, (0, 0, 0, 0, 0), {}),
+    (32, 48, 400, 0, (4, 0, 0, 0, 0), {}),                 # more rays with emission than buffers
+    (32, 48, 400, 0, (16, 0, 1, 0, 0), {}),
+    (32, 48, 3, 0, (0, 0, 2, 0, 0), {}),
+    (32, 48, 3, 0, (0, 0, 0, 0, 0), {"eps_kernel": 5}),    # radial-kernel variants: device memory
+    (32, 48, 3, 0, (2, 0, 0, 0, 0), {}),                   # 2 waves: device memory
+    (32, 20, 400, 1, (0, 0, 0, 0, 0), {}),
+    (32, 100, 400, 1, (8, 0, 0, 0, 0), {}),                # two mask words
+    (32, 48, 3, 1, (0, 0, 2, 0, 0), {}),
+    (32, 48, 400, 1, (0, 0, 0, 0, 0), {"theta": 0.05}),    # walks by the fallback pass
+    (64, 24, 3, 0, (0, 0, 0, 0, 0), {}),
+    (64, 48, 400, 1, (0, 0, 0, 0, 0), {}),
+    (64, 100, 3, 1, (0, 0, 1, 0, 0), {}),
+])
+def test_marks_outside_lds(T, orc, nside, n_radial, n_src, prec, launch, over):
+    """N_side 32 and 64: the masks and numbers of 12288 and 49152 rays do not
+    fit in LDS beside ray buffers, wherever those are."""
+    P = W.small_lognormal(16, n_src=n_src, seed=90, nside=nside, n_radial=n_radial)
+    P.params.subsample = 3
+    for k, v in over.items():
+        setattr(P.params, k, v)
+    tg = np.sort(np.random.default_rng(91).choice(P.total_cells(), 24, replace=False))
+    f0, i0 = orc_sweep(orc, P, thin=True, targets=tg)
+    tol = TOL64 if prec == T.TR_FP64 else TOL32
+    g0, j0, st = gpu_sweep(T, P, prec, thin=True, targets=tg, launch=launch)
+    compare(g0, j0, f0, i0, tol, name=f"N_side {nside} N_R {n_radial} {n_src} sources prec {prec} launch {launch}")
+    in_lds = launch[2] != 2 and launch[0] != 2 and "eps_kernel" not in over
+    assert (st.buffer_in_lds != 0) == in_lds
