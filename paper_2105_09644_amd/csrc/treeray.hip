@@ -1392,7 +1392,10 @@ __device__ void mark_nodes(const SweepArgs &a, unsigned long long *emask, int ew
 // KV: the radial-kernel variants of App. A (otherwise two-point W_f,3 and
 // W_p), whose emission may be spread; every ray has a buffer then, and cmask
 // (by buffer) is marked here.
-template <typename Real, int ATOMIC, bool KV, bool CLASSIFY>
+// LDSBUF false (buffers in device memory): a lane per point of a pair, the
+// points of 64 pairs laid end to end: neighbouring lanes add to neighbouring
+// points, so an atomic instruction touches a few cache lines and not 64.
+template <typename Real, int ATOMIC, bool LDSBUF, bool KV, bool CLASSIFY>
 __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, const unsigned *rinfo, unsigned long long *cmask,
                           int ew, const int *per, const Real *rt, int nr, Real rc_inv, Real rcoef, int n,
                           unsigned entry, int cnt, int tx, int ty, int tz, int tsize, uint64_t &guard_count,
@@ -1495,6 +1498,36 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, const unsi
     const Real wsf = wscale > (Real)0 ? wscale : -fb0;
     PairStream<CLASSIFY> ps(lane, entry, CLASSIFY ? __ballot(lane < cnt && entry == kNoEntry) : 0ull);
     if (CLASSIFY) tab_count += ps.n_ent;
+    // this lane's points i0 .. i0 + npt - 1 of a pair's support (buffer k, weight wk), by the whole wave
+    auto add_points = [&](int node, int npk, int k, Real wk, int i0, int npt) {
+        const int jlo = (npk & 255) + i0;
+        const Real jd = __shfl(d, node, 64), jhinv = __shfl(hinv, node, 64), jwf = __shfl(wsf, node, 64);
+        const Real ja = __shfl(qa, node, 64), je = __shfl(qe, node, 64), jv = __shfl(qv, node, 64);
+        const int jep = KV ? __shfl(epacked, node, 64) : 0;
+        const int jemode = jep & 3, jle = (jep >> 2) & 255, jne = (jep >> 10) & 255;
+        Real jea = 0, jeb = 0, jqeps = 0;
+        if (KV) {
+            jea = __shfl(ea, node, 64);
+            jeb = __shfl(eb, node, 64);
+            jqeps = __shfl(qeps, node, 64);
+        }
+        const Real jfb = -jwf;   // the bracket weight when there is no W_p support
+        Real *row = R.b + ((int)__umul24(k, R.stride) + R.oa + jlo);
+        Real fi = (Real)jlo;
+        for (int io = 0; io < npt; ++io, ++row, fi += (Real)1) {
+            const Real ws = here(smooth_kernel<Real>(mg, (rcoef * (fi * fi) - jd) * jhinv) * jwf);
+            const Real w = jwf > (Real)0 ? ws : (i0 + io == 0 ? jfb : (Real)1 - jfb);
+            buf_add3<Real, ATOMIC>(wk, row, w * ja, row + nrm, w * je, row + 2 * nrm, w * jv);
+            if (KV && jemode != 0) {   // the emission row
+                const Real wq = emission_weight<Real>(jemode, jlo + io, i0 + io, jle, jne, jea, jeb, jfb, rcoef, jd, jhinv,
+                                                      a.eps_kernel == K_G) * jqeps;
+                if (wq != (Real)0) {
+                    buf_add<Real, 1>(&R.eps(k, jlo + io), wk * wq);
+                    mark_points(cmask + (size_t)k * ew, jlo + io, true, false);
+                }
+            }
+        }
+    };
     // pairs collected so far, lanes below qfill: kc with the node's lane above it (pixel 16 bits, count 7, lane 6)
     int q = 0, qfill = 0;
     for (;;) {
@@ -1531,11 +1564,8 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, const unsi
         node = (batch >> 23) & 63;
         kc = batch & 0x7fffff;
         const int npk = __shfl(packed, node, 64);
-        const int jlo = npk & 255;
         const unsigned ri = valid ? rinfo[kc & 0xffff] : 0u;
-        const int npt = valid ? min((npk >> 8) & 255, (int)(ri & 255u) - jlo + 1) : 0;
-        const Real jd = __shfl(d, node, 64), jhinv = __shfl(hinv, node, 64), jwf = __shfl(wsf, node, 64);
-        const Real ja = __shfl(qa, node, 64), je = __shfl(qe, node, 64), jv = __shfl(qv, node, 64);
+        const int npt = valid ? min((npk >> 8) & 255, (int)(ri & 255u) - (npk & 255) + 1) : 0;
         const int k = (int)(ri >> 8);
         const Real wk = (Real)(kc >> 16) * inv_s3;
         if (any_emits) {
@@ -1550,28 +1580,19 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, const unsi
                 if (KV) mark_points(cmask + (size_t)k * ew, jie, je0 != (Real)0, je1 != (Real)0);
             }
         }
-        const int jep = KV ? __shfl(epacked, node, 64) : 0;
-        const int jemode = jep & 3, jle = (jep >> 2) & 255, jne = (jep >> 10) & 255;
-        Real jea = 0, jeb = 0, jqeps = 0;
-        if (KV) {
-            jea = __shfl(ea, node, 64);
-            jeb = __shfl(eb, node, 64);
-            jqeps = __shfl(qeps, node, 64);
-        }
-        const Real jfb = -jwf;   // the bracket weight when there is no W_p support
-        Real *row = R.b + ((int)__umul24(k, R.stride) + R.oa + jlo);
-        Real fi = (Real)jlo;
-        for (int io = 0; io < npt; ++io, ++row, fi += (Real)1) {
-            const Real ws = here(smooth_kernel<Real>(mg, (rcoef * (fi * fi) - jd) * jhinv) * jwf);
-            const Real w = jwf > (Real)0 ? ws : (io == 0 ? jfb : (Real)1 - jfb);
-            buf_add3<Real, ATOMIC>(wk, row, w * ja, row + nrm, w * je, row + 2 * nrm, w * jv);
-            if (KV && jemode != 0) {   // the emission row
-                const Real wq = emission_weight<Real>(jemode, jlo + io, io, jle, jne, jea, jeb, jfb, rcoef, jd, jhinv,
-                                                      a.eps_kernel == K_G) * jqeps;
-                if (wq != (Real)0) {
-                    buf_add<Real, 1>(&R.eps(k, jlo + io), wk * wq);
-                    mark_points(cmask + (size_t)k * ew, jlo + io, true, false);
-                }
+        if constexpr (LDSBUF) {
+            add_points(node, npk, k, wk, 0, npt);
+        } else {
+            int tot;
+            const int off = wave_excl_scan_dpp(max(npt, 0), tot);
+            for (int b = 0; b < tot; b += 64) {
+                // the pair of this lane's point: the last one that starts at or before it
+                int src = 0;
+#pragma unroll
+                for (int h = 32; h > 0; h >>= 1) src = __shfl(off, src + h, 64) <= b + lane ? src + h : src;
+                const int pn = __shfl(node, src, 64);
+                add_points(pn, __shfl(packed, pn, 64), __shfl(k, src, 64), __shfl(wk, src, 64),
+                           b + lane - __shfl(off, src, 64), b + lane < tot ? 1 : 0);
             }
         }
     }
@@ -1775,7 +1796,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
     }
 }
 
-// Bytes of a workgroup's marks and ray numbers in device memory (MEMMASK): the
+// Bytes of a workgroup's marks and ray numbers in device memory: the
 // masks of all rays, of the rays with a buffer (in LDS when the buffers are), and the rays' buffers
 __host__ __device__ inline size_t mask_slab_bytes(int npix, int rays, int ew, bool ldsbuf)
 {
@@ -1866,16 +1887,15 @@ struct Target {
 
 // The sweep of one launch over the listed targets of a chunk.  FALLBACK: the
 // second pass over the items whose walks did not fit in the lists, walked here
-// by the whole workgroup with lists in device memory.  WIDE: ray buffers in LDS,
-// but the marks and numbers of all rays in device memory, as they always are
-// beside ray buffers there: 12 to 20 bytes a ray, which from N_side 32 on
-// (12288 rays) leave LDS no room for buffers or do not fit at all.
+// by the whole workgroup with lists in device memory.  WIDE: the marks and
+// numbers of all rays in device memory, wherever the ray buffers are: 12 to 20
+// bytes a ray, which from N_side 32 on (12288 rays) leave LDS no room for buffers
+// or do not fit at all.
 template <typename Real, int WAVES, bool LDSBUF, bool FALLBACK, bool KV, bool CAS = false, bool WIDE = false>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 {
     using R4 = typename R4T<Real>::T;
     constexpr int ATOMIC = CAS ? 2 : 1;
-    constexpr bool MEMMASK = WIDE || !LDSBUF;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar loops over waves' work
@@ -1886,18 +1906,18 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     unsigned long long *emask;   // the masks of all rays, marked before the mapping
     unsigned long long *cmask;   // those of the rays with a buffer
     unsigned *rinfo;             // per ray: its buffer << 8 | its outermost emitting point, 0: no buffer
-    if constexpr (MEMMASK) {
+    if constexpr (WIDE) {
         emask = (unsigned long long *)(a.mbuf + (size_t)blockIdx.x * (size_t)a.mbuf_stride);
         rinfo = (unsigned *)(emask + ((size_t)npix + (LDSBUF ? 0 : rays)) * ew);
     } else {
         emask = (unsigned long long *)p;
         p += (size_t)npix * ew * 8;
     }
-    if constexpr (LDSBUF) {
+    if constexpr (WIDE && !LDSBUF) {
+        cmask = emask + (size_t)npix * ew;
+    } else {
         cmask = (unsigned long long *)p;
         p += (size_t)rays * ew * 8;
-    } else {
-        cmask = emask + (size_t)npix * ew;
     }
     Real *buf;
     if constexpr (LDSBUF) {
@@ -1922,7 +1942,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     p += WAVES * sizeof(double);
     int *sc = (int *)p;
     p += S_COUNT * sizeof(int);
-    if constexpr (!MEMMASK) rinfo = (unsigned *)p;
+    if constexpr (!WIDE) rinfo = (unsigned *)p;
     int *fr0 = nullptr;   // fallback: frontiers of gfmax entries, then gamax accepted nodes
     if (FALLBACK) fr0 = a.glist + (size_t)blockIdx.x * (2 * (size_t)a.gfmax + a.gamax);
 
@@ -2099,7 +2119,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                 const uint64_t on = __ballot(top > 0);
                 const int i = ns + bits_below(on) - r0;
                 ns += (int)__popcll(on);
-                if (MEMMASK && (base >> 6) % WAVES != wave) continue;
+                if (WIDE && (base >> 6) % WAVES != wave) continue;
                 const bool mine = top > 0 && i >= 0 && i < rays;
                 if (k < npix) rinfo[k] = mine ? (unsigned)(i << 8 | top) : 0u;
                 if (mine) {
@@ -2158,7 +2178,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                         if (FALLBACK) v.x = fr0[2 * (size_t)a.gfmax + c + WAVES * lane];
                         else v = a.lists[t.list + c + WAVES * lane];
                     }
-                    map_nodes<Real, ATOMIC, KV, FALLBACK>(a, R, rinfo, cmask, ew, per, rt, nr, rc_inv, rcoef, v.x,
+                    map_nodes<Real, ATOMIC, LDSBUF, KV, FALLBACK>(a, R, rinfo, cmask, ew, per, rt, nr, rc_inv, rcoef, v.x,
                                                           (unsigned)v.y, cnt, t.tx, t.ty, t.tz, t.tsize, n_guard, n_tab);
                 }
             }
@@ -2341,6 +2361,19 @@ template <typename Real, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_wide_fallback(SweepArgs a)
 {
     sweep_body<Real, WAVES, true, true, false, sizeof(Real) == 4, true>(a);
+}
+
+// both in device memory (8 waves)
+template <typename Real, bool KV>
+__global__ __launch_bounds__(512, 4) void k_sweep_wide_mem(SweepArgs a)
+{
+    sweep_body<Real, 8, false, false, KV, false, true>(a);
+}
+
+template <typename Real, bool KV>
+__global__ __launch_bounds__(512, 4) void k_sweep_wide_mem_fallback(SweepArgs a)
+{
+    sweep_body<Real, 8, false, true, KV, false, true>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -2825,13 +2858,13 @@ tr_status dalloc(tr_ctx *c, void **p, size_t bytes)
 size_t sweep_lds_bytes(size_t real, int npix, int rays, int stride_k, int nrm, int waves, bool ldsbuf, bool wide)
 {
     const size_t ew = nrm > 64 ? 2 : 1;
-    size_t b = 0;
-    if (ldsbuf) b += (size_t)rays * 8 * ew + (((size_t)rays * stride_k * real + 15) / 16) * 16;
+    size_t b = wide && !ldsbuf ? 0 : (size_t)rays * 8 * ew;
+    if (ldsbuf) b += (((size_t)rays * stride_k * real + 15) / 16) * 16;
     b += 2 * (((size_t)nrm * real + 15) / 16) * 16;
     b += 2 * (size_t)nrm * 8;
     b += (size_t)waves * 8;
     b += S_COUNT * 4;
-    if (ldsbuf && !wide) b += (size_t)npix * (8 * ew + 4);
+    if (!wide) b += (size_t)npix * (8 * ew + 4);
     return b;
 }
 
@@ -2863,6 +2896,13 @@ KernelFn pick_kernel_wide(int waves, bool fallback)
     if (waves == 4) return fallback ? (KernelFn)k_sweep_wide_fallback<Real, 4> : (KernelFn)k_sweep_wide<Real, 4>;
     if (waves == 8) return fallback ? (KernelFn)k_sweep_wide_fallback<Real, 8> : (KernelFn)k_sweep_wide<Real, 8>;
     return fallback ? (KernelFn)k_sweep_wide_fallback<Real, 16> : (KernelFn)k_sweep_wide<Real, 16>;
+}
+
+template <typename Real>
+KernelFn pick_kernel_wide_mem(bool kv, bool fallback)
+{
+    if (kv) return fallback ? (KernelFn)k_sweep_wide_mem_fallback<Real, true> : (KernelFn)k_sweep_wide_mem<Real, true>;
+    return fallback ? (KernelFn)k_sweep_wide_mem_fallback<Real, false> : (KernelFn)k_sweep_wide_mem<Real, false>;
 }
 
 KernelFn pick_kernel_cas(int waves, bool fallback)
@@ -2900,7 +2940,7 @@ struct LaunchPlan {
     size_t lds = 0;
     bool ldsbuf = true;
     bool cas = false;   // FP32 LDS buffers accumulated by compare-and-swap
-    bool wide = false;  // ray buffers in LDS, marks and ray numbers in device memory
+    bool wide = false;  // marks and ray numbers in device memory
     bool split = false; // A, E, V rows in LDS, emission rows in device memory
     int rays = 0;       // ray buffers of a workgroup
     int intm = 1;   // integration: 1 a lane per ray, 2 a wave per ray, 3/4/5 a group of 4/8/16 lanes,
@@ -2954,7 +2994,7 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
         if (L.cas) L.fn = pick_kernel_cas(waves, false);
     }
     // from N_side 32 on the marks of all rays are in device memory; the radial-kernel variants and
-    // 1 or 2 waves have their ray buffers there too
+    // 1 or 2 waves (taken as 8) have their ray buffers there too
     L.wide = npix >= kWidePix && bm != 2 && !kv && waves >= 4;
     const bool lds_ok = bm != 2 && (npix < kWidePix || L.wide);
     if (L.wide) {
@@ -2994,13 +3034,16 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     if (bm == 1 && !L.ldsbuf) return fail(c, TR_EINVAL, "ray buffers do not fit in LDS for this N_PIX and N_R");
     if (!L.ldsbuf) {
         L.rays = std::min(npix, kWidePix);
-        L.wide = false;
+        L.wide = npix >= kWidePix;
         L.split = false;
         L.cas = false;
-        L.fn = kv ? (f32 ? pick_kernel_kv<float>(waves, false, false) : pick_kernel_kv<double>(waves, false, false))
-                  : (f32 ? pick_kernel<float>(waves, false, false) : pick_kernel<double>(waves, false, false));
+        if (L.wide) L.waves = waves = 8;
+        L.fn = L.wide ? (f32 ? pick_kernel_wide_mem<float>(kv, false) : pick_kernel_wide_mem<double>(kv, false))
+               : kv   ? (f32 ? pick_kernel_kv<float>(waves, false, false) : pick_kernel_kv<double>(waves, false, false))
+                      : (f32 ? pick_kernel<float>(waves, false, false) : pick_kernel<double>(waves, false, false));
     }
-    L.fn_fb = L.wide ? (f32 ? pick_kernel_wide<float>(waves, true) : pick_kernel_wide<double>(waves, true))
+    L.fn_fb = L.wide ? (L.ldsbuf ? (f32 ? pick_kernel_wide<float>(waves, true) : pick_kernel_wide<double>(waves, true))
+                                 : (f32 ? pick_kernel_wide_mem<float>(kv, true) : pick_kernel_wide_mem<double>(kv, true)))
                     : L.cas ? pick_kernel_cas(waves, true)
                     : kv ? (f32 ? pick_kernel_kv<float>(waves, L.ldsbuf, true) : pick_kernel_kv<double>(waves, L.ldsbuf, true))
                          : (f32 ? pick_kernel<float>(waves, L.ldsbuf, true) : pick_kernel<double>(waves, L.ldsbuf, true));
@@ -3068,7 +3111,7 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
             c->gbuf_bytes = need;
         }
     }
-    if (!L.ldsbuf || L.wide) {
+    if (L.wide) {
         L.mbuf_stride = (int64_t)mask_slab_bytes(npix, L.rays, nrm > 64 ? 2 : 1, L.ldsbuf);
         const size_t need = nblk * (size_t)L.mbuf_stride;
         if (need > c->mbuf_bytes) {

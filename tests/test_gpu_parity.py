@@ -689,3 +689,25 @@ def test_marks_outside_lds(T, orc, nside, n_radial, n_src, prec, launch, over):
     compare(g0, j0, f0, i0, tol, name=f"N_side {nside} N_R {n_radial} {n_src} sources prec {prec} launch {launch}")
     in_lds = launch[2] != 2 and launch[0] != 2 and "eps_kernel" not in over
     assert (st.buffer_in_lds != 0) == in_lds
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("nside,n_radial,waves,over", [
+    (2, 100, 8, {}),                     # supports of many points, two mask words
+    (4, 20, 1, {}),
+    (8, 24, 16, {"eps_kernel": 5}),      # spread emission (run by 8 waves)
+    (2, 20, 4, {"eps_kernel": 4, "mass_kernel": 6}),
+    (4, 100, 8, {"eps_kernel": 6}),
+])
+def test_device_memory_points(T, orc, nside, n_radial, waves, over, prec):
+    """Ray buffers in device memory: a lane per point of the pairs' supports,
+    laid end to end over pairs without any point below their ray's outermost
+    emitting one, with one and with more points than a wave has lanes."""
+    P = W.small_lognormal(16, n_src=6, seed=95, nside=nside, n_radial=n_radial)
+    for k, v in over.items():
+        setattr(P.params, k, v)
+    tg = np.sort(np.random.default_rng(96).choice(P.total_cells(), 200, replace=False))
+    f0, i0 = orc_sweep(orc, P, thin=True, targets=tg)
+    g0, j0, st = gpu_sweep(T, P, prec, thin=True, targets=tg, launch=(waves, 0, 2, 0, 0))
+    assert st.buffer_in_lds == 0
+    compare(g0, j0, f0, i0, TOL64 if prec == T.TR_FP64 else TOL32, name=f"N_side {nside} N_R {n_radial} {over}")
