@@ -205,10 +205,10 @@ tr_status tr_set_precision(tr_ctx *c, tr_precision prec);
  * (0 = tuned or default, compare-and-swap; 1 = hardware atomic
  * adds; 2 = compare-and-swap loops on the values' bits) and at 4 waves (2 =
  * compare-and-swap, also the default where 4 waves are the library's own
- * choice; elsewhere hardware atomics).  At N_side 32 and 64 the waves of a
- * target accumulate into FP32 buffers in LDS by compare-and-swap, and buffers in
- * device memory (also 1 or 2 waves, and the radial-kernel variants) are served by
- * 8 waves.  Zeros restore the tuned default.  Results do not depend on the
+ * choice; elsewhere hardware atomics).  From N_side 16 on 4 waves and
+ * more accumulate into FP32 buffers in LDS by compare-and-swap; at N_side 32 and 64
+ * buffers in device memory (also with 1 or 2 waves, and for the radial-kernel
+ * variants) are served by 8 waves.  Zeros restore the tuned default.  Results do not depend on the
  * shape beyond rounding. */
 tr_status tr_set_launch(tr_ctx *c, int32_t waves_per_target, int32_t targets_per_cu, int32_t buffer,
                         int32_t integration, int32_t atomics);

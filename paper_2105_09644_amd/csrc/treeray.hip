@@ -2869,9 +2869,14 @@ size_t sweep_lds_bytes(size_t real, int npix, int rays, int stride_k, int nrm, i
 }
 
 constexpr size_t kLdsMax = 160 * 1024, kLdsGranule = 1280;
-// N_side 32 and 64: marks and ray numbers in device memory (at N_side 16 they
-// take 36 or 60 KB of LDS; N_side 32 would take 144 or 240 KB)
-constexpr int kWidePix = 12 * 32 * 32;
+// From N_side 32 on marks and ray numbers do not fit in LDS (144 or 240 KB); beside
+// ray buffers in LDS they leave it from N_side 16 on, where they take 36 or 60 KB
+// of it (32^3 with 32 points, 1 / 2000 sources: FP32C 3.58 / 78.0 ms with the marks
+// in LDS, 3.15 / 63.6 ms without, FP64 4.49 / 179 against 3.91 / 133; 100 points
+// 9.65 / 256 against 5.18 / 200 and 13.3 / 557 against 10.8 / 432), not at N_side 8
+// (9 or 15 KB: FP32C 1.43 / 15.2 ms against 1.73 / 15.5, FP64 1.97 / 27.8 against
+// 1.85 / 26.5)
+constexpr int kWidePix = 12 * 16 * 16, kWideMemPix = 12 * 32 * 32;
 constexpr size_t kSlabBytes = (size_t)16 << 30;   // most for the ray buffers in device memory
 
 using KernelFn = void (*)(SweepArgs);
@@ -2993,10 +2998,10 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
                 (waves == 8 || waves == 16 ? (am > 0 ? am == 2 : true) : waves == 4 && (am > 0 ? am == 2 : waves_req <= 0));
         if (L.cas) L.fn = pick_kernel_cas(waves, false);
     }
-    // from N_side 32 on the marks of all rays are in device memory; the radial-kernel variants and
-    // 1 or 2 waves (taken as 8) have their ray buffers there too
+    // the radial-kernel variants and 1 or 2 waves have their ray buffers in device memory (8 waves)
+    // where marks and numbers do not fit in LDS
     L.wide = npix >= kWidePix && bm != 2 && !kv && waves >= 4;
-    const bool lds_ok = bm != 2 && (npix < kWidePix || L.wide);
+    const bool lds_ok = bm != 2 && (npix < kWideMemPix || L.wide);
     if (L.wide) {
         L.cas = f32;
         L.fn = f32 ? pick_kernel_wide<float>(waves, false) : pick_kernel_wide<double>(waves, false);
@@ -3033,8 +3038,8 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     L.ldsbuf = occ >= 1;
     if (bm == 1 && !L.ldsbuf) return fail(c, TR_EINVAL, "ray buffers do not fit in LDS for this N_PIX and N_R");
     if (!L.ldsbuf) {
-        L.rays = std::min(npix, kWidePix);
-        L.wide = npix >= kWidePix;
+        L.rays = std::min(npix, kWideMemPix);
+        L.wide = npix >= kWideMemPix;
         L.split = false;
         L.cas = false;
         if (L.wide) L.waves = waves = 8;
