@@ -2963,6 +2963,8 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     const int npix = 12 * c->p.nside * c->p.nside;
     const int nrm = c->nr_max;
     int waves = waves_req;
+    // the radial-kernel variants are built for 4 and 8 waves per target only
+    const bool kv = !((c->p.eps_kernel == 0 || c->p.eps_kernel == 3) && (c->p.mass_kernel == 0 || c->p.mass_kernel == 5));
     if (waves <= 0) {
         waves = c->tuned_waves[f32 ? 1 : 0];
         // Several targets are resident, and the fewer waves share one the better their phases
@@ -2975,13 +2977,16 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
         // N_side 4 all rays' buffers fit 6 targets (the emission rows in device memory).  A list of
         // no more targets than a few a compute unit has nothing to overlap with: 8 waves finish
         // each sooner (1000 targets of 128^3 with their build 0.66 against 0.62 ms).
+        // The radial-kernel variants give all rays buffers: 8 waves (FP64 4 / 8 waves: 48^3 N_side 2
+        // 10.4 / 9.4 ms, 24^3 N_side 8 11.7 / 8.9 ms, 32^3 N_side 4 with 100 points 30.6 / 24.1 ms;
+        // FP32C N_side 8 10.9 / 9.9 ms), but in FP32 4 where few passes hold all rays (N_side 2
+        // 19.0 / 20.0 ms, N_side 4 9.7 / 10.1 ms, with 100 points 27.4 / 26.4 ms).
+        if (waves <= 0 && kv) waves = f32 && npix * nrm <= 192 * 64 && n_items > 4 * (int64_t)c->n_cu ? 4 : 8;
         if (waves <= 0) {
             const int64_t few = (int64_t)(npix >= 192 ? 8 : 16) * c->n_dom;
             waves = n_items > 4 * (int64_t)c->n_cu && ((f32 && npix < 192) || c->n_src_dev <= few) ? 4 : 8;
         }
     }
-    // the radial-kernel variants are built for 4 and 8 waves per target only
-    const bool kv = !((c->p.eps_kernel == 0 || c->p.eps_kernel == 3) && (c->p.mass_kernel == 0 || c->p.mass_kernel == 5));
     if (kv) waves = waves <= 4 ? 4 : 8;
     L.waves = waves;
     int bm = buf_req > 0 ? buf_req : c->tuned_buf[f32 ? 1 : 0];
@@ -3036,6 +3041,12 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
         }
     }
     L.ldsbuf = occ >= 1;
+    // With the radial-kernel variants every pass maps all nodes of the target again: device memory
+    // where passes x points grow beyond these (24^3 FP64: N_side 8 with 64 points (1472) LDS 20.2,
+    // device memory 23.8 ms; 100 points (1700) 34.9 / 30.8; N_side 16 with 32 points (2400) 22.2 /
+    // 14.3; FP32C: N_side 8 with 64 points (704) 17.8 / 20.7; N_side 16 with 32 points (1184)
+    // 13.6 / 12.6; N_side 8 with 100 points (1900) 29.4 / 24.3)
+    if (L.ldsbuf && kv && bm != 1 && (npix + L.rays - 1) / L.rays * nrm > (f32 ? 1000 : 1600)) L.ldsbuf = false;
     if (bm == 1 && !L.ldsbuf) return fail(c, TR_EINVAL, "ray buffers do not fit in LDS for this N_PIX and N_R");
     if (!L.ldsbuf) {
         L.rays = std::min(npix, kWideMemPix);

@@ -711,3 +711,17 @@ def test_device_memory_points(T, orc, nside, n_radial, waves, over, prec):
     g0, j0, st = gpu_sweep(T, P, prec, thin=True, targets=tg, launch=(waves, 0, 2, 0, 0))
     assert st.buffer_in_lds == 0
     compare(g0, j0, f0, i0, TOL64 if prec == T.TR_FP64 else TOL32, name=f"N_side {nside} N_R {n_radial} {over}")
+
+
+@pytest.mark.parametrize("nside,n_radial,prec,in_lds", [(8, 64, 0, True), (8, 100, 0, False), (16, 16, 0, True),
+                                                        (16, 32, 0, False), (8, 64, 1, True), (16, 32, 1, False)])
+def test_kernel_variant_buffers(T, orc, nside, n_radial, prec, in_lds):
+    """Radial-kernel variants on either side of the rule that puts their ray
+    buffers (of all rays) in LDS in passes or in device memory."""
+    P = W.small_lognormal(16, n_src=4, seed=97, nside=nside, n_radial=n_radial)
+    P.params.eps_kernel, P.params.mass_kernel = 5, 6
+    tg = np.sort(np.random.default_rng(98).choice(P.total_cells(), 100, replace=False))
+    f0, i0 = orc_sweep(orc, P, thin=True, targets=tg)
+    g0, j0, st = gpu_sweep(T, P, prec, thin=True, targets=tg)
+    assert (st.buffer_in_lds != 0) == in_lds
+    compare(g0, j0, f0, i0, TOL64 if prec == T.TR_FP64 else TOL32, name=f"variants N_side {nside} N_R {n_radial}")
