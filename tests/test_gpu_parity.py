@@ -725,3 +725,25 @@ def test_kernel_variant_buffers(T, orc, nside, n_radial, prec, in_lds):
     g0, j0, st = gpu_sweep(T, P, prec, thin=True, targets=tg)
     assert (st.buffer_in_lds != 0) == in_lds
     compare(g0, j0, f0, i0, TOL64 if prec == T.TR_FP64 else TOL32, name=f"variants N_side {nside} N_R {n_radial}")
+
+
+@pytest.mark.parametrize("n_dom", [15, 16, 17, 64, 700])
+def test_delta_many_domains(T, orc, n_dom):
+    """Up to 16 domains the median's bins are picked by the last block of a
+    pass, beyond that by a launch: the same medians, in a context and (up to
+    64 domains) without one."""
+    rng = np.random.default_rng(110 + n_dom)
+    A = W.small_lognormal(8, n_src=1, seed=1, nside=1, n_radial=12)
+    P = W.Problem("many", A.domains * n_dom, A.n_h * n_dom, A.src_xyz * n_dom, A.src_q * n_dom, A.params)
+    old = np.exp(20.0 * rng.standard_normal(512 * n_dom))
+    old[::7] = 0.0
+    new = old * (1.0 + 0.1 * rng.standard_normal(old.size)) + 1e-3
+    a, b = torch.tensor(new, device="cuda"), torch.tensor(old, device="cuda")
+    ref = np.array([orc.delta_cell(new[512 * d:512 * d + 512], old[512 * d:512 * d + 512]) for d in range(n_dom)])
+    with T.context_for(P, T.TR_FP64) as ctx:
+        for _ in range(2):   # (the second call finds the first one's scratch)
+            np.testing.assert_allclose(ctx.delta(a, b), ref, rtol=1e-15)
+    if n_dom <= 64:
+        out = torch.zeros(n_dom, dtype=torch.float64, device="cuda")
+        T.delta_noalloc(a, b, 512 * np.arange(n_dom + 1), out)
+        np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=1e-15)
