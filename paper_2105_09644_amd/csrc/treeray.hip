@@ -2786,6 +2786,7 @@ struct tr_ctx {
     uint64_t graph_clock = 0;
     hipStream_t cap_stream = nullptr;
     void *pinned = nullptr;              // host copies of the flags and deltas
+    size_t pinned_bytes = 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
 };
 
@@ -3857,7 +3858,14 @@ tr_status tr_step(tr_ctx *c, const double *n_h, const double *f_prev, double *f_
         LaunchPlan L;
         if ((s = plan_sweep(c, c->n_cells, c->waves, c->tpc, c->bufmode, c->intmode, L))) return s;
         if (!c->cap_stream) HIPCHK(hipStreamCreate(&c->cap_stream));
-        if (!c->pinned) HIPCHK(hipHostMalloc(&c->pinned, 64 + sizeof(unsigned long long) * (size_t)nd));
+        const size_t host = 64 + sizeof(unsigned long long) * (size_t)nd;
+        if (c->pinned_bytes < host) {   // (more domains than any step before: no captured graph writes the old one)
+            if (c->pinned) (void)hipHostFree(c->pinned);
+            c->pinned = nullptr;
+            c->pinned_bytes = 0;
+            HIPCHK(hipHostMalloc(&c->pinned, host));
+            c->pinned_bytes = host;
+        }
         hipStream_t user = c->stream;
         c->stream = c->cap_stream;
         HIPCHK(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeRelaxed));

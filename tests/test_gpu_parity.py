@@ -747,3 +747,47 @@ def test_delta_many_domains(T, orc, n_dom):
         out = torch.zeros(n_dom, dtype=torch.float64, device="cuda")
         T.delta_noalloc(a, b, 512 * np.arange(n_dom + 1), out)
         np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=1e-15)
+
+
+def test_step_after_more_domains(T, orc):
+    """A context that stepped one domain is given 700 (their delta_cell takes
+    more host memory than a page), then one again: every step's fluxes and
+    deltas as those of a fresh context's eager calls."""
+    import ctypes as C
+    A = W.small_lognormal(8, n_src=1, seed=100, nside=1, n_radial=12)
+    B = W.small_lognormal(8, n_src=2, seed=101, nside=1, n_radial=12)
+
+    def step(ctx, probs):
+        nh = torch.tensor(np.concatenate([p.n_h[0] for p in probs]), device="cuda")
+        fp = torch.full((nh.numel(),), 1e8, dtype=torch.float64, device="cuda")
+        out = torch.zeros_like(fp)
+        return ctx.step(nh, fp, out), out.cpu().numpy(), (nh, fp)
+
+    def eager(probs):
+        P = W.Problem("many", [p.domains[0] for p in probs], [p.n_h[0] for p in probs],
+                      [p.src_xyz[0] for p in probs], [p.src_q[0] for p in probs], A.params)
+        with T.context_for(P, T.TR_FP64) as ctx:
+            nh = torch.tensor(np.concatenate(P.n_h), device="cuda")
+            fp = torch.full((nh.numel(),), 1e8, dtype=torch.float64, device="cuda")
+            out = torch.zeros_like(fp)
+            ctx.build(nh, fp)
+            ctx.sweep(out)
+            d = ctx.delta(out, fp)
+            ctx.sync()
+            return d, out.cpu().numpy()
+
+    with T.context_for(A, T.TR_FP64) as ctx:
+        for probs in ([A], [A, B] * 350, [B]):
+            if ctx.n_domains != len(probs) or probs[0] is B:
+                arr = (T._Domain * len(probs))()
+                for i, p in enumerate(probs):
+                    arr[i].nroot[:] = [int(v) for v in p.domains[0].nroot]
+                    arr[i].root_block_cm = float(p.domains[0].root_block_cm)
+                ctx._check(ctx.L.tr_set_domains(ctx.h, len(probs), arr))
+                ctx.n_domains = len(probs)
+                for i, p in enumerate(probs):
+                    ctx.set_sources(i, p.src_xyz[0], p.src_q[0])
+            d, f, _ = step(ctx, probs)
+            d0, f0 = eager(probs)
+            np.testing.assert_allclose(f, f0, rtol=1e-10, atol=1e-12 * f0.max())
+            np.testing.assert_allclose(d, d0, rtol=1e-9)
