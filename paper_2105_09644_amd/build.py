@@ -18,7 +18,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libtreeray.so")
 SOURCES = ["treeray.hip", "topology.cpp"]
-HEADERS = ["kernels.h", "tr_internal.h"]
+HEADERS = ["kernels.h", "tr_internal.h", "chunk.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("TREERAY_ARCH", "gfx950")

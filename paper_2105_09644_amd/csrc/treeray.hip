@@ -20,6 +20,7 @@
 #include <string>
 #include <vector>
 
+#include "chunk.h"
 #include "kernels.h"
 #include "tr_internal.h"
 
@@ -2751,7 +2752,7 @@ struct tr_ctx {
     TargetRec *rec = nullptr;
     int32_t *dyn_pool = nullptr;
     int32_t dyn_units = 0;
-    int64_t list_targets = 0;
+    int64_t list_targets = 0, list_tried = 0;   // targets they hold, and that were asked for
     int32_t *glist = nullptr;            // walk lists of the fallback pass
     int32_t *ovf = nullptr;              // items queued for it
     int64_t ovf_cap = 0;
@@ -2844,7 +2845,7 @@ void free_domains(tr_ctx *c)
     dfree(c->emit_at);
     dfree(c->rec);
     dfree(c->dyn_pool);
-    c->list_targets = 0;
+    c->list_targets = c->list_tried = 0;
     dfree(c->glist);
     dfree(c->ovf);
     c->ovf_cap = 0;
@@ -3120,26 +3121,39 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     L.intm = im > 0 ? im : 3 + (f32 ? 3 : 0);
     if (L.intm >= 6 && !f32) L.intm -= 3;
     L.chunk = std::min<int64_t>(n_items, kListTargets);
-    L.blocks = (int)std::min<int64_t>((int64_t)c->n_cu * L.per_cu, L.chunk);
-    // (a captured step graph holds these too)
-    if (c->list_targets < L.chunk) {
+    // (a captured step graph holds these too.)  Where there is no memory for them, fewer targets at a
+    // time, down to a few a compute unit: 36 KB a target, 1.2 GB for 32768
+    if (c->list_tried < L.chunk) {
         drop_graph(c);
-        dfree(c->lists);
-        dfree(c->emit_at);
-        dfree(c->rec);
-        dfree(c->dyn_pool);
-        c->list_targets = 0;
-        // pairs outside the table: 4% of some 1000 nodes of about 3 (N_side 2) to 12 (N_side 8)
-        // pairs; room for 1024 a target up to N_side 4, 4096 beyond, and a block for every wave
-        c->dyn_units = (int32_t)std::min<int64_t>(
-            (1 << 25) - 1, L.chunk * (c->p.nside <= 4 ? 256 : 1024) + (int64_t)c->n_cu * kWalkPerCu * kWalkWaves * kDynBlock);
-        if (dalloc(c, (void **)&c->lists, sizeof(int2) * (size_t)L.chunk * kListCap) ||
-            dalloc(c, (void **)&c->emit_at, sizeof(uint16_t) * (size_t)L.chunk * kListCap) ||
-            dalloc(c, (void **)&c->rec, sizeof(TargetRec) * (size_t)L.chunk) ||
-            dalloc(c, (void **)&c->dyn_pool, 16 * (size_t)c->dyn_units))
-            return TR_ENOMEM;
-        c->list_targets = L.chunk;
+        auto take = [&](int64_t n) {
+            dfree(c->lists);
+            dfree(c->emit_at);
+            dfree(c->rec);
+            dfree(c->dyn_pool);
+            // pairs outside the table: 4% of some 1000 nodes of about 3 (N_side 2) to 12 (N_side 8)
+            // pairs; room for 1024 a target up to N_side 4, 4096 beyond, and a block for every wave
+            c->dyn_units = (int32_t)std::min<int64_t>(
+                (1 << 25) - 1, n * (c->p.nside <= 4 ? 256 : 1024) + (int64_t)c->n_cu * kWalkPerCu * kWalkWaves * kDynBlock);
+            if (!dalloc(c, (void **)&c->lists, sizeof(int2) * (size_t)n * kListCap) &&
+                !dalloc(c, (void **)&c->emit_at, sizeof(uint16_t) * (size_t)n * kListCap) &&
+                !dalloc(c, (void **)&c->rec, sizeof(TargetRec) * (size_t)n) &&
+                !dalloc(c, (void **)&c->dyn_pool, 16 * (size_t)c->dyn_units))
+                return true;
+            dfree(c->lists);
+            dfree(c->emit_at);
+            dfree(c->rec);
+            dfree(c->dyn_pool);
+            (void)hipGetLastError();
+            return false;
+        };
+        c->list_tried = 0;
+        c->list_targets = take_chunk(L.chunk, std::min<int64_t>(L.chunk, 4 * (int64_t)c->n_cu), take);
+        if (c->list_targets == 0) return TR_ENOMEM;
+        c->list_tried = L.chunk;
+        if (c->list_targets < L.chunk) c->err.clear();
     }
+    L.chunk = std::min(L.chunk, c->list_targets);
+    L.blocks = (int)std::min<int64_t>((int64_t)c->n_cu * L.per_cu, L.chunk);
     if (!c->glist &&
         dalloc(c, (void **)&c->glist, sizeof(int32_t) * (size_t)c->n_cu * kFallbackPerCu * 3 * kGlobalList))
         return TR_ENOMEM;
