@@ -1341,8 +1341,7 @@ __device__ inline unsigned table_entry(const SweepArgs &a, const int4 g, const i
 // source, 60% on 128^3 N_side 2 with 16).  rt: the evaluation points.
 template <typename Real, bool CLASSIFY>
 __device__ void mark_nodes(const SweepArgs &a, unsigned long long *emask, int ew, const int *per, const Real *rt, int nr,
-                           Real rc_inv, int n, unsigned entry, int cnt, int tx, int ty, int tz, int tsize,
-                           uint64_t &guard_count)
+                           Real rc_inv, int n, unsigned entry, int cnt, int tx, int ty, int tz, int tsize)
 {
     using R4 = typename R4T<Real>::T;
     const int lane = here(lane_id());
@@ -1362,7 +1361,9 @@ __device__ void mark_nodes(const SweepArgs &a, unsigned long long *emask, int ew
             mark |= (A.w * u0 != (Real)0 ? 256 : 0) | (A.w * u1 != (Real)0 ? 512 : 0);
         }
     }
-    PairStream<CLASSIFY> ps(lane, entry, CLASSIFY ? __ballot(lane < cnt && entry == kNoEntry) : 0ull);
+    if (CLASSIFY && mark < 256) entry = kNoEntry;   // (the fallback pass lists all nodes)
+    PairStream<CLASSIFY> ps(lane, entry, CLASSIFY ? __ballot(mark >= 256 && entry == kNoEntry) : 0ull);
+    uint64_t guard_count = 0;   // (the mapping counts them)
     for (;;) {
         int node, kc;
         const int fill = ps.next(a, n, per, tx, ty, tz, guard_count, node, kc);
@@ -1701,6 +1702,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
         int *cur = front[wave][0], *nxt = front[wave][1];
         if (lane == 0) cur[0] = D.root;
         int nfr = 1, na = 0, ne = 0;
+        uint64_t t_test = 0, t_tab = 0, t_guard = 0;   // (a walk that does not fit is counted by the fallback pass)
         bool ovf = false;
         while (nfr > 0 && !ovf) {
             int nn = 0;
@@ -1721,7 +1723,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
                     nch = what == 2 ? tp.y : 0;
                     fc = tp.x;
                 }
-                n_test += min(64, nfr - base);
+                t_test += min(64, nfr - base);
                 const uint64_t macc = __ballot(acc_it), me = __ballot(acc_it && (g.w & kSrcBit) != 0);
                 int tot = 0;
                 const int off = wave_excl_scan_dpp(nch, tot);
@@ -1732,7 +1734,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
                 }
                 // the nodes without a table entry, one by one
                 uint64_t todo = __ballot(acc_it && entry == kNoEntry);
-                n_tab += ca - (int)__popcll(todo);
+                t_tab += ca - (int)__popcll(todo);
                 while (todo) {
                     const int j = __ffsll((unsigned long long)todo) - 1;
                     todo &= todo - 1;
@@ -1741,7 +1743,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
                     int kc = 0;
                     const int nd = classify_box(L, a.nside, a.npix, a.guard_tol,
                                                 node_box(a, rdlane(n, j), jg, jsh, r.tx, r.ty, r.tz), r.tx, r.ty, r.tz,
-                                                &a.queue[1], n_guard, kc);
+                                                &a.queue[1], t_guard, kc);
                     const int need = (nd + 3) >> 2;
                     if (dpos + need > dend) {
                         int q = 0;
@@ -1776,7 +1778,12 @@ __global__ __launch_bounds__(kWalkWaves * 64) void k_walk(SweepArgs a)
         }
         r.n_acc = na;
         r.n_emit = ovf ? -1 : ne;
-        n_acc += ovf ? 0 : na;
+        if (!ovf) {
+            n_acc += na;
+            n_test += t_test;
+            n_tab += t_tab;
+            n_guard += t_guard;
+        }
         if (lane == 0) {
             if (a.f32) {
                 const float4 A = ((const float4 *)a.pA)[tnode], B = ((const float4 *)a.pB)[tnode];
@@ -2028,7 +2035,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                         else v = a.lists[x.list + a.emit_at[x.list + e0 + lane]];
                     }
                     mark_nodes<Real, FALLBACK>(a, emask, ew, a.periodic ? D.ext : nullptr, rtg, D.nr, (Real)D.rc_inv, v.x,
-                                               (unsigned)v.y, cnt, x.tx, x.ty, x.tz, x.tsize, n_guard);
+                                               (unsigned)v.y, cnt, x.tx, x.ty, x.tz, x.tsize);
                 }
             }
         }
@@ -2172,6 +2179,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             // 14.2 against 13.5 ms ---
             if (np > 0) {
                 const int lane = here(lane_id());
+                uint64_t p_guard = 0, p_tab = 0;
                 for (int c = wave; c < t.na; c += 64 * WAVES) {
                     const int cnt = min(64, (t.na - c + WAVES - 1) / WAVES);
                     int2 v{0, (int)kNoEntry};
@@ -2180,7 +2188,11 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                         else v = a.lists[t.list + c + WAVES * lane];
                     }
                     map_nodes<Real, ATOMIC, LDSBUF, KV, FALLBACK>(a, R, rinfo, cmask, ew, per, rt, nr, rc_inv, rcoef, v.x,
-                                                          (unsigned)v.y, cnt, t.tx, t.ty, t.tz, t.tsize, n_guard, n_tab);
+                                                          (unsigned)v.y, cnt, t.tx, t.ty, t.tz, t.tsize, p_guard, p_tab);
+                }
+                if (r0 == 0) {   // (the same nodes in every pass)
+                    n_guard += p_guard;
+                    n_tab += p_tab;
                 }
             }
             __syncthreads();

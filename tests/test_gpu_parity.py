@@ -791,3 +791,18 @@ def test_step_after_more_domains(T, orc):
             d0, f0 = eager(probs)
             np.testing.assert_allclose(f, f0, rtol=1e-10, atol=1e-12 * f0.max())
             np.testing.assert_allclose(d, d0, rtol=1e-9)
+
+
+@pytest.mark.parametrize("prec,n_src", [(0, 3), (0, 400), (1, 3)])
+def test_statistics_of_long_walks(T, prec, n_src):
+    """theta = 0 opens every node: each of the targets tests all nodes and
+    accepts all other cells (4095, more than the lists hold: the fallback
+    pass), every one of them of the target's own size and so in the angular
+    table, also where the rays take several passes (400 sources in FP64)."""
+    P = W.small_lognormal(16, n_src=n_src, seed=120, nside=8, n_radial=40)
+    tg = np.arange(0, P.total_cells(), 37)
+    _, _, st = gpu_sweep(T, P, prec, thin=True, targets=tg, theta=0.0)
+    assert st.nodes_accepted == tg.size * (P.total_cells() - 1) and st.nodes_accepted > tg.size * 3072
+    assert st.nodes_tested == tg.size * st.n_nodes
+    assert st.nodes_tabulated == st.nodes_accepted
+    assert st.guard_recomputes == 0
