@@ -530,13 +530,19 @@ __device__ inline void node_shift(const int *per, const int4 g, int tx, int ty, 
     sh[2] = nearest_copy_shift(2 * g.z + size - tz, per[2]);
 }
 
-// distance of a node's (shifted) mass centre from the target
+// Distance of a node's (shifted) mass centre from the target.  The marking and
+// the mapping both take it, and the emission bracket below, and must end on the
+// same two points bit for bit: emission mapped onto an unmarked point would be
+// lost, and with split rows stay in the plane that only the march of the marked
+// points clears.  So the fused operations are written out and the compiler adds
+// none of its own.
 template <typename Real, typename R4>
 __device__ inline Real centre_distance(const R4 A, const int sh[3], int tx, int ty, int tz)
 {
+#pragma clang fp contract(off)
     const Real dx = (A.x + (Real)sh[0]) - (Real)0.5 * (Real)tx, dy = (A.y + (Real)sh[1]) - (Real)0.5 * (Real)ty,
                dz = (A.z + (Real)sh[2]) - (Real)0.5 * (Real)tz;
-    return fsqrt(dx * dx + dy * dy + dz * dz);
+    return fsqrt(__builtin_elementwise_fma(dz, dz, __builtin_elementwise_fma(dx, dx, dy * dy)));
 }
 
 // Per ray, a mask of the points 1 .. N_R - 1 that received emission: ew words
@@ -1156,10 +1162,12 @@ __device__ inline Real emission_weight(int mode, int i, int io, int le, int ne, 
 }
 
 // W_f,3 (App. A.3): the bracket r_i <= d < r_{i+1}, i >= 1, and its two weights
-// (beyond either end all on the end point).  Returns i.
+// (beyond either end all on the end point).  Returns i.  The same bits wherever
+// it is inlined (see centre_distance).
 template <typename Real>
 __device__ inline int emission_bracket(const Real *rt, int nr, Real rc_inv, Real d, Real &u0, Real &u1)
 {
+#pragma clang fp contract(off)
     u0 = 1;
     u1 = 0;
     if (d >= rt[nr - 1]) return nr - 1;
@@ -1169,8 +1177,9 @@ __device__ inline int emission_bracket(const Real *rt, int nr, Real rc_inv, Real
     while (k > 1 && rt[k] > d) --k;
     while (k < nr - 2 && rt[k + 1] <= d) ++k;
     const Real ai = frcp(rt[k] * rt[k]), an = frcp(rt[k + 1] * rt[k + 1]), ad = frcp(d * d);
-    u0 = (ad - an) * frcp(ai - an);
-    u1 = (Real)1 - u0;
+    const Real dn = ad - an, di = frcp(ai - an);
+    u0 = dn * di;
+    u1 = __builtin_elementwise_fma(-dn, di, (Real)1);
     return k;
 }
 

@@ -806,3 +806,27 @@ def test_statistics_of_long_walks(T, prec, n_src):
     assert st.nodes_tested == tg.size * st.n_nodes
     assert st.nodes_tabulated == st.nodes_accepted
     assert st.guard_recomputes == 0
+
+
+@pytest.mark.parametrize("prec,nside,n_radial,split", [(1, 4, 40, True), (1, 2, 60, False), (0, 4, 40, False)])
+def test_marked_and_mapped_points_agree(T, prec, nside, n_radial, split):
+    """The points that the marking gives a target's emission and those that the
+    mapping adds it to are the same: a domain whose sources are 1e13 times
+    fainter than its neighbour's is swept after and beside that one as it is
+    alone (emission left on an unmarked point of the neighbour's, 1e-8 of a
+    source or more, would swamp it).  A lane per ray reads every point."""
+    A = W.small_lognormal(24, n_src=600, seed=130, nside=nside, n_radial=n_radial)
+    B = W.small_lognormal(16, n_src=3, seed=131, nside=nside, n_radial=n_radial)
+    scale = 1e-13
+    both = W.Problem("two", A.domains + B.domains, A.n_h + B.n_h, A.src_xyz + B.src_xyz,
+                     [A.src_q[0], scale * B.src_q[0]], A.params)
+    n_a = A.total_cells()
+    for integration in (1, 0):
+        alone, _, _ = gpu_sweep(T, B, prec, thin=True, launch=(4, 0, 0, integration, 2))
+        rng = np.random.default_rng(132)
+        tg = rng.permutation(both.total_cells())   # the domains' targets follow each other in a workgroup
+        f, _, st = gpu_sweep(T, both, prec, thin=True, targets=tg, launch=(4, 0, 0, integration, 2))
+        assert (st.buffer_in_lds == 2) == split
+        g = np.empty_like(f)
+        g[tg] = f
+        np.testing.assert_allclose(g[n_a:], scale * alone, rtol=1e-3 if prec == 1 else 1e-9)
