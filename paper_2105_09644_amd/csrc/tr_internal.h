@@ -20,7 +20,7 @@ constexpr int kMaxLevels = 24;
 constexpr int kListCap = 3072;         // accepted nodes listed per target, and
 constexpr int kListTargets = 1 << 15;  // targets walked and listed at a time (1 GB of lists)
 constexpr int kWalkFront = 1024;       // frontier entries of a walk in LDS
-constexpr int kWalkPerCu = 5;          // workgroups per compute unit of the walk kernel
+constexpr int kWalkPerCu = 4;          // workgroups per compute unit of the walk kernel
 constexpr int kGlobalList = 1 << 16;   // frontier / accepted-list entries of the fallback walk
 constexpr int kFallbackPerCu = 2;       // workgroups per compute unit in the fallback pass
 constexpr int kGlNodes = 24;            // Gauss-Legendre nodes of the sphere-deposit quadrature

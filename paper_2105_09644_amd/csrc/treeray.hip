@@ -1666,8 +1666,11 @@ __device__ inline void queue_overflow(const SweepArgs &a, bool fallback, int64_t
 // sub-points are classified here and the pairs go to the chunk's pool, of
 // which a wave takes 256 units of 4 pairs at a time.  A walk is a chain of
 // dependent node reads (a level at a time), so it is bound by latency: in a
-// kernel of its own many walks hide each other's (5 workgroups of 4 waves per
-// compute unit by the frontiers' 32 KB), where inside the sweep one target's
+// kernel of its own many walks hide each other's (4 workgroups of 4 waves per
+// compute unit: the frontiers' 32768 B are 33280 in the LDS granule of 1280, so
+// a fifth does not fit, and launched it ran alone at the end with its share of
+// the targets: sweeps of 128^3 N_side 2 FP32C 112.9 ms with 5 against 106.1 with
+// 4, 64^3 N_side 4 10.7 / 10.1, adaptive 72.0 / 67.0), where inside the sweep one target's
 // walk held up the others' barrier; and the sweep is rid of the classifier,
 // whose FP64 guard costs it registers.
 constexpr int kWalkWaves = 4;
