@@ -3475,6 +3475,7 @@ tr_status build_angular_table(tr_ctx *c)
             dfree(c->atab_idx);
             if (ratios == 1) return st;
             (void)hipGetLastError();   // no memory for it: without the largest ratio
+            c->err.clear();
             continue;
         }
         hipError_t e = hipMemcpyAsync(sums, h.data(), sizeof(int64_t) * (size_t)waves, hipMemcpyHostToDevice, c->stream);

@@ -808,8 +808,8 @@ def test_statistics_of_long_walks(T, prec, n_src):
     assert st.guard_recomputes == 0
 
 
-@pytest.mark.parametrize("prec,nside,n_radial,split", [(1, 4, 40, True), (1, 2, 60, False), (0, 4, 40, False)])
-def test_marked_and_mapped_points_agree(T, prec, nside, n_radial, split):
+@pytest.mark.parametrize("prec,nside,n_radial", [(1, 4, 40), (1, 2, 60), (0, 4, 40)])
+def test_marked_and_mapped_points_agree(T, prec, nside, n_radial):
     """The points that the marking gives a target's emission and those that the
     mapping adds it to are the same: a domain whose sources are 1e13 times
     fainter than its neighbour's is swept after and beside that one as it is
@@ -826,7 +826,54 @@ def test_marked_and_mapped_points_agree(T, prec, nside, n_radial, split):
         rng = np.random.default_rng(132)
         tg = rng.permutation(both.total_cells())   # the domains' targets follow each other in a workgroup
         f, _, st = gpu_sweep(T, both, prec, thin=True, targets=tg, launch=(4, 0, 0, integration, 2))
-        assert (st.buffer_in_lds == 2) == split
+        assert (st.buffer_in_lds == 2) == (prec == 1)   # split rows in FP32
         g = np.empty_like(f)
         g[tg] = f
         np.testing.assert_allclose(g[n_a:], scale * alone, rtol=1e-3 if prec == 1 else 1e-9)
+
+
+def test_table_without_its_largest_ratio(T, orc):
+    """N_side 8 with s = 4 on 80^3: the pairs of nodes of 32 target sizes (15
+    million offsets) do not fit the entries' 25 bits, and the table does
+    without them: the walk classifies those nodes, with the same weights."""
+    P = W.small_lognormal(80, n_src=5, seed=140, nside=8, n_radial=40)
+    P.params.subsample = 4
+    tg = np.sort(np.random.default_rng(141).choice(P.total_cells(), 200, replace=False))
+    f0, i0 = orc_sweep(orc, P, thin=True, targets=tg)
+    for prec, tol in ((T.TR_FP64, TOL64), (T.TR_FP32C, TOL32)):
+        with T.context_for(P, prec) as ctx:
+            assert ctx.L.tr_last_error(ctx.h) == b""
+            ctx.build(torch.tensor(P.n_h[0], device="cuda"), thin=True)
+            out = torch.zeros(tg.size, dtype=torch.float64, device="cuda")
+            ion = torch.zeros(tg.size, dtype=torch.uint8, device="cuda")
+            ctx.sweep_targets(torch.tensor(tg, device="cuda"), out, ion)
+            ctx.sync()
+            st = ctx.stats()
+            # a few nodes of 32 target sizes a target (grids of 80 cells hold 3 of them an axis)
+            assert 0 < st.nodes_accepted - st.nodes_tabulated < 40 * tg.size
+            compare(out.cpu().numpy(), ion.cpu().numpy(), f0, i0, tol, name=f"table prec {prec}")
+
+
+def test_pool_of_pairs_used_up(T, orc):
+    """A coarse target beside refined blocks accepts some 500 nodes finer than
+    itself, which no table holds; at N_side 32 their pairs take several times
+    its share of the chunk's pool, so 600 such targets use it up and the rest
+    are walked by the fallback pass."""
+    P = W.small_amr(2, seed=3, threshold=150.0, nside=32)
+    dom, theta = P.domains[0], 0.3
+    lo, size = W.cell_lo_size(dom)
+    coarse = np.nonzero(size == 2)[0]
+    c = int(coarse[1200])
+    ls, _ = orc.accepted(dom, P.params, P.n_h[0], P.src_xyz[0], P.src_q[0], c, theta=theta)
+    fine = ls[ls[:, 3] == 1]
+    xt = lo[c] + 0.5 * size[c]
+    units = sum(-(-len(orc.node_pixels(32, P.params.subsample, b[:3], b[:3] + 1, xt)) // 4) for b in fine)
+    n = 600
+    pool = n * 1024 + torch.cuda.get_device_properties(0).multi_processor_count * 16 * 256
+    assert len(ls) < 3072 and n * units > 1.2 * pool   # the lists would hold the walk, the pool does not
+    tg = np.full(n, c, np.int64)
+    f0, i0 = orc_sweep(orc, P, thin=True, targets=tg[:1], theta=theta)
+    for prec, tol in ((T.TR_FP64, TOL64), (T.TR_FP32C, TOL32)):
+        g, j, st = gpu_sweep(T, P, prec, thin=True, targets=tg, theta=theta)
+        assert st.overflow == 0 and st.nodes_accepted == n * len(ls)
+        compare(g, j, np.repeat(f0, n), np.repeat(i0, n), tol, name=f"pool prec {prec}")
