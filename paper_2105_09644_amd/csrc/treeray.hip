@@ -542,7 +542,7 @@ __device__ inline Real centre_distance(const R4 A, const int sh[3], int tx, int 
 #pragma clang fp contract(off)
     const Real dx = (A.x + (Real)sh[0]) - (Real)0.5 * (Real)tx, dy = (A.y + (Real)sh[1]) - (Real)0.5 * (Real)ty,
                dz = (A.z + (Real)sh[2]) - (Real)0.5 * (Real)tz;
-    return fsqrt(__builtin_elementwise_fma(dz, dz, __builtin_elementwise_fma(dx, dx, dy * dy)));
+    return fsqrt(__builtin_elementwise_fma(dz, dz, __builtin_elementwise_fma(dy, dy, dx * dx)));
 }
 
 // Per ray, a mask of the points 1 .. N_R - 1 that received emission: ew words
