@@ -2813,6 +2813,8 @@ struct tr_ctx {
     void *pinned = nullptr;              // host copies of the flags and deltas
     size_t pinned_bytes = 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    // the sweep kernels that this context has asked about: workgroups a compute unit by their registers
+    std::vector<std::pair<const void *, int>> kernels;
 };
 
 namespace {
@@ -3018,6 +3020,101 @@ struct LaunchPlan {
 // lanes that integrate one ray in integration mode m
 inline int lanes_per_ray(int m) { return m == 2 ? 64 : (m >= 3 ? 4 << ((m - 3) % 3) : 1); }
 
+// Workgroups a compute unit by their LDS (the runtime's own figure leaves out the granule)
+int targets_by_lds(size_t lds) { return (int)(kLdsMax / ((lds + kLdsGranule - 1) / kLdsGranule * kLdsGranule)); }
+
+// Workgroups a compute unit by the kernel's registers, asked of the runtime once a
+// context (as is the leave to use all of LDS): a plan asks about up to three kernels.
+tr_status targets_by_registers(tr_ctx *c, KernelFn fn, int waves, int &n)
+{
+    for (const auto &k : c->kernels)
+        if (k.first == (const void *)fn) {
+            n = k.second;
+            return TR_OK;
+        }
+    HIPCHK(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
+    HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)fn, waves * 64, 0));
+    c->kernels.emplace_back((const void *)fn, n);
+    return TR_OK;
+}
+
+// Ray buffers: a target's rays that hold emission (KV: all) are mapped and integrated as
+// many at a time as there are buffers.  Four rows per ray (odd stride: ray k of lane k hits
+// distinct banks), or in FP32 the A, E, V rows in LDS and the emission rows in device memory
+// where that holds more rays.  As many targets share a compute unit as the registers allow,
+// fewer while that leaves a target less than `want` buffers: as many as rays that probably
+// hold emission, between 16 and 32 (4 waves, targets a compute unit with 16 / with 32:
+// 48^3 N_side 4, 64 points FP64 2 sources 4 / 2 targets 6.3 / 9.1 ms, 8 sources 14.6 / 12.8;
+// 100 points FP32C 2 sources 6 / 3 targets 6.0 / 8.7, 16 sources 19.0 / 18.4; N_side 2, 64
+// points FP64 2 sources 4 / 2 targets 5.7 / 8.3, 32 sources 12.5 / 11.4); below 16 for one
+// target alone, all buffers are in device memory.
+struct LdsFit {
+    int targets = 0, rays = 0;   // a compute unit, a target
+    bool split = false;
+};
+
+tr_status fit_lds(tr_ctx *c, KernelFn fn, bool f32, int npix, int nrm, int waves, int tpc_req, bool wide, bool may_split,
+                  int want, LdsFit &F)
+{
+    const size_t real = f32 ? 4 : 8;
+    const size_t fixed = sweep_lds_bytes(real, npix, 0, 0, nrm, waves, true, wide);
+    if (fixed >= kLdsMax) return TR_OK;
+    tr_status s = targets_by_registers(c, fn, waves, F.targets);
+    if (s) return s;
+    if (tpc_req > 0) F.targets = std::min(F.targets, tpc_req);
+    for (; F.targets >= 1; --F.targets) {
+        const size_t room = kLdsMax / (size_t)F.targets / kLdsGranule * kLdsGranule;
+        auto fit = [&](int stride) {
+            if (sweep_lds_bytes(real, npix, npix, stride, nrm, waves, true, wide) <= room) return npix;
+            const size_t each = (size_t)stride * real + 8 * (nrm > 64 ? 2 : 1);
+            return room <= fixed + 16 ? 0 : std::min(npix, (int)((room - fixed - 16) / each));
+        };
+        const int r4 = fit(4 * nrm + 1), r3 = may_split ? fit(3 * nrm + 1) : 0;
+        F.split = r4 < npix && r3 > r4;
+        F.rays = F.split ? r3 : r4;
+        if (F.rays >= std::min(npix, F.targets > 1 ? want : 16)) break;
+    }
+    return TR_OK;
+}
+
+// Rays of a target that probably hold emission: a source puts it on as many rays as
+// a node has pixels, about (1 + 0.34 N_side)^2, at random.  Sphere sources count one
+// each: from most targets they are a few nodes.
+double lit_rays(const tr_ctx *c, int npix)
+{
+    const double each = (1.0 + 0.34 * c->p.nside) * (1.0 + 0.34 * c->p.nside);
+    return npix * (1.0 - std::exp(-each * c->n_src_dev / c->n_dom / npix));
+}
+
+int want_buffers(double lit) { return (int)std::min(32.0, std::max(16.0, lit)); }
+
+// 4 or 8 waves per target where the caller leaves it open.  Several targets are
+// resident, and the fewer waves share one the better their phases overlap (64^3
+// N_side 2 FP32C: 6 targets of 4 waves 9.9 ms, 2 of 8 waves 13.6), as long as a
+// target's rays with emission fit its share of the buffers; beyond that 8 waves
+// on fewer targets save passes.  4 waves while those rays need 1.25 buffers at most
+// (FP32 1.5; 0.75 where only 3 targets of 4 waves fit; never where fewer do), 4 / 8
+// waves on either side (rays a buffer):
+//   64^3 N_side 4, 32 points  FP32C 16 sources (1.2) 16.1 / 18.5 ms, 32 (1.9) 21.2 / 21.0
+//                             FP64 8 (1.2) 15.5 / 17.8, 16 (2.0) 25.1 / 20.4
+//   64^3 N_side 2, 32 points  FP64 32 (1.2) 15.8 / 18.0, 256 (1.4) 24.2 / 23.9, 2000 30.6 / 28.8
+//   48^3 N_side 4, 64 points  FP32C 4 (0.5) 5.9 / 8.3, 16 (1.8) 10.8 / 9.9; FP64 (2 targets) 4 10.0 / 9.2
+//   32^3 N_side 8, 32 points  FP32C 1 (0.3) 1.38 / 1.95, 8 (2.5) 2.94 / 2.49
+//   48^3 N_side 4, a sphere of 8 / 12 cells: FP64 7.7 / 8.1 and 10.7 / 10.1, FP32C 6.0 / 7.4 and 7.8 / 9.2
+tr_status default_waves(tr_ctx *c, bool f32, int npix, int nrm, int tpc_req, int &waves)
+{
+    const bool wide = npix >= kWidePix;
+    const KernelFn fn = wide ? (f32 ? pick_kernel_wide<float>(4, false) : pick_kernel_wide<double>(4, false))
+                             : f32 ? pick_kernel_cas(4, false) : pick_kernel<double>(4, true, false);
+    const double lit = lit_rays(c, npix);
+    LdsFit F;
+    tr_status s = fit_lds(c, fn, f32, npix, nrm, 4, tpc_req, wide, f32, want_buffers(lit), F);
+    if (s) return s;
+    const double room = F.targets >= 4 ? (f32 ? 1.5 : 1.25) : F.targets == 3 ? 0.75 : 0.0;
+    waves = lit <= room * F.rays || (F.rays == npix && F.targets >= 3) ? 4 : 8;
+    return TR_OK;
+}
+
 tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int buf_req, int int_req, LaunchPlan &L,
                      int atom_req = 0)
 {
@@ -3025,34 +3122,35 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
     const size_t real = f32 ? 4 : 8;
     const int npix = 12 * c->p.nside * c->p.nside;
     const int nrm = c->nr_max;
+    tr_status s;
     int waves = waves_req;
+    int bm = buf_req > 0 ? buf_req : c->tuned_buf[f32 ? 1 : 0];
     // the radial-kernel variants are built for 4 and 8 waves per target only
     const bool kv = !((c->p.eps_kernel == 0 || c->p.eps_kernel == 3) && (c->p.mass_kernel == 0 || c->p.mass_kernel == 5));
+    if (waves <= 0) waves = c->tuned_waves[f32 ? 1 : 0];
     if (waves <= 0) {
-        waves = c->tuned_waves[f32 ? 1 : 0];
-        // Several targets are resident, and the fewer waves share one the better their phases
-        // overlap (128^3 N_side 2 FP32C, 16 sources: 6 targets of 4 waves 120 ms, 2 of 8 waves
-        // 164 ms), as long as a target's rays with emission fit its share of the buffers at once:
-        // with many sources most rays hold emission, and 8 waves on fewer targets save passes
-        // (N_side 4, FP32C / FP64: one source on 64^3, 4 waves 13.5 / 18.2 ms, 8 waves 18.2 /
-        // 20.1 ms; 200 / 60 sources on an adaptive grid 80 / 31.5 ms against 69 / 27.5 ms; N_side 2
-        // FP64, one source 7.9 against 10.0 ms, 1000 sources 63.5 against 60.0 ms).  In FP32 below
-        // N_side 4 all rays' buffers fit 6 targets (the emission rows in device memory).  A list of
-        // no more targets than a few a compute unit has nothing to overlap with: 8 waves finish
-        // each sooner (1000 targets of 128^3 with their build 0.66 against 0.62 ms).
-        // The radial-kernel variants give all rays buffers: 8 waves (FP64 4 / 8 waves: 48^3 N_side 2
-        // 10.4 / 9.4 ms, 24^3 N_side 8 11.7 / 8.9 ms, 32^3 N_side 4 with 100 points 30.6 / 24.1 ms;
-        // FP32C N_side 8 10.9 / 9.9 ms), but in FP32 4 where few passes hold all rays (N_side 2
-        // 19.0 / 20.0 ms, N_side 4 9.7 / 10.1 ms, with 100 points 27.4 / 26.4 ms).
-        if (waves <= 0 && kv) waves = f32 && npix * nrm <= 192 * 64 && n_items > 4 * (int64_t)c->n_cu ? 4 : 8;
-        if (waves <= 0) {
-            const int64_t few = (int64_t)(npix >= 192 ? 8 : 16) * c->n_dom;
-            waves = n_items > 4 * (int64_t)c->n_cu && ((f32 && npix < 192) || c->n_src_dev <= few) ? 4 : 8;
+        // A list of no more targets than a few a compute unit has nothing to overlap with: 8 waves
+        // finish each sooner (64^3 N_side 4 FP32C, 4 sources, 4 / 8 waves: 256 targets 0.109 /
+        // 0.097 ms, 1000 0.165 / 0.160, 2048 0.262 / 0.256, 4096 0.398 / 0.430).
+        waves = 8;
+        if (n_items > 4 * (int64_t)c->n_cu) {
+            if (kv) {
+                // All rays have buffers: 8 waves (FP64 4 / 8 waves: 48^3 N_side 2 10.4 / 9.4 ms, 24^3
+                // N_side 8 11.7 / 8.9 ms, 32^3 N_side 4 with 100 points 30.6 / 24.1 ms; FP32C N_side 8
+                // 10.9 / 9.9 ms; N_side 2 with buffers in device memory 55.0 / 50.0 ms), but in FP32 4
+                // where few passes hold all rays (N_side 2 19.0 / 20.0 ms, N_side 4 9.7 / 10.1 ms, with
+                // 100 points 27.4 / 26.4 ms).
+                if (f32 && bm != 2 && npix * nrm <= 192 * 64) waves = 4;
+            } else if (bm == 2) {
+                // (32^3 N_side 4 with 4 sources FP32C 5.6 / 6.4 ms, 48^3 N_side 2 with 60 33.2 / 30.9 ms)
+                if (c->n_src_dev <= 16 * c->n_dom) waves = 4;
+            } else if ((s = default_waves(c, f32, npix, nrm, tpc_req, waves))) {
+                return s;
+            }
         }
     }
     if (kv) waves = waves <= 4 ? 4 : 8;
     L.waves = waves;
-    int bm = buf_req > 0 ? buf_req : c->tuned_buf[f32 ? 1 : 0];
     if (kv) {
         L.fn = f32 ? pick_kernel_kv<float>(waves, bm != 2, false) : pick_kernel_kv<double>(waves, bm != 2, false);
     } else {
@@ -3074,36 +3172,13 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
         L.cas = f32;
         L.fn = f32 ? pick_kernel_wide<float>(waves, false) : pick_kernel_wide<double>(waves, false);
     }
-    // Ray buffers: a target's rays that hold emission (KV: all) are mapped and integrated as
-    // many at a time as there are buffers.  Four rows per ray (odd stride: ray k of lane k hits
-    // distinct banks), or in FP32 the A, E, V rows in LDS and the emission rows in device memory
-    // where that holds more rays.  As many targets share a compute unit as the registers allow,
-    // fewer while that leaves a target less than 32 buffers; below 16 for one target alone, all
-    // buffers are in device memory.
     const int stride4 = 4 * nrm + 1, stride3 = 3 * nrm + 1;
-    int occ = 0;
-    const size_t fixed = sweep_lds_bytes(real, npix, 0, stride4, nrm, waves, true, L.wide);
-    if (lds_ok && fixed < kLdsMax) {
-        HIPCHK(hipFuncSetAttribute((const void *)L.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
-        HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void *)L.fn, waves * 64, 0));
-        if (tpc_req > 0) occ = std::min(occ, tpc_req);
-        for (; occ >= 1; --occ) {
-            const size_t room = kLdsMax / (size_t)occ / kLdsGranule * kLdsGranule;
-            auto fit = [&](int stride) {
-                int r = npix;
-                if (sweep_lds_bytes(real, npix, r, stride, nrm, waves, true, L.wide) > room) {
-                    r = room <= fixed + 16 ? 0 : (int)((room - fixed - 16) / ((size_t)stride * real + 8 * (nrm > 64 ? 2 : 1)));
-                    r = std::min(r, npix);
-                }
-                return r;
-            };
-            const int r4 = fit(stride4), r3 = f32 && !kv ? fit(stride3) : 0;
-            L.split = r4 < npix && r3 > r4;
-            L.rays = L.split ? r3 : r4;
-            if (L.rays >= std::min(npix, occ > 1 ? 32 : 16)) break;
-        }
-    }
-    L.ldsbuf = occ >= 1;
+    LdsFit fit;
+    const int want = kv ? 32 : want_buffers(lit_rays(c, npix));
+    if (lds_ok && (s = fit_lds(c, L.fn, f32, npix, nrm, waves, tpc_req, L.wide, f32 && !kv, want, fit))) return s;
+    L.split = fit.split;
+    L.rays = fit.rays;
+    L.ldsbuf = fit.targets >= 1;
     // With the radial-kernel variants every pass maps all nodes of the target again: device memory
     // where passes x points grow beyond these (24^3 FP64: N_side 8 with 64 points (1472) LDS 20.2,
     // device memory 23.8 ms; 100 points (1700) 34.9 / 30.8; N_side 16 with 32 points (2400) 22.2 /
@@ -3127,12 +3202,13 @@ tr_status plan_sweep(tr_ctx *c, int64_t n_items, int waves_req, int tpc_req, int
                     : kv ? (f32 ? pick_kernel_kv<float>(waves, L.ldsbuf, true) : pick_kernel_kv<double>(waves, L.ldsbuf, true))
                          : (f32 ? pick_kernel<float>(waves, L.ldsbuf, true) : pick_kernel<double>(waves, L.ldsbuf, true));
     L.stride_k = L.split ? stride3 : stride4;
+    int occ = 0;
     L.lds = sweep_lds_bytes(real, npix, L.rays, L.stride_k, nrm, waves, L.ldsbuf, L.wide);
     if (L.lds > kLdsMax)
         return fail(c, TR_EINVAL, "sweep kernel does not fit on a compute unit (LDS " + std::to_string(L.lds) + " B)");
-    HIPCHK(hipFuncSetAttribute((const void *)L.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.lds));
-    HIPCHK(hipFuncSetAttribute((const void *)L.fn_fb, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.lds));
-    HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void *)L.fn, waves * 64, L.lds));
+    int fb = 0;
+    if ((s = targets_by_registers(c, L.fn, waves, occ)) || (s = targets_by_registers(c, L.fn_fb, waves, fb))) return s;
+    occ = std::min(occ, targets_by_lds(L.lds));
     if (occ <= 0) return fail(c, TR_EINVAL, "sweep kernel does not fit on a compute unit (LDS " + std::to_string(L.lds) + " B)");
     L.per_cu = tpc_req > 0 ? std::min(tpc_req, occ) : occ;
     if (!L.ldsbuf)   // (N_side 32: 6 to 50 MB a workgroup)
