@@ -352,7 +352,6 @@ struct SweepArgs {
     const float *r32;
     const int64_t *targets;  // explicit target list, or NULL
     const int32_t *order;    // all cells in (domain, Morton) order
-    int64_t n_items;
     int64_t n_cells;
     // the chunk of the work items [item0, item0 + n_chunk) whose walks are
     // listed: target i's accepted nodes at lists[i list_cap ..], each with where
@@ -457,23 +456,10 @@ __device__ inline unsigned lds_swap(unsigned *q, unsigned expected, unsigned des
                                          __HIP_MEMORY_SCOPE_WORKGROUP);
     return expected;   // what the word held
 }
-template <typename Real, int AM>
+template <typename Real>
 __device__ inline void buf_add(Real *p, Real v)
 {
-    if constexpr (AM == 2 && sizeof(Real) == 4) {
-        unsigned *q = (unsigned *)p;
-        unsigned old = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        for (;;) {
-            unsigned seen = old;
-            const unsigned nv = __float_as_uint(__uint_as_float(old) + v);
-            if (__hip_atomic_compare_exchange_strong(q, &seen, nv, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_WORKGROUP))
-                break;
-            old = seen;
-        }
-    } else {
-        __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Three adds at once (A, E, V of one ray point): wk x0, wk x1, wk x2.  In the
@@ -504,9 +490,9 @@ __device__ inline void buf_add3(Real wk, Real *p0, Real x0, Real *p1, Real x1, R
             x2 = d2 ? 0.0f : x2;
         }
     } else {
-        buf_add<Real, AM>(p0, wk * x0);
-        buf_add<Real, AM>(p1, wk * x1);
-        buf_add<Real, AM>(p2, wk * x2);
+        buf_add<Real>(p0, wk * x0);
+        buf_add<Real>(p1, wk * x1);
+        buf_add<Real>(p2, wk * x2);
     }
 }
 
@@ -1533,7 +1519,7 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, const unsi
                 const Real wq = emission_weight<Real>(jemode, jlo + io, i0 + io, jle, jne, jea, jeb, jfb, rcoef, jd, jhinv,
                                                       a.eps_kernel == K_G) * jqeps;
                 if (wq != (Real)0) {
-                    buf_add<Real, 1>(&R.eps(k, jlo + io), wk * wq);
+                    buf_add<Real>(&R.eps(k, jlo + io), wk * wq);
                     mark_points(cmask + (size_t)k * ew, jlo + io, true, false);
                 }
             }
@@ -1586,8 +1572,8 @@ __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, const unsi
             if (valid && ((npk >> 24) & 1)) {
                 const int jie = (npk >> 16) & 255;
                 Real *row = &R.eps(k, jie);
-                if (je0 != (Real)0) buf_add<Real, 1>(row, wk * je0);
-                if (je1 != (Real)0) buf_add<Real, 1>(row + 1, wk * je1);
+                if (je0 != (Real)0) buf_add<Real>(row, wk * je0);
+                if (je1 != (Real)0) buf_add<Real>(row + 1, wk * je1);
                 if (KV) mark_points(cmask + (size_t)k * ew, jie, je0 != (Real)0, je1 != (Real)0);
             }
         }
@@ -3332,7 +3318,6 @@ tr_status launch_sweep(tr_ctx *c, const int64_t *targets, int64_t n, double *f_o
     a.r32 = c->r32;
     a.targets = targets;
     a.order = c->order;
-    a.n_items = n;
     a.n_cells = c->n_cells;
     a.f_out = f_out;
     a.ion_out = ion;
