@@ -2476,14 +2476,14 @@ __global__ __launch_bounds__(256) void k_atab(AtabGeom G, int ns, int s, float g
 // bits of neighbouring values are mostly equal, and lanes that meet on a bin
 // are served one by one); the last block to finish picks every domain's bin.
 // 8M cells of 7 domains: 1316 us with 8 bits a pass, a lookup per cell and a
-// launch for every pick, 162 us now (189 us with bins by lane in the pick; then two
+// launch for every pick, 151 us now (189 us with 32 bins by lane in the pick; then two
 // blocks a compute unit took 223 us and 512 threads a block 195 us: each block's fence
 // writes an L2 back).
 // ---------------------------------------------------------------------------
 constexpr int kSelBits = 11, kSelBins = 1 << kSelBits, kSelPasses = 6, kSelCopies = 4, kSelThreads = 1024;
 // The picks by the last block up to a domain a wave, beyond that in a launch of
 // their own: with the last block alone 512 domains of 512 cells took 4.2 ms and 64
-// of 4096 0.60 ms, now 0.16 and 0.11 ms; 16 domains have no more picks than the
+// of 4096 0.60 ms, now 0.15 and 0.10 ms; 16 domains have no more picks than the
 // block has waves, and a launch after each of the six passes would cost more
 constexpr int kSelPickWaves = kSelThreads / 64;
 __host__ __device__ inline int select_shift(int pass) { return pass < 5 ? 64 - kSelBits * (pass + 1) : 0; }
@@ -2545,10 +2545,23 @@ __device__ inline void block_run(int64_t n_cells, int64_t &lo, int64_t &hi)
     hi = lo + per < n_cells ? lo + per : n_cells;
 }
 
-// The bin of domain d that holds its median, by a wave: 32 rows of 64 bins, the
-// row by the rows' totals, the bin by a scan of the row.  Leaves the histogram
-// zero.  Counts are summed in halves of 16 bits, so that a row may hold 2^32
-// cells and more.
+// Sum of v over the lanes, and below: over the lanes below this one.  BIG: sums of
+// 2^32 and more, in halves of 16 bits.
+template <bool BIG>
+__device__ inline unsigned long long wave_total(unsigned v, unsigned long long &below)
+{
+    int lo, hi = 0, h = 0;
+    const int l = wave_excl_scan_dpp((int)(BIG ? v & 0xffffu : v), lo);
+    if (BIG) h = wave_excl_scan_dpp((int)(v >> 16), hi);
+    below = ((unsigned long long)(unsigned)h << 16) + (unsigned)l;
+    return ((unsigned long long)(unsigned)hi << 16) + (unsigned)lo;
+}
+
+// The bin of domain d that holds its median, by a wave: 32 rows of 64 bins (whole
+// cache lines, which other blocks wrote: four bins a lane took 8M cells of 7
+// domains from 160 to 205 us), the row by the rows' totals, the bin by a scan of
+// the row.  Leaves the histogram zero.
+template <bool BIG>
 __device__ inline void pick_bin(const SelectState &st, int d, int shift)
 {
     constexpr int kRows = kSelBins / 64;
@@ -2557,41 +2570,35 @@ __device__ inline void pick_bin(const SelectState &st, int d, int shift)
     unsigned v[kRows];
 #pragma unroll
     for (int q = 0; q < kRows; ++q) v[q] = __hip_atomic_load(&hd[64 * q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned long long k = st.rank[d];
-    int row = kRows - 1;
-    unsigned mine = v[kRows - 1];
+    unsigned long long k = st.rank[d], below;
+    int row = 0;
+    unsigned mine = 0;
     bool found = false;
 #pragma unroll
     for (int q = 0; q < kRows; ++q) {
         hd[64 * q] = 0;
-        int lo, hi;
-        (void)wave_excl_scan_dpp((int)(v[q] & 0xffffu), lo);
-        (void)wave_excl_scan_dpp((int)(v[q] >> 16), hi);
-        const unsigned long long tot = ((unsigned long long)(unsigned)hi << 16) + (unsigned)lo;
-        if (!found) {
-            if (k < tot) {
-                found = true;
-                row = q;
-                mine = v[q];
-            } else if (q + 1 < kRows) {
-                k -= tot;
-            }
+        const unsigned long long tot = wave_total<BIG>(v[q], below);
+        if (!found) {   // (uniform)
+            found = k < tot;
+            row = q;
+            mine = v[q];
+            k -= found ? 0 : tot;
         }
     }
-    int lo, hi;
-    const int l = wave_excl_scan_dpp((int)(mine & 0xffffu), lo), h = wave_excl_scan_dpp((int)(mine >> 16), hi);
-    const unsigned long long before = ((unsigned long long)(unsigned)h << 16) + (unsigned)l;
-    if (k >= before && k < before + mine) {   // one lane
-        st.rank[d] = k - before;
+    (void)wave_total<BIG>(mine, below);
+    if (k >= below && k < below + mine) {   // one lane
+        st.rank[d] = k - below;
         st.prefix[d] |= (unsigned long long)(64 * row + lane) << shift;
     }
 }
 
 // The picks of more domains than the last block of k_select has waves
-__global__ __launch_bounds__(256) void k_pick(int n_dom, int pass, SelectState st)
+__global__ __launch_bounds__(256) void k_pick(int n_dom, int64_t n_cells, int pass, SelectState st)
 {
     const int d = (int)blockIdx.x * 4 + uniform((int)(threadIdx.x >> 6));
-    if (d < n_dom) pick_bin(st, d, select_shift(pass));
+    if (d >= n_dom) return;
+    if (n_cells >> 32) pick_bin<true>(st, d, select_shift(pass));
+    else pick_bin<false>(st, d, select_shift(pass));
 }
 
 template <typename Doms>
@@ -2653,7 +2660,10 @@ __global__ __launch_bounds__(kSelThreads) void k_select(Doms D, int64_t n_cells,
     __syncthreads();
     if (!is_last) return;
     const int d = uniform(tid >> 6);
-    if (d < D.n) pick_bin(st, d, shift);
+    if (d < D.n) {
+        if (n_cells >> 32) pick_bin<true>(st, d, shift);
+        else pick_bin<false>(st, d, shift);
+    }
     if (tid == 0) *st.done = 0;
 }
 
@@ -3866,7 +3876,7 @@ void launch_delta(const Doms &D, int64_t n_cells, const double *f_new, const dou
     hipLaunchKernelGGL(k_select_init<Doms>, dim3(grid1((int64_t)D.n * kSelBins)), dim3(256), 0, stream, D, n_cells, st);
     for (int pass = 0; pass < kSelPasses; ++pass) {
         hipLaunchKernelGGL(k_select<Doms>, dim3(std::min(blocks, (unsigned)n_cu)), dim3(kSelThreads), 0, stream, D, n_cells, f_old, pass, st);
-        if (D.n > kSelPickWaves) hipLaunchKernelGGL(k_pick, dim3(grid1(D.n, 4)), dim3(256), 0, stream, D.n, pass, st);
+        if (D.n > kSelPickWaves) hipLaunchKernelGGL(k_pick, dim3(grid1(D.n, 4)), dim3(256), 0, stream, D.n, n_cells, pass, st);
     }
     hipLaunchKernelGGL(k_delta<Doms>, dim3(blocks), dim3(kSelThreads), 0, stream, D, n_cells, f_new, f_old, st);
 }
