@@ -877,3 +877,54 @@ def test_pool_of_pairs_used_up(T, orc):
         g, j, st = gpu_sweep(T, P, prec, thin=True, targets=tg, theta=theta)
         assert st.overflow == 0 and st.nodes_accepted == n * len(ls)
         compare(g, j, np.repeat(f0, n), np.repeat(i0, n), tol, name=f"pool prec {prec}")
+
+
+@pytest.mark.parametrize("nside,n_radial,waves", [(2, 64, 4), (4, 32, 4), (4, 32, 0), (8, 32, 8)])
+def test_fp64_rays_in_passes_with_many_sources(T, orc, nside, n_radial, waves):
+    """FP64 with emission on nearly every ray: more than a target has buffers
+    for, so they are mapped and integrated in several passes."""
+    P = W.small_lognormal(16, n_src=400, seed=150, nside=nside, n_radial=n_radial)
+    tg = np.sort(np.random.default_rng(151).choice(P.total_cells(), 1100, replace=False))
+    f0, i0 = orc_sweep(orc, P, thin=True, targets=tg)
+    g0, j0, st = gpu_sweep(T, P, T.TR_FP64, thin=True, targets=tg, launch=(waves, 0, 1, 0, 0))
+    assert st.buffer_in_lds == 3
+    compare(g0, j0, f0, i0, TOL64, name=f"N_side {nside} N_R {n_radial} waves {waves}")
+    f1, i1 = orc_sweep(orc, P, f_prev=np.repeat(1e9, P.total_cells()), targets=tg)
+    g1, j1, _ = gpu_sweep(T, P, T.TR_FP64, f_prev=np.repeat(1e9, P.total_cells()), targets=tg, launch=(waves, 0, 1, 0, 0))
+    compare(g1, j1, f1, i1, TOL64, name=f"N_side {nside} N_R {n_radial} waves {waves} absorbing")
+
+
+@pytest.mark.parametrize("nside,sub", [(1, 4), (8, 3)])
+def test_nodes_outside_the_table(T, orc, nside, sub):
+    """24 cells a side pad the octree: some nodes are partial, which no table
+    holds, and the walk classifies them."""
+    P = W.small_lognormal(24, n_src=5, seed=160, nside=nside, n_radial=20)
+    P.params.subsample = sub
+    tg = np.sort(np.random.default_rng(161).choice(P.total_cells(), 150, replace=False))
+    f0, i0 = orc_sweep(orc, P, thin=True, targets=tg)
+    for prec, tol in ((T.TR_FP64, TOL64), (T.TR_FP32C, TOL32)):
+        g0, j0, st = gpu_sweep(T, P, prec, thin=True, targets=tg)
+        assert 0.5 * st.nodes_accepted < st.nodes_tabulated < st.nodes_accepted
+        compare(g0, j0, f0, i0, tol, name=f"partial nodes N_side {nside} prec {prec}")
+
+
+def test_delta_beyond_32_bits(T):
+    """One domain of 8.6e9 cells (69 GB, the two fields the same memory a cell
+    apart): counts of 2^32 cells and more.  The lower median is the second
+    value, so the largest change is from it to the third."""
+    sizes, values = (4_100_000_000, 4_200_000_000, 300_000_000), (1e-300, 1.0, 4.0)
+    n = sum(sizes)
+    if torch.cuda.mem_get_info()[0] < 8 * n + (8 << 30):
+        pytest.skip("needs 77 GB of free device memory")
+    f = torch.empty(n + 1, dtype=torch.float64, device="cuda")
+    at = 0
+    for m, v in zip(sizes, values):
+        f[at:at + m] = v
+        at += m
+    f[n] = values[2]
+    out = torch.zeros(1, dtype=torch.float64, device="cuda")
+    T.delta_noalloc(f[1:], f, np.array([0, n]), out)
+    got = out.item()
+    del f
+    torch.cuda.empty_cache()
+    assert got == 3.0   # 0.75 with the third value as the median, 1e300 with the first
