@@ -2525,11 +2525,11 @@ struct SelectState {
 template <typename Doms>
 __global__ void k_select_init(Doms D, int64_t n_cells, SelectState st)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < D.n * kSelBins) st.hist[i] = 0;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < (int64_t)D.n * kSelBins) st.hist[i] = 0;
     if (i == 0) *st.done = 0;
     if (i < D.n) {
-        const int64_t n = (i + 1 < D.n ? D.begin(i + 1) : n_cells) - D.begin(i);
+        const int64_t n = (i + 1 < D.n ? D.begin((int)i + 1) : n_cells) - D.begin((int)i);
         st.rank[i] = (unsigned long long)((n - 1) / 2);   // lower median
         st.prefix[i] = 0ull;
         st.dmax[i] = 0ull;
@@ -2640,7 +2640,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(Doms D, int64_t n_cells,
                 v += h[kSelCopies * i + q];
                 h[kSelCopies * i + q] = 0;
             }
-            if (v) atomicAdd(&st.hist[d * kSelBins + i], v);
+            if (v) atomicAdd(&st.hist[(size_t)d * kSelBins + i], v);
         }
         __syncthreads();
         lo = end;
@@ -3479,7 +3479,7 @@ float guard_tolerance(int nside) { return 1e-5f * std::max(2.0f, (float)nside); 
 // about 50 nodes of each of the middle ratios), so that the table has paid for
 // itself within about two sweeps, at least 65536 and at most 16 million (theta
 // 0.5 needs 1.8 million at r = 16 and 14.7 million at r = 32, 0.4 to 0.6 GB,
-// which takes the walks of 128^3 from 55 to 33 ms, built in 5 ms; r = 64 would take 8 times
+// which takes the walks of 128^3 from 55 to 33 ms, built in 8 ms (k_atab twice); r = 64 would take 8 times
 // that for under 1% of the nodes).
 tr_status build_angular_table(tr_ctx *c)
 {
