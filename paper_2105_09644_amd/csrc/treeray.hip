@@ -781,8 +781,9 @@ __device__ double integrate_ray_wave(const RayRows<Real> &R, int k, const double
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
         if (live[h]) s += ph[h] * drcp(rp[h] * rp[h]);
-        // emission rows kept in device memory are left zero for the next target
-        if (clear_eps && ep[h] > 0.0) R.eps(k, lane + 64 * h) = (Real)0;
+        // emission rows kept in device memory are left zero for the next target (a bracket weight
+        // that rounds to less than nothing leaves a negative entry)
+        if (clear_eps && ep[h] != 0.0) R.eps(k, lane + 64 * h) = (Real)0;
     }
     return wave_sum(s);
 }

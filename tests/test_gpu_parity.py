@@ -928,3 +928,32 @@ def test_delta_beyond_32_bits(T):
     del f
     torch.cuda.empty_cache()
     assert got == 3.0   # 0.75 with the third value as the median, 1e300 with the first
+
+
+@pytest.mark.parametrize("integration", [1, 2, 3, 6])
+def test_emission_rows_left_zero(T, integration):
+    """Emission rows in device memory are zero for the next target also where a
+    source lies exactly on an evaluation point and the weight of the next
+    point rounds to a negative value: a domain with faint sources beside one
+    with bright ones is as it is alone.  9 x 8 root-block diagonals and 37
+    points put 72 (i/36)^2 on whole cells."""
+    P0 = W.small_lognormal(8, n_src=1, seed=1, nside=4, n_radial=37)
+    nroot, rb = (1, 4, 8), P0.domains[0].root_block_cm
+    dom = W.Domain(nroot=nroot, root_block_cm=rb)
+    n, rng = dom.n_cells(), np.random.default_rng(5)
+
+    def centres(k):
+        return (np.floor(rng.uniform(0, 1, (k, 3)) * 8 * np.array(nroot)) + 0.5) * (rb / 8)
+
+    bright, faint = (centres(40), np.full(40, 1e49)), (centres(2), np.full(2, 1e36))
+    flux = []
+    for srcs in ([faint], [bright, faint]):
+        P = W.Problem("rows", [dom] * len(srcs), [np.full(n, 1.0)] * len(srcs), [s[0] for s in srcs],
+                      [s[1] for s in srcs], P0.params)
+        tg = np.random.default_rng(6).permutation(P.total_cells())
+        f, _, st = gpu_sweep(T, P, T.TR_FP32C, thin=True, targets=tg, launch=(4, 0, 0, integration, 2), theta=0.0)
+        assert st.buffer_in_lds == 2
+        g = np.empty_like(f)
+        g[tg] = f
+        flux.append(g[-n:])
+    np.testing.assert_allclose(flux[1], flux[0], rtol=1e-3)
