@@ -1392,7 +1392,9 @@ __device__ void mark_nodes(const SweepArgs &a, unsigned long long *emask, int ew
 // (by buffer) is marked here.
 // LDSBUF false (buffers in device memory): a lane per point of a pair, the
 // points of 64 pairs laid end to end: neighbouring lanes add to neighbouring
-// points, so an atomic instruction touches a few cache lines and not 64.
+// points, so an atomic instruction touches a few cache lines and not 64 (W_p
+// emission, every ray with a buffer: 48^3 N_side 2 FP64 50.6 ms, a lane per pair
+// 104.8; 32^3 N_side 4 with 100 points 35.7 / 153.6, FP32C 29.1 / 158.9).
 template <typename Real, int ATOMIC, bool LDSBUF, bool KV, bool CLASSIFY>
 __device__ void map_nodes(const SweepArgs &a, const RayRows<Real> &R, const unsigned *rinfo, unsigned long long *cmask,
                           int ew, const int *per, const Real *rt, int nr, Real rc_inv, Real rcoef, int n,
@@ -2362,7 +2364,11 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_cas_fallback(SweepArgs 
 }
 
 // Ray buffers in LDS, marks and ray numbers in device memory (4, 8 and 16
-// waves; FP32 buffers by compare-and-swap)
+// waves; FP32 buffers by compare-and-swap).  Bound as k_sweep is, by the mapping;
+// the marks (a few atomics and 12 to 20 B a ray and target) stay in L2.  1000 targets
+// of 24^3, 4 sources: N_side 32 with 48 points FP32C 0.70 ms, FP64 1.47 ms (44.4 and
+// 89.9 with passes over fixed pixel ranges, marks in LDS), 300 targets at N_side 64 0.90
+// and 1.97 ms (84.5 and 171).
 template <typename Real, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_wide(SweepArgs a)
 {
@@ -2375,7 +2381,8 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_sweep_wide_fallback(SweepArgs
     sweep_body<Real, WAVES, true, true, false, sizeof(Real) == 4, true>(a);
 }
 
-// both in device memory (8 waves)
+// both in device memory (8 waves): bound by the adds to L2.  The same at N_side 32, W_p
+// emission (every ray has a buffer): FP32C 9.0 ms, FP64 13.3 ms.
 template <typename Real, bool KV>
 __global__ __launch_bounds__(512, 4) void k_sweep_wide_mem(SweepArgs a)
 {
@@ -2477,14 +2484,14 @@ __global__ __launch_bounds__(256) void k_atab(AtabGeom G, int ns, int s, float g
 // bits of neighbouring values are mostly equal, and lanes that meet on a bin
 // are served one by one); the last block to finish picks every domain's bin.
 // 8M cells of 7 domains: 1316 us with 8 bits a pass, a lookup per cell and a
-// launch for every pick, 151 us now (189 us with 32 bins by lane in the pick; then two
+// launch for every pick, 147 us now (189 us with 32 bins by lane in the pick; then two
 // blocks a compute unit took 223 us and 512 threads a block 195 us: each block's fence
 // writes an L2 back).
 // ---------------------------------------------------------------------------
 constexpr int kSelBits = 11, kSelBins = 1 << kSelBits, kSelPasses = 6, kSelCopies = 4, kSelThreads = 1024;
 // The picks by the last block up to a domain a wave, beyond that in a launch of
 // their own: with the last block alone 512 domains of 512 cells took 4.2 ms and 64
-// of 4096 0.60 ms, now 0.15 and 0.10 ms; 16 domains have no more picks than the
+// of 4096 0.60 ms, now 0.15 and 0.09 ms; 16 domains have no more picks than the
 // block has waves, and a launch after each of the six passes would cost more
 constexpr int kSelPickWaves = kSelThreads / 64;
 __host__ __device__ inline int select_shift(int pass) { return pass < 5 ? 64 - kSelBits * (pass + 1) : 0; }
@@ -2560,8 +2567,8 @@ __device__ inline unsigned long long wave_total(unsigned v, unsigned long long &
 
 // The bin of domain d that holds its median, by a wave: 32 rows of 64 bins (whole
 // cache lines, which other blocks wrote: four bins a lane took 8M cells of 7
-// domains from 160 to 205 us), the row by the rows' totals, the bin by a scan of
-// the row.  Leaves the histogram zero.
+// domains from 160 to 205 us; a row at a time 151, now 147), the row by the totals of pairs of rows, the bin by a
+// scan of the row.  Leaves the histogram zero.
 template <bool BIG>
 __device__ inline void pick_bin(const SelectState &st, int d, int shift)
 {
@@ -2573,20 +2580,29 @@ __device__ inline void pick_bin(const SelectState &st, int d, int shift)
     for (int q = 0; q < kRows; ++q) v[q] = __hip_atomic_load(&hd[64 * q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned long long k = st.rank[d], below;
     int row = 0;
-    unsigned mine = 0;
+    unsigned mine = 0, next = 0;
     bool found = false;
 #pragma unroll
-    for (int q = 0; q < kRows; ++q) {
+    for (int q = 0; q < kRows; q += 2) {   // two rows at a time
         hd[64 * q] = 0;
-        const unsigned long long tot = wave_total<BIG>(v[q], below);
+        hd[64 * q + 64] = 0;
+        const unsigned long long tot = BIG ? wave_total<BIG>(v[q], below) + wave_total<BIG>(v[q + 1], below)
+                                           : wave_total<BIG>(v[q] + v[q + 1], below);
         if (!found) {   // (uniform)
             found = k < tot;
             row = q;
             mine = v[q];
+            next = v[q + 1];
             k -= found ? 0 : tot;
         }
     }
-    (void)wave_total<BIG>(mine, below);
+    const unsigned long long tot = wave_total<BIG>(mine, below);
+    if (k >= tot) {   // (uniform)
+        k -= tot;
+        ++row;
+        mine = next;
+        (void)wave_total<BIG>(mine, below);
+    }
     if (k >= below && k < below + mine) {   // one lane
         st.rank[d] = k - below;
         st.prefix[d] |= (unsigned long long)(64 * row + lane) << shift;
